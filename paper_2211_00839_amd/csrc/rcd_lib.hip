@@ -19,6 +19,7 @@
 #include "recompute_kernels.hip"
 #include "incremental_kernels.hip"
 #include "multi_wg_kernels.hip"
+#include "resident_kernels.hip"
 
 static_assert(RCD_KMAX == RCD_MAX_K, "public and internal block limits differ");
 
@@ -372,6 +373,7 @@ struct Lane {
     // several workgroups per class for the step loops of large classes (incremental gains, graph cut)
     bool mw = false;
     int mw_wgs = 0;
+    resident::Choice res = {};  // the step loop with the gains in registers, where every class of the group fits one
     unsigned mw_epoch = 0;      // exchanges the earlier launches of this call may have used
     long long mw_spin_ticks = 200000000;   // bound of a grid-barrier wait, 100 MHz ticks (2 s)
     dim3 update_grid;
@@ -418,6 +420,8 @@ struct Lane {
         if (mw)
             hipLaunchKernelGGL(rcd_k_gc_steps_mw, dim3(mw_wgs), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, (const RcdWg *)g->wgmap_dev, gc_max_steps, epoch0, mw_spin_ticks);
+        else if (res.gc)
+            hipLaunchKernelGGL(res.gc, dim3(ncls), dim3(res.threads), 0, stream, g->classes_dev, g->plan_dev, gc_max_steps);
         else
             hipLaunchKernelGGL(rcd_k_gc_steps, dim3(ncls), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, gc_max_steps);
@@ -527,6 +531,12 @@ struct Lane {
                     for (RcdClass &c : g->host) { c.mw = 0; c.mwseg = 0; }
                 }
             }
+        }
+        res = resident::Choice{};
+        if (graph_cut && !mw && env_int("RCD_RESIDENT", 1, 0, 1) != 0) {
+            int max_ld = 0;
+            for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
+            res = resident::choose(max_ld, first.K);
         }
         if (graph_cut) {
             // initial marginal values = column sums of S without the diagonal

@@ -1,0 +1,78 @@
+"""The step loops that keep a class's gains in registers against the loops that keep them in memory (RCD_RESIDENT = 0),
+which the oracle referees in the other files: same assignment, order and objectives to the bit, at the edges of every
+variant's sample and block range, with zero quotas and samples left over, with groups of identical samples (exact
+ties), with the state stored and loaded again in mid-run, and for classes of unequal size in one launch."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rcd():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: there is no CPU path")
+    import paper_2211_00839_amd as m
+
+    m.load_library()
+    return m
+
+
+def both(monkeypatch, call):
+    got = []
+    for on in ("1", "0"):
+        monkeypatch.setenv("RCD_RESIDENT", on)
+        assign, order, obj = call()
+        got.append((assign.cpu().numpy(), order.cpu().numpy(), obj))
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
+    return got[0]
+
+
+def quotas(rng, n, K, full):
+    w = rng.integers(0, 5, K) + (np.arange(K) == rng.integers(0, K))
+    cap = (n * w // w.sum()).astype(np.int64)
+    if full:
+        cap[int(np.argmax(cap))] += n - int(cap.sum())
+    return cap
+
+
+# (n, K): both sides of every variant's last sample, and its most blocks
+EDGES = [(1, 1), (2, 3), (255, 2), (256, 16), (257, 5), (512, 16), (513, 3), (1024, 16), (1025, 8), (2048, 16), (2049, 4),
+         (3072, 8), (3072, 16), (3073, 12), (4096, 9), (4097, 4), (5120, 8), (5121, 8), (6144, 5), (6145, 3), (8192, 4),
+         (8193, 2)]
+
+
+@pytest.mark.parametrize("n,K", EDGES)
+def test_graph_cut_class(rcd, monkeypatch, n, K):
+    print(f"resident graph cut n={n} K={K}", flush=True)
+    rng = np.random.default_rng(n + K)
+    X = torch.from_numpy(si.make_class(seed=n, n=n, d=64)).cuda()
+    if n % 2 == 0:
+        X[n // 2:] = X[: n - n // 2]                     # every sample twice: exact ties
+    S = rcd.similarity(X, 64.0)
+    cap = quotas(rng, n, K, full=K % 2 == 0)
+    # a few steps per launch as well: the state goes through memory in between
+    for steps in ("", "7") if n < 1000 else ("", "1000"):
+        monkeypatch.setenv("RCD_GC_STEPS", steps)
+        assign, order, _ = both(monkeypatch, lambda: rcd.partition_class_graph_cut(S, cap))
+        assert np.bincount(assign[assign >= 0], minlength=K).tolist() == cap.tolist()
+        assert sorted(order[order >= 0].tolist()) == list(range(int(cap.sum())))
+
+
+@pytest.mark.parametrize("sizes,K", [((1, 700, 256, 90), 4), ((2500, 300, 40), 8), ((4000, 5000), 3), ((300,) * 40, 16)])
+def test_graph_cut_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
+    print(f"resident graph cut classes {sizes[:4]} K={K}", flush=True)
+    rng = np.random.default_rng(K)
+    X = np.concatenate([si.make_class(seed=i, n=n, d=32) for i, n in enumerate(sizes)])
+    labels = np.concatenate([np.full(n, i, np.int32) for i, n in enumerate(sizes)])
+    at = rng.permutation(len(X))
+    Xd, yd = torch.from_numpy(X[at]).cuda(), torch.from_numpy(labels[at]).cuda()
+    r = rng.integers(1, 5, K).astype(np.int32)
+    _, full = rcd.dataset_workspace_bytes(len(X), len(sizes), max(sizes), K, rcd.MODE_STORED)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    both(monkeypatch, lambda: rcd.partition_dataset(Xd, yd, len(sizes), r, 32.0, workspace=ws, graph_cut=True))
