@@ -38,7 +38,7 @@ namespace {
 
 thread_local char g_hip_err[320] = "";
 thread_local int64_t g_stats[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-thread_local RcdPlan *g_pinned = nullptr;   // per lane 2 progress slots of 2 plan headers, pinned, never freed
+thread_local RcdPlan *g_pinned = nullptr;   // RCD_PINNED_BYTES of pinned memory, freed by rcd_release
 // optional per-kernel timing (HIP events between the launches of a round)
 thread_local int g_profile_on = 0;
 thread_local double g_prof[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // ms: steps, sweep, apply; rounds; similarity ms
@@ -110,6 +110,9 @@ constexpr int RCD_MAX_CLASSES = 8192;
 constexpr int RCD_MAX_LANES = 4;
 // Progress records (and their events) a lane cycles through: batches in flight + 1 at most.
 constexpr int RCD_SLOTS = 4;
+
+// The calling thread's pinned buffer: the progress records while step loops run, before that the class sizes.
+constexpr size_t RCD_PINNED_BYTES = (RCD_MAX_CLASSES + 64) * 4;
 
 size_t plan_area_bytes(int ncls) { return up256(2 * sizeof(RcdPlan) + 2 * (size_t)(ncls + 1) * 4); }
 
@@ -333,7 +336,8 @@ int ensure_pinned()
 {
     if (!g_pinned) {
         void *p = nullptr;
-        HIP_TRY(hipHostMalloc(&p, RCD_MAX_LANES * RCD_SLOTS * 2 * sizeof(RcdPlan), hipHostMallocDefault));
+        static_assert(RCD_PINNED_BYTES >= RCD_MAX_LANES * RCD_SLOTS * 2 * sizeof(RcdPlan), "progress records");
+        HIP_TRY(hipHostMalloc(&p, RCD_PINNED_BYTES, hipHostMallocDefault));
         g_pinned = (RcdPlan *)p;
     }
     return RCD_OK;
@@ -1058,6 +1062,30 @@ int check_common(int64_t n, int K)
 
 void reset_stats() { memset(g_stats, 0, sizeof g_stats); }
 
+// Stable counting sort of the sample indices by label: index_dev gets the classes end to end, count_host their sizes.
+// count_dev: L ints and a plan header (whose `bad` a label out of range raises), read back in one piece; nothing of the
+// sort waits for the host.  Waits for the stream.
+int split_by_label(const int32_t *labels, int64_t N, int L, int allow_unassigned, int nchunks, int32_t *chunk_hist,
+                   int32_t *count_dev, int32_t *index_dev, int32_t *count_host, hipStream_t stream)
+{
+    RCD_TRY(ensure_pinned());
+    RcdPlan *flag = reinterpret_cast<RcdPlan *>(count_dev + L);
+    const size_t back = ((size_t)L + sizeof(RcdPlan) / 4) * 4;
+    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
+    hipLaunchKernelGGL(split::k_hist, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels, (long long)N, L, chunk_hist,
+                       flag, allow_unassigned);
+    hipLaunchKernelGGL(split::k_scan, dim3((unsigned)L), dim3(256), 0, stream, chunk_hist, nchunks, L, count_dev);
+    HIP_TRY(hipMemcpyAsync(g_pinned, count_dev, back, hipMemcpyDeviceToHost, stream));
+    hipLaunchKernelGGL(split::k_scatter, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels, (long long)N, L,
+                       split::bits_of(L), (const int32_t *)chunk_hist, (const int32_t *)count_dev, index_dev);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(stream));
+    memcpy(count_host, g_pinned, (size_t)L * 4);
+    RcdPlan seen;
+    memcpy(&seen, reinterpret_cast<const int32_t *>(g_pinned) + L, sizeof seen);
+    return seen.bad ? RCD_ERR_BAD_LABEL : RCD_OK;
+}
+
 } // namespace
 
 // ===========================================================================
@@ -1222,36 +1250,19 @@ int rcd_worker_shards(const int32_t *assign_dev, int64_t N, int K, int32_t *inde
     if (!assign_dev || !index_dev) return RCD_ERR_INVALID_ARG;
     RCD_TRY(check_workspace(workspace_dev, workspace_bytes, rcd_worker_shards_workspace_bytes(N, K)));
     // the class split's stable counting sort, keyed by worker instead of label
-    const int nchunks = (int)((N + split::CHUNK - 1) / split::CHUNK);
     Carver cv(workspace_dev, workspace_bytes);
+    const int nchunks = (int)((N + split::CHUNK - 1) / split::CHUNK);
     int32_t *chunk_hist = cv.take<int32_t>((size_t)nchunks * K);
-    int32_t *count_dev = cv.take<int32_t>((size_t)K);
-    int32_t *offset_dev = cv.take<int32_t>((size_t)K);
-    RcdPlan *flag = reinterpret_cast<RcdPlan *>(cv.take<char>(sizeof(RcdPlan)));
+    int32_t *count_dev = cv.take<int32_t>((size_t)K + sizeof(RcdPlan) / 4);
     if (cv.fail) return RCD_ERR_WORKSPACE;
-    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
-    hipLaunchKernelGGL(split::k_hist, dim3(nchunks), dim3(64), (size_t)K * 4, stream, assign_dev, (long long)N, K,
-                       chunk_hist, flag, 1);
-    hipLaunchKernelGGL(split::k_scan, dim3((K + 255) / 256), dim3(256), 0, stream, chunk_hist, nchunks, K, count_dev);
-    HIP_TRY(hipGetLastError());
-    std::vector<int32_t> count(K), offset(K);
-    RcdPlan flag_host;
-    HIP_TRY(hipMemcpyAsync(count.data(), count_dev, sizeof(int32_t) * K, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(&flag_host, flag, sizeof flag_host, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    if (flag_host.bad) return RCD_ERR_BAD_LABEL;
-    int32_t run = 0;
+    std::vector<int32_t> count(K);
+    RCD_TRY(split_by_label(assign_dev, N, K, 1, nchunks, chunk_hist, count_dev, index_dev, count.data(), stream));
+    int64_t run = 0;
     for (int k = 0; k < K; ++k) {
-        offset[k] = run;
         offset_host[k] = run;
         run += count[k];
     }
     offset_host[K] = run;
-    HIP_TRY(hipMemcpyAsync(offset_dev, offset.data(), sizeof(int32_t) * K, hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(split::k_scatter, dim3(nchunks), dim3(64), (size_t)K * 4, stream, assign_dev, (long long)N, K,
-                       (const int32_t *)chunk_hist, (const int32_t *)offset_dev, index_dev);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(stream));
     return RCD_OK;
 }
 
@@ -1525,32 +1536,16 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
     Carver cv(workspace_dev, workspace_bytes);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) != 0) return RCD_ERR_WORKSPACE;
     int32_t *idx = cv.take<int32_t>((size_t)N);
-    int32_t *class_count = cv.take<int32_t>((size_t)L);
-    int32_t *class_offset = cv.take<int32_t>((size_t)L);
+    int32_t *class_count = cv.take<int32_t>((size_t)L + sizeof(RcdPlan) / 4);
     int32_t *chunk_hist = cv.take<int32_t>((size_t)nchunks * L);
-    RcdPlan *flag = reinterpret_cast<RcdPlan *>(cv.take<char>(sizeof(RcdPlan)));
     if (cv.fail) return RCD_ERR_WORKSPACE;
-    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
-    hipLaunchKernelGGL(split::k_hist, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels_dev, (long long)N, L,
-                       chunk_hist, flag, 0);
-    hipLaunchKernelGGL(split::k_scan, dim3((L + 255) / 256), dim3(256), 0, stream, chunk_hist, nchunks, L,
-                       class_count);
-    HIP_TRY(hipGetLastError());
     std::vector<int32_t> count(L), offset(L);
-    RcdPlan flag_host;
-    HIP_TRY(hipMemcpyAsync(count.data(), class_count, sizeof(int32_t) * L, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipMemcpyAsync(&flag_host, flag, sizeof flag_host, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    if (flag_host.bad) return RCD_ERR_BAD_LABEL;
+    RCD_TRY(split_by_label(labels_dev, N, L, 0, nchunks, chunk_hist, class_count, idx, count.data(), stream));
     int32_t run = 0;
     for (int l = 0; l < L; ++l) {
         offset[l] = run;
         run += count[l];
     }
-    HIP_TRY(hipMemcpyAsync(class_offset, offset.data(), sizeof(int32_t) * L, hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(split::k_scatter, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels_dev, (long long)N, L,
-                       (const int32_t *)chunk_hist, (const int32_t *)class_offset, idx);
-    HIP_TRY(hipGetLastError());
 
     // ---- quotas (same r for every class: the extras land on the same workers)
     std::vector<int64_t> cap((size_t)L * K);

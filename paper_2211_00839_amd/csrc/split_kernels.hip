@@ -35,50 +35,97 @@ k_hist(const int32_t *__restrict__ labels, long long N, int L, int32_t *__restri
     if (bad) plan->bad = 1;
 }
 
-// Per class: exclusive prefix of chunk_hist over chunks (in place) and the class total.
+// Per class: exclusive prefix of chunk_hist over chunks (in place) and the class total.  One workgroup per class, a run
+// of consecutive chunks per thread: with one thread per class walking all its chunks, a million labels in eight classes
+// took 128 us, 977 dependent trips to memory; here the chunks are read side by side (4.6 us).
 __global__ void __launch_bounds__(256)
 k_scan(int32_t *__restrict__ chunk_hist, int nchunks, int L, int32_t *__restrict__ class_count)
 {
-    const int l = blockIdx.x * 256 + threadIdx.x;
-    if (l >= L) return;
-    int run = 0;
-    for (int c = 0; c < nchunks; ++c) {
+    __shared__ int s_wave[4];
+    const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (nchunks + 255) / 256;
+    const int c0 = min(tid * per, nchunks), c1 = min(c0 + per, nchunks);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += chunk_hist[(size_t)c * L + l];
+    int incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+    }
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int w = 0; w < wave; ++w) run += s_wave[w];
+    for (int c = c0; c < c1; ++c) {
         const int v = chunk_hist[(size_t)c * L + l];
         chunk_hist[(size_t)c * L + l] = run;
         run += v;
     }
-    class_count[l] = run;
+    if (tid == 255) class_count[l] = run;
 }
 
-// idx[class_offset[l] + rank] = i, rank = number of earlier samples with label l.
+// idx[offset of class l + rank] = i, rank = number of earlier samples with label l, the classes end to end in order.
+// One wave per chunk; every lane finds the lanes of its group of 64 that share its label with one ballot per bit of a
+// label (label_bits of them), so a group costs the same however many labels it holds (a loop over the distinct labels with
+// two barriers in each took 25 us for a million labels of eight classes, this takes 8.0), and all labels of the chunk are
+// on their way at once.
 __global__ void __launch_bounds__(64)
-k_scatter(const int32_t *__restrict__ labels, long long N, int L, const int32_t *__restrict__ chunk_base,
-          const int32_t *__restrict__ class_offset, int32_t *__restrict__ idx)
+k_scatter(const int32_t *__restrict__ labels, long long N, int L, int label_bits, const int32_t *__restrict__ chunk_base,
+          const int32_t *__restrict__ class_count, int32_t *__restrict__ idx)
 {
     extern __shared__ int s_cnt[];
     const int lane = threadIdx.x;
-    for (int l = lane; l < L; l += 64) s_cnt[l] = chunk_base[(size_t)blockIdx.x * L + l] + class_offset[l];
-    __syncthreads();
     const long long base = (long long)blockIdx.x * CHUNK;
-    for (int g = 0; g < CHUNK / 64; ++g) {
+    constexpr int GROUPS = CHUNK / 64;
+    int lab[GROUPS];
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
         const long long i = base + g * 64 + lane;
-        const int lab = i < N ? labels[i] : -1;
-        unsigned long long todo = __ballot(lab >= 0 && lab < L);
-        while (todo) {
-            const int leader = __ffsll((long long)todo) - 1;
-            const int l0 = __shfl(lab, leader);
-            const unsigned long long same = __ballot(lab == l0);
-            const int start = s_cnt[l0];
-            __syncthreads();
-            if (lab == l0) {
-                const int rank = __popcll(same & ((1ull << lane) - 1ull));
-                idx[start + rank] = (int32_t)i;
-            }
-            if (lane == leader) s_cnt[l0] = start + __popcll(same);
-            __syncthreads();
-            todo &= ~same;
-        }
+        lab[g] = i < N ? labels[i] : -1;
     }
+    // where this chunk's first sample of each class goes
+    int before = 0;
+    for (int l0 = 0; l0 < L; l0 += 64) {
+        const int l = l0 + lane;
+        const int c = l < L ? class_count[l] : 0;
+        int incl = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int up = __shfl_up(incl, off);
+            if (lane >= off) incl += up;
+        }
+        if (l < L) s_cnt[l] = before + incl - c + chunk_base[(size_t)blockIdx.x * L + l];
+        before += __shfl(incl, 63);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+        const int l = lab[g];
+        const bool has = l >= 0 && l < L;
+        unsigned long long same = __ballot(has);
+        for (int b = 0; b < label_bits; ++b) {
+            const unsigned long long ones = __ballot((l >> b) & 1);
+            same &= ((l >> b) & 1) ? ones : ~ones;
+        }
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        int start = 0;
+        if (has) {
+            start = s_cnt[l];
+            idx[start + rank] = (int32_t)(base + g * 64 + lane);
+        }
+        __syncthreads();           // every lane has read the counters (one wave: no wait, the order of the LDS accesses)
+        if (has && rank == 0) s_cnt[l] = start + __popcll(same);
+        __syncthreads();
+    }
+}
+
+// bits that tell the labels 0 .. L-1 apart
+inline int bits_of(int L)
+{
+    int b = 0;
+    while ((1ll << b) < L) ++b;
+    return b;
 }
 
 } // namespace split

@@ -93,3 +93,36 @@ def test_batch_sizes_match_the_oracle():
         m.batch_sizes(0, [1, 2])
     with pytest.raises(m.RcdError):
         m.batch_sizes(8, [1, 0])
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 7, 16])
+@pytest.mark.parametrize("N", [1, 64, 1023, 1024, 1025, 65536, 262144, 262145, 600001])
+def test_shards_at_the_edges_of_chunks_and_scan_runs(rcd, N, K):
+    # chunks of 1024 samples, one thread of the scan per run of ceil(chunks / 256) of them
+    print(f"shards edges N={N} K={K}", flush=True)
+    assign = np.random.default_rng(N + K).integers(-1, K, N).astype(np.int32)
+    index, offset = rcd.worker_shards(torch.from_numpy(assign).cuda(), K)
+    order = np.argsort(assign, kind="stable")
+    left = int(np.sum(assign < 0))
+    assert offset.tolist() == [int(np.sum((assign >= 0) & (assign < k))) for k in range(K + 1)]
+    assert np.array_equal(index.cpu().numpy()[: N - left], order[left:])
+
+
+@pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 129, 1000])
+def test_class_split_of_many_classes(rcd, L):
+    # every class is its own run of steps: the order inside a class counts 0, 1, ... and the quotas are the class's own
+    print(f"class split L={L}", flush=True)
+    rng = np.random.default_rng(L)
+    N = 3 * L + 1500
+    labels = rng.integers(0, L, N).astype(np.int32)
+    X = torch.from_numpy(rng.standard_normal((N, 8)).astype(np.float32)).cuda()
+    r = np.array([1, 2, 2], np.int32)
+    most = int(np.bincount(labels).max())
+    _, full = rcd.dataset_workspace_bytes(N, L, most, 3, rcd.MODE_STORED)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    assign, order, _ = rcd.partition_dataset(X, torch.from_numpy(labels).cuda(), L, r, 8.0, workspace=ws, graph_cut=True)
+    assign, order = assign.cpu().numpy(), order.cpu().numpy()
+    for c in range(L):
+        at = np.flatnonzero(labels == c)
+        assert sorted(order[at].tolist()) == list(range(len(at)))
+        assert np.array_equal(np.bincount(assign[at], minlength=3), rcd.quota(len(at), r))
