@@ -126,10 +126,10 @@ int rcd_quota(int64_t n_l, const int32_t *r_host, int K, int64_t *cap_host);
  * One gain sweep (the GreedyStep of Algorithm 1 evaluated for every candidate
  * and every block at once, facility-location f of Section 4):
  *     gains[k*n + v] = sum_{j<n} max(0, S[j*ld_s + v] - cur[k*n + j])
- * for all k < K, v < n, accumulated in fp32 in a fixed order.  S must be
- * symmetric with entries in [0,1]; cur_dev is K x n (coverage vectors).
- * Exposed so that the kernel can be checked and timed on its own; the
- * partition entry points run the same kernel on their internal state.
+ * for all k < K, v < n, accumulated in a fixed order (fp32 within chunks of
+ * rows, the chunks in double).  S must be symmetric with entries in [0,1];
+ * cur_dev is K x n (coverage vectors).  S is read once, in place; the partition
+ * entry points evaluate the same sums on their own copy, candidate by candidate.
  * Synchronises `stream` before returning.
  */
 int rcd_gain_sweep(const float *S_dev, int64_t ld_s, int64_t n, int K, const float *cur_dev,

@@ -1370,41 +1370,35 @@ int rcd_gain_sweep(const float *S_dev, int64_t ld_s, int64_t n, int K, const flo
     if (!S_dev || !cur_dev || !gains_dev || ld_s < n) return RCD_ERR_INVALID_ARG;
     if (!stored_supported(n, K)) return RCD_ERR_UNSUPPORTED;
     RCD_TRY(check_workspace(workspace_dev, workspace_bytes, rcd_class_workspace_bytes(n, K, RCD_MODE_STORED)));
-    Carver cv(workspace_dev, workspace_bytes);
-    Group g;
-    if (!carve_group_fixed(cv, g, 1, K)) return RCD_ERR_WORKSPACE;
-    g.host.resize(1);
-    std::vector<int64_t> cap(K, 0);
-    RcdClass &c = g.host[0];
-    if (!carve_class(cv, c, n, K, cap.data(), true)) return RCD_ERR_WORKSPACE;
-    c.assign_out = nullptr;
-    c.nneed = K;
-    for (int k = 0; k < K; ++k) c.need[k] = k;
-    stored_chunks(c.ld, K, &c.C, &c.rpc);
     RCD_TRY(sweep_setup());
-    const std::vector<RcdWg> map =
-        deal_workgroups(g.host, env_int("RCD_SWEEP_WGS", 2 * cu_count(), 1, RCD_MAX_SWEEP_WGS));
-    RcdPlan plan[2];
-    memset(plan, 0, sizeof plan);
-    plan[0].ncls = plan[1].ncls = 1;
-    HIP_TRY(hipMemcpyAsync(g.plan_dev, plan, sizeof plan, hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(g.classes_dev, g.host.data(), sizeof(RcdClass), hipMemcpyHostToDevice, stream));
-    HIP_TRY(hipMemcpyAsync(g.wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
-    hipLaunchKernelGGL(rcd_k_copy_check, dim3((unsigned)(c.ld / 32), (unsigned)((n + 31) / 32)), dim3(256), 0, stream,
-                       S_dev, (long long)ld_s, c.M, c.ld, c.n, g.plan_dev);
-    hipLaunchKernelGGL(rcd_k_init, dim3(64, 1), dim3(256), 0, stream, (const RcdClass *)g.classes_dev);
-    hipLaunchKernelGGL(rcd_k_import_cur, dim3((unsigned)((n + 255) / 256), K), dim3(256), 0, stream,
-                       (const RcdClass *)g.classes_dev, cur_dev);
-    hipLaunchKernelGGL(rcd_k_sweep_rows, dim3((unsigned)map.size()), dim3(RCD_SWEEP_THREADS), RCD_SWEEP_LDS_FLOATS * 4,
-                       stream, (const RcdClass *)g.classes_dev, (const RcdWg *)g.wgmap_dev);
-    hipLaunchKernelGGL(rcd_k_export_gains, dim3((unsigned)((n + 255) / 256), K), dim3(256), 0, stream,
-                       (const RcdClass *)g.classes_dev, gains_dev);
+    RCD_TRY(ensure_pinned());
+    Carver cv(workspace_dev, workspace_bytes);
+    RcdPlan *flag = cv.take<RcdPlan>(1);
+    // Chunks of rows: about three workgroups per compute unit, at least 32 rows each (8 per wave); no more than the
+    // workspace's matrix has room for (n / K of them; a class of fewer than 32 K samples has the partial sums' 32).
+    const int tiles = (int)((n + 255) / 256);
+    int chunks = std::max(1, 3 * cu_count() / tiles);
+    chunks = (int)std::min<int64_t>(chunks, (n + 31) / 32);
+    chunks = std::max(1, (int)std::min<int64_t>(chunks, std::max<int64_t>(RCD_CMAX, n / K)));
+    const int rows = (int)((n + chunks - 1) / chunks);
+    chunks = (int)((n + rows - 1) / rows);
+    float *part = cv.take<float>((size_t)chunks * K * n);
+    if (cv.fail) return RCD_ERR_WORKSPACE;
+    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
+    const bool vec = (reinterpret_cast<uintptr_t>(S_dev) & 15) == 0 && ld_s % 4 == 0;
+    void (*kernel)(const float *, long long, int, int, const float *, int, float *, RcdPlan *) =
+        K <= 2 ? (vec ? rcd_k_gain_columns<2, true> : rcd_k_gain_columns<2, false>)
+        : K <= 4 ? (vec ? rcd_k_gain_columns<4, true> : rcd_k_gain_columns<4, false>)
+        : K <= 8 ? (vec ? rcd_k_gain_columns<8, true> : rcd_k_gain_columns<8, false>)
+                 : (vec ? rcd_k_gain_columns<16, true> : rcd_k_gain_columns<16, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles, (unsigned)chunks), dim3(256), 0, stream, S_dev, (long long)ld_s, (int)n,
+                       K, cur_dev, rows, part, flag);
+    hipLaunchKernelGGL(rcd_k_gain_total, dim3((unsigned)((n + 255) / 256), (unsigned)K), dim3(256), 0, stream,
+                       (const float *)part, chunks, (int)n, K, gains_dev);
     HIP_TRY(hipGetLastError());
-    RcdPlan back;
-    HIP_TRY(hipMemcpyAsync(&back, &g.plan_dev[0], sizeof back, hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipMemcpyAsync(g_pinned, flag, sizeof(RcdPlan), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    if (back.bad) return RCD_ERR_BAD_SIMILARITY;
-    return RCD_OK;
+    return g_pinned->bad ? RCD_ERR_BAD_SIMILARITY : RCD_OK;
 }
 
 // objective: 0 = facility location, 1 = graph cut (stored S only)

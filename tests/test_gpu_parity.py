@@ -176,6 +176,30 @@ def test_gain_sweep_matches_oracle_rows(rcd, n, K):
     assert np.allclose(g[0], S.astype(np.float64).sum(axis=0), rtol=1e-5)
 
 
+@pytest.mark.parametrize("K", [1, 2, 3, 5, 9, 16])
+@pytest.mark.parametrize("n,pitch,shift", [(1, 1, 0), (3, 4, 0), (31, 31, 0), (32, 36, 0), (255, 256, 0), (256, 256, 0),
+                                           (257, 260, 0), (257, 259, 1), (1000, 1004, 0), (1025, 1025, 0), (2050, 2052, 2)])
+def test_gain_sweep_columns_of_any_matrix(rcd, n, K, pitch, shift):
+    # column sums of the matrix as it lies there: pitched, not 16-byte aligned, not symmetric, -0 among the entries
+    print(f"gain sweep columns n={n} K={K} pitch={pitch} shift={shift}", flush=True)
+    rng = np.random.default_rng(n + K)
+    flat = torch.from_numpy(rng.random(n * pitch + shift).astype(np.float32)).cuda()
+    S = flat[shift:].view(n, pitch)[:, :n]
+    S[0, n // 2] = -0.0
+    cur = torch.from_numpy(rng.random((K, n)).astype(np.float32)).cuda()
+    cur[0] = 0.0
+    g = rcd.gain_sweep(S, cur).cpu().numpy()
+    ref = torch.stack([(S.double() - c[:, None]).clamp_(min=0).sum(0) for c in cur.double()]).cpu().numpy()
+    # fp32 sums of non-negative terms: at most 3 + 8 + n / 256 + 3 additions deep, each rounding by 2^-24, and one per term
+    depth = 15 + n / 256
+    assert np.all(np.abs(g - ref) <= depth * 2.0 ** -24 * ref + 1e-30)
+    for bad in (float("nan"), 1.0000001, -1e-6):
+        S[n - 1, n // 3] = bad
+        with pytest.raises(rcd.RcdError) as e:
+            rcd.gain_sweep(S, cur)
+        assert e.value.status == 7
+
+
 def test_gain_sweep_rejects_similarity_outside_unit_interval(rcd):
     S = mixture_S(5, 40)
     S[3, 4] = 1.5
