@@ -360,6 +360,13 @@ bool multi_wg_wanted(int64_t max_n)
     return min_n > 0 && max_n >= min_n;
 }
 
+// Does the incremental route keep the gains of these classes in registers?  Where they fit, and as long as the device has a
+// compute unit to spare for every class's helpers.
+bool resident_incremental(int max_ld, int K, int ncls)
+{
+    return env_int("RCD_RESIDENT", 1, 0, 1) != 0 && 2 * ncls <= cu_count() && resident::choose_inc(max_ld, K).inc != nullptr;
+}
+
 // One group of classes on one stream.  The host keeps a few batches of rounds
 // queued ahead of the device: start(), then enqueue_batch() while fewer than
 // `depth` batches are unread and poll() to read the oldest one's progress record,
@@ -378,6 +385,7 @@ struct Lane {
     bool mw = false;
     int mw_wgs = 0;
     resident::Choice res = {};  // the step loop with the gains in registers, where every class of the group fits one
+    int res_helpers = 0, res_launch = 0;   // incremental route: helper workgroups per class, launches so far
     unsigned mw_epoch = 0;      // exchanges the earlier launches of this call may have used
     long long mw_spin_ticks = 200000000;   // bound of a grid-barrier wait, 100 MHz ticks (2 s)
     dim3 update_grid;
@@ -412,6 +420,9 @@ struct Lane {
             hipLaunchKernelGGL(rcd_k_inc_steps_mw, dim3(mw_wgs), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, (const RcdWg *)g->wgmap_dev, inc_max_steps, inc_small_bytes, epoch0,
                                mw_spin_ticks);
+        else if (res.inc)
+            hipLaunchKernelGGL(res.inc, dim3(ncls * (1 + res_helpers)), dim3(res.threads), 0, stream, g->classes_dev,
+                               g->plan_dev, ncls, inc_max_steps, inc_small_bytes, ++res_launch, mw_spin_ticks);
         else
             hipLaunchKernelGGL(rcd_k_inc_steps, dim3(ncls), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, inc_max_steps, inc_small_bytes);
@@ -537,10 +548,23 @@ struct Lane {
             }
         }
         res = resident::Choice{};
-        if (graph_cut && !mw && env_int("RCD_RESIDENT", 1, 0, 1) != 0) {
+        if ((graph_cut || incremental) && !mw) {
             int max_ld = 0;
             for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
-            res = resident::choose(max_ld, first.K);
+            if (graph_cut) {
+                if (env_int("RCD_RESIDENT", 1, 0, 1) != 0) res = resident::choose_gc(max_ld, first.K);
+            } else if (resident_incremental(max_ld, first.K, ncls)) {
+                res = resident::choose_inc(max_ld, first.K);
+                res_helpers = std::max(1, std::min(env_int("RCD_HELPERS", 12, 1, 64), cu_count() / ncls - 1));
+                res_launch = 0;
+                mw_spin_ticks = (long long)env_int("RCD_MW_SPIN_MS", 2000, 0, 60000) * 100000LL;
+                inc_max_steps = env_int("RCD_INC_STEPS", 1 << 20, 1, 1 << 20);
+                // Lists of more than twelve rows are handed out (measured, 8 to 24 rows: 500 samples 3.4 .. 3.6 ms, 1500 6.1 ..
+                // 5.8, 5000 25.1 .. 25.4; 1 or 50 rows cost 2 to 20 % more).
+                inc_small_bytes = env_int("RCD_INC_SMALL_KB", (48 * max_ld + 1023) / 1024, 1, 1 << 20) * 1024;
+                rounds = env_int("RCD_ROUNDS_PER_BATCH", 1, 1, 1024);
+                max_batches = (max_total + 2) / rounds + 3 + RCD_SLOTS;
+            }
         }
         if (graph_cut) {
             // initial marginal values = column sums of S without the diagonal
@@ -642,6 +666,8 @@ struct Lane {
             else if (recompute)
                 hipLaunchKernelGGL(round_rc, dim3(items_ub), dim3(256), round_rc_lds, stream, g->classes_dev, g->plan_dev,
                                    buf);
+            else if (incremental && res.inc)
+                ;   // the step launch's own helpers apply the long lists
             else if (incremental)
             {
                 hipLaunchKernelGGL(rcd_k_inc_update, update_grid, dim3(256), 0, stream, (const RcdClass *)g->classes_dev,
@@ -1624,6 +1650,8 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
             // step loops that share classes among workgroups wait for one another inside the kernel: such
             // launches stay on one stream, so that two of them never compete for the compute units
             if (stored && (objective == 1 || incremental || auto_incremental) && multi_wg_wanted(max_count)) nl = 1;
+            // and so does a launch whose classes have helpers: it runs from start to end without the host
+            if (stored && (incremental || auto_incremental) && resident_incremental(pitch_of(max_count), K, live)) nl = 1;
             std::vector<Group> lanes(nl);
             {
                 std::vector<double> cum(live + 1, 0.0);

@@ -64,9 +64,32 @@ def test_graph_cut_class(rcd, monkeypatch, n, K):
         assert sorted(order[order >= 0].tolist()) == list(range(int(cap.sum())))
 
 
+INC_EDGES = [(1, 1), (2, 3), (255, 2), (256, 16), (257, 5), (512, 16), (513, 3), (1024, 16), (1025, 8), (2048, 16), (2049, 4),
+             (3072, 8), (3072, 16), (3073, 3), (5120, 4), (5120, 8), (5121, 8), (6144, 5), (6145, 3), (8192, 4)]
+
+
+@pytest.mark.parametrize("n,K", INC_EDGES)
+def test_incremental_class(rcd, monkeypatch, n, K):
+    print(f"resident incremental n={n} K={K}", flush=True)
+    rng = np.random.default_rng(n + K)
+    X = torch.from_numpy(si.make_class(seed=n, n=n, d=64)).cuda()
+    if n % 2 == 0:
+        X[n // 2:] = X[: n - n // 2]                     # every sample twice: exact ties
+    S = rcd.similarity(X, 64.0)
+    cap = quotas(rng, n, K, full=K % 2 == 0)
+    # as it is; every list of more than four rows handed out, to one helper; the state through memory in mid-run
+    for env in ({}, {"RCD_INC_SMALL_KB": "1", "RCD_HELPERS": "1"}, {"RCD_INC_STEPS": "7" if n < 1000 else "1000"}):
+        with monkeypatch.context() as m:
+            for k, v in env.items():
+                m.setenv(k, v)
+            assign, order, _ = both(m, lambda: rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL))
+        assert np.bincount(assign[assign >= 0], minlength=K).tolist() == cap.tolist()
+        assert sorted(order[order >= 0].tolist()) == list(range(int(cap.sum())))
+
+
 @pytest.mark.parametrize("sizes,K", [((1, 700, 256, 90), 4), ((2500, 300, 40), 8), ((4000, 5000), 3), ((300,) * 40, 16)])
-def test_graph_cut_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
-    print(f"resident graph cut classes {sizes[:4]} K={K}", flush=True)
+def test_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
+    print(f"resident classes {sizes[:4]} K={K}", flush=True)
     rng = np.random.default_rng(K)
     X = np.concatenate([si.make_class(seed=i, n=n, d=32) for i, n in enumerate(sizes)])
     labels = np.concatenate([np.full(n, i, np.int32) for i, n in enumerate(sizes)])
@@ -76,3 +99,15 @@ def test_graph_cut_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
     _, full = rcd.dataset_workspace_bytes(len(X), len(sizes), max(sizes), K, rcd.MODE_STORED)
     ws = torch.empty(full, dtype=torch.uint8, device="cuda")
     both(monkeypatch, lambda: rcd.partition_dataset(Xd, yd, len(sizes), r, 32.0, workspace=ws, graph_cut=True))
+    both(monkeypatch, lambda: rcd.partition_dataset(Xd, yd, len(sizes), r, 32.0, rcd.MODE_INCREMENTAL, ws))
+
+
+def test_classes_without_room_for_helpers(rcd, monkeypatch):
+    # more classes than half the compute units: two lanes of 70 classes with helpers, of 140 without
+    for L in (140, 280):
+        rng = np.random.default_rng(L)
+        X = torch.from_numpy(rng.standard_normal((40 * L, 16)).astype(np.float32)).cuda()
+        y = torch.from_numpy(rng.permutation(np.repeat(np.arange(L), 40)).astype(np.int32)).cuda()
+        _, full = rcd.dataset_workspace_bytes(40 * L, L, 60, 4, rcd.MODE_STORED)
+        ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+        both(monkeypatch, lambda: rcd.partition_dataset(X, y, L, [1, 2, 3, 1], 16.0, rcd.MODE_INCREMENTAL, ws))
