@@ -888,6 +888,26 @@ bool mirror_wanted(int dt, int64_t d, int64_t tiles_in_flight)
     return (dt == RCD_F32 ? 32 : 2) * d >= 2048 && sweep_setup() == RCD_OK && tiles_in_flight > cu_count();
 }
 
+// How often `tiles` workgroups fill the device, one per compute unit.
+int64_t tile_rounds(int64_t tiles)
+{
+    const int64_t cus = cu_count();
+    return (tiles + cus - 1) / cus;
+}
+
+// Similarity builds of few tiles: rounds = how often the 256 x 256 tiles fill the device, pieces = number of 64 x 64 ones.
+// In units of a 32 x 32 piece's multiplies, a round of big tiles takes 16 and a round of small ones 2, or 8 for
+// bf16, whose operands memory cannot feed at the multiply rate.  Measured, small against big in us: fp32 d = 512 500
+// samples 22 / 129, 1000 24 / 130, 2000 84 / 133, 3000 174 / 134; d = 64 1000 12 / 31, 3000 39 / 33; bf16 d = 2048 1000
+// 42 / 52, 1500 103 / 59; d = 512 1000 15 / 26, 1500 31 / 26.
+bool few_tiles_pay(int dt, int64_t rounds, int64_t pieces)
+{
+    const int mode = env_int("RCD_SIM_FEW", 1, 0, 2);
+    if (mode != 1) return mode == 2;
+    if (sweep_setup() != RCD_OK) return false;
+    return (dt == RCD_F32 ? 2 : 8) * tile_rounds(pieces) < 16 * rounds;
+}
+
 int launch_similarity(const void *X, int dt, int64_t n, int64_t d, int64_t ldx, const int32_t *row_index,
                       float sigma2, float *S, int64_t ld_s, int ncols_pad, float *sq, hipStream_t stream)
 {
@@ -909,6 +929,18 @@ int launch_similarity(const void *X, int dt, int64_t n, int64_t d, int64_t ldx, 
     // build only leaves more of them idle).
     // RCD_SIM_MIRROR: 0 never, 1 by that rule, 2 whenever the layout allows.
     const int64_t tm = (n + sim::pipe::TM - 1) / sim::pipe::TM;
+    const int64_t small_rows = (n + sim::few::TILE - 1) / sim::few::TILE, small_cols = (ncols_pad + sim::few::TILE - 1) / sim::few::TILE;
+    if (few_tiles_pay(dt, tile_rounds(tm * tm), small_rows * small_cols)) {
+        const dim3 grid((unsigned)small_cols, (unsigned)small_rows);
+        if (dt == RCD_F32)
+            hipLaunchKernelGGL(sim::k_gram_rbf_few<float>, grid, dim3(256), 0, stream, (const float *)X, (long long)ldx, row_index,
+                               (int)n, (int)d, (const float *)sq, exp_scale, S, (long long)ld_s, ncols_pad);
+        else
+            hipLaunchKernelGGL(sim::k_gram_rbf_few<__bf16>, grid, dim3(256), 0, stream, (const __bf16 *)X, (long long)ldx,
+                               row_index, (int)n, (int)d, (const float *)sq, exp_scale, S, (long long)ld_s, ncols_pad);
+        HIP_TRY(hipGetLastError());
+        return RCD_OK;
+    }
     const bool mirror = fast && mirror_wanted(dt, d, tm * tm) &&
                         (ncols_pad + sim::pipe::TN - 1) / sim::pipe::TN == tm &&
                         (reinterpret_cast<uintptr_t>(S) & 15) == 0 && ld_s % 4 == 0;
@@ -993,19 +1025,25 @@ int launch_similarity_batch(const void *X, int dt, int64_t d, int64_t ldx, float
                             const std::vector<SimRequest> &req, hipStream_t stream)
 {
     if (req.empty()) return RCD_OK;
-    if (!rows_fit_fast_path(X, dt, d, ldx) || req.size() == 1 || env_int("RCD_SIM_BATCH", 1, 0, 1) == 0) {
+    // (rows that do not fit the fast path would take a launch per class: 100 classes of 500 samples, d = 300 fp32,
+    // 6.2 ms in launches of big tiles, 0.39 ms in two of small ones)
+    const bool fast = rows_fit_fast_path(X, dt, d, ldx);
+    int64_t all_tiles = 0, pieces = 0, launches = 0;
+    for (const SimRequest &q : req) {
+        const int64_t tm = (q.n + sim::pipe::TM - 1) / sim::pipe::TM;
+        all_tiles += tm * tm;
+        launches += tile_rounds(tm * tm);
+        pieces += ((q.n + sim::few::TILE - 1) / sim::few::TILE) * ((q.ld + sim::few::TILE - 1) / sim::few::TILE);
+    }
+    const bool few = few_tiles_pay(dt, fast ? tile_rounds(all_tiles) : launches, pieces);
+    if ((!few && !fast) || req.size() == 1 || env_int("RCD_SIM_BATCH", 1, 0, 1) == 0) {
         for (const SimRequest &q : req)
             RCD_TRY(launch_similarity(X, dt, q.n, d, ldx, q.row_index, sigma2, q.S, q.ld, (int)q.ld, q.sq, stream));
         return RCD_OK;
     }
     RCD_TRY(fast_setup());
     const float exp_scale = (float)(-1.4426950408889634 / (2.0 * (double)sigma2));
-    int64_t all_tiles = 0;
-    for (const SimRequest &q : req) {
-        const int64_t tm = (q.n + sim::pipe::TM - 1) / sim::pipe::TM;
-        all_tiles += tm * tm;
-    }
-    const bool mirror = mirror_wanted(dt, d, all_tiles);
+    const bool mirror = !few && mirror_wanted(dt, d, all_tiles);
     for (size_t first = 0; first < req.size(); first += sim::SIM_BATCH) {
         sim::SimBatch b;
         memset(&b, 0, sizeof b);
@@ -1014,7 +1052,8 @@ int launch_similarity_batch(const void *X, int dt, int64_t d, int64_t ldx, float
         for (int j = 0; j < b.njobs; ++j) {
             const SimRequest &q = req[first + j];
             const int64_t tm = (q.n + sim::pipe::TM - 1) / sim::pipe::TM;
-            const int64_t tiles = mirror ? ((tm + 1) / 2) * (tm + 1) : tm * ((q.ld + sim::pipe::TN - 1) / sim::pipe::TN);
+            const int64_t tiles = few ? ((q.n + sim::few::TILE - 1) / sim::few::TILE) * ((q.ld + sim::few::TILE - 1) / sim::few::TILE)
+                                  : mirror ? ((tm + 1) / 2) * (tm + 1) : tm * ((q.ld + sim::pipe::TN - 1) / sim::pipe::TN);
             sim::SimJob &job = b.job[j];
             job.row_index = q.row_index;
             job.sq = q.sq;
@@ -1032,7 +1071,10 @@ int launch_similarity_batch(const void *X, int dt, int64_t d, int64_t ldx, float
         if (dt == RCD_F32) {
             hipLaunchKernelGGL(sim::k_row_norms_batch<float>, dim3((unsigned)row_wgs), dim3(256), 0, stream,
                                (const float *)X, (long long)ldx, (int)d, b);
-            if (mirror)
+            if (few)
+                hipLaunchKernelGGL(sim::k_gram_rbf_few_batch<float>, dim3((unsigned)wgs), dim3(256), 0, stream, (const float *)X,
+                                   (long long)ldx, (int)d, exp_scale, b);
+            else if (mirror)
                 hipLaunchKernelGGL((sim::k_gram_rbf_fast_batch<float, sim::EPI_RBF_MIRROR>), dim3((unsigned)wgs),
                                    dim3(sim::THREADS), sim::pipe::LDS_BYTES, stream, (const float *)X, (long long)ldx,
                                    (int)d, exp_scale, b);
@@ -1043,7 +1085,10 @@ int launch_similarity_batch(const void *X, int dt, int64_t d, int64_t ldx, float
         } else {
             hipLaunchKernelGGL(sim::k_row_norms_batch<__bf16>, dim3((unsigned)row_wgs), dim3(256), 0, stream,
                                (const __bf16 *)X, (long long)ldx, (int)d, b);
-            if (mirror)
+            if (few)
+                hipLaunchKernelGGL(sim::k_gram_rbf_few_batch<__bf16>, dim3((unsigned)wgs), dim3(256), 0, stream, (const __bf16 *)X,
+                                   (long long)ldx, (int)d, exp_scale, b);
+            else if (mirror)
                 hipLaunchKernelGGL((sim::k_gram_rbf_fast_batch<__bf16, sim::EPI_RBF_MIRROR>), dim3((unsigned)wgs),
                                    dim3(sim::THREADS), sim::pipe::LDS_BYTES, stream, (const __bf16 *)X, (long long)ldx,
                                    (int)d, exp_scale, b);

@@ -863,6 +863,132 @@ k_gram_rbf(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ r
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few tiles.  A 256 x 256 tile keeps a compute unit busy for d / 2 x 1024 cycles (fp32; 110 us at d = 512) however many
+// others stand idle: a class of 500 samples is four of them.  Here a wave takes 32 x 32 (a workgroup 64 x 64), sixteen times
+// as many pieces for the chip to share, and feeds the matrix cores straight from global memory: lane l reads 16 bytes
+// of row l & 31, lanes 32-63 the second half of a 32-byte k group, which is how the multiply wants them; 8 groups are
+// multiplied while the next 8 are on their way, no LDS, no barrier.  An operand row is read by n / 32 waves instead of n / 256
+// workgroups, which L2 can feed at the fp32 rate and at a quarter of the bf16 one: that is the limit of few_tiles_pay().
+// Any alignment and any d; k in the order of the other kernels, hence the same bits.
+// ---------------------------------------------------------------------------
+namespace few {
+
+constexpr int TILE = 64;       // rows and columns of a workgroup
+constexpr int U = 8;           // 32-byte k groups per batch
+
+template <typename T> struct Batch { uint4 a[U], b[U]; };
+
+template <typename T>
+__device__ __forceinline__ void mma(f32x16 &acc, const Batch<T> &f)
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if constexpr (sizeof(T) == 2) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.a[u]), __builtin_bit_cast(bf16x8, f.b[u]),
+                                                          acc, 0, 0, 0);
+        } else {
+            const f32x4 va = __builtin_bit_cast(f32x4, f.a[u]), vb = __builtin_bit_cast(f32x4, f.b[u]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[e], vb[e], acc, 0, 0, 0);
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void tile(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ row_index, int n, int d,
+                                     const float *__restrict__ sq, float exp_scale, float *__restrict__ S, long long lds_out,
+                                     int ncols_pad, int ti, int tj)
+{
+    constexpr int E = CHUNK / (int)sizeof(T), G = 2 * E;       // elements per lane and per k group
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = ti * TILE + (wave >> 1) * 32, j0 = tj * TILE + (wave & 1) * 32;
+    if (i0 >= n || j0 >= ncols_pad) return;
+    const int r = lane & 31, half = (lane >> 5) * E;
+    const int gi = min(i0 + r, n - 1), gj = min(j0 + r, n - 1);
+    const int ra = row_index ? row_index[gi] : gi, rb = row_index ? row_index[gj] : gj;
+    const bool vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0) && ((ldx * (long long)sizeof(T)) % 16 == 0);
+    const T *pa = X + (size_t)ra * ldx + half, *pb = X + (size_t)rb * ldx + half;
+    f32x16 acc;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) acc[x] = 0.f;
+    auto load = [&](Batch<T> &f, int g) {           // whole groups, aligned rows
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            f.a[u] = *reinterpret_cast<const uint4 *>(pa + (g + u) * G);
+            f.b[u] = *reinterpret_cast<const uint4 *>(pb + (g + u) * G);
+        }
+    };
+    const int groups = (d + G - 1) / G, whole = vec_ok ? d / G : 0;
+    int g = 0;
+    if (whole >= U) {
+        Batch<T> f0, f1;
+        load(f0, 0);
+        for (; g + 3 * U <= whole; g += 2 * U) {
+            load(f1, g + U);
+            mma<T>(acc, f0);
+            load(f0, g + 2 * U);
+            mma<T>(acc, f1);
+        }
+        if (g + 2 * U <= whole) {
+            load(f1, g + U);
+            mma<T>(acc, f0);
+            mma<T>(acc, f1);
+            g += 2 * U;
+        } else {
+            mma<T>(acc, f0);
+            g += U;
+        }
+    }
+    for (; g < groups; g += U) {
+        Batch<T> f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            f.a[u] = load_chunk<T>(X, ldx, ra, (g + u) * G + half, d, vec_ok);
+            f.b[u] = load_chunk<T>(X, ldx, rb, (g + u) * G + half, d, vec_ok);
+        }
+        mma<T>(acc, f);
+    }
+    // a lane holds column lane & 31, rows 8 q + 4 (lane >> 5) + e
+    const int j = j0 + r;
+    const float sqj = j < n ? sq[j] * exp_scale : 0.f, scale2 = -2.f * exp_scale;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = i0 + q * 8 + (lane >> 5) * 4 + e;
+            if (i < n && j < ncols_pad) {
+                float v = rbf_value(acc[q * 4 + e], sq[i] * exp_scale, sqj, scale2);
+                if (i == j) v = 1.f;
+                S[(size_t)i * lds_out + j] = j < n ? v : 0.f;
+            }
+        }
+}
+
+} // namespace few
+
+// grid = (column tiles, row tiles) of 64
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_gram_rbf_few(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ row_index, int n, int d,
+               const float *__restrict__ sq, float exp_scale, float *__restrict__ S, long long lds_out, int ncols_pad)
+{
+    few::tile<T>(X, ldx, row_index, n, d, sq, exp_scale, S, lds_out, ncols_pad, (int)blockIdx.y, (int)blockIdx.x);
+}
+
+// The same for the classes of a data set: job j owns workgroups wg_begin .. wg_begin + wg_count, row tiles first.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_gram_rbf_few_batch(const T *__restrict__ X, long long ldx, int d, float exp_scale, const SimBatch b)
+{
+    const int wg = (int)blockIdx.x;
+    int j = 0;
+    while (j + 1 < b.njobs && wg >= b.job[j + 1].wg_begin) ++j;
+    const SimJob &q = b.job[j];
+    const int t = wg - q.wg_begin, rows = (q.n + few::TILE - 1) / few::TILE;
+    few::tile<T>(X, ldx, q.row_index, q.n, d, q.sq, exp_scale, q.S, q.lds_out, q.ncols_pad, t % rows, t / rows);
+}
+
 // out[0] = sum of count doubles, in a fixed order: one workgroup, strided partial sums, then a tree.
 __global__ void __launch_bounds__(1024)
 k_sum_doubles(const double *__restrict__ v, long long count, double *__restrict__ out)
