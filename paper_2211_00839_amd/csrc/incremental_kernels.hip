@@ -140,14 +140,27 @@ rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int f
                 acc[3] += inc_term(m[u].w, cn[u], co[u]);
             }
         }
-        for (; e < nd; ++e) {
-            const int j = dl[e];
-            const float cn = cur[j], co = dold[e];
-            const f32x4 m = __builtin_nontemporal_load((gcf32x4)(M + (size_t)j * ld));
-            acc[0] += inc_term(m.x, cn, co);
-            acc[1] += inc_term(m.y, cn, co);
-            acc[2] += inc_term(m.z, cn, co);
-            acc[3] += inc_term(m.w, cn, co);
+        if (e < nd) {
+            // the segment's last rows, all of them asked for before the first is used (one at a time, up to seven trips to
+            // memory per segment, and a shared class has up to 32 segments)
+            f32x4 m[U - 1];
+            float cn[U - 1], co[U - 1];
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (e + u < nd) {
+                    const int j = dl[e + u];
+                    cn[u] = cur[j];
+                    co[u] = dold[e + u];
+                    m[u] = __builtin_nontemporal_load((gcf32x4)(M + (size_t)j * ld));
+                }
+#pragma unroll
+            for (int u = 0; u < U - 1; ++u)
+                if (e + u < nd) {
+                    acc[0] += inc_term(m[u].x, cn[u], co[u]);
+                    acc[1] += inc_term(m[u].y, cn[u], co[u]);
+                    acc[2] += inc_term(m[u].z, cn[u], co[u]);
+                    acc[3] += inc_term(m[u].w, cn[u], co[u]);
+                }
         }
     }
     double *g = inc_gains(st) + (size_t)k * ld + v0 + lane * 4;
