@@ -95,6 +95,7 @@ def test_batch_sizes_match_the_oracle():
         m.batch_sizes(8, [1, 0])
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("K", [1, 2, 3, 7, 16])
 @pytest.mark.parametrize("N", [1, 64, 1023, 1024, 1025, 65536, 262144, 262145, 600001])
 def test_shards_at_the_edges_of_chunks_and_scan_runs(rcd, N, K):
@@ -108,6 +109,7 @@ def test_shards_at_the_edges_of_chunks_and_scan_runs(rcd, N, K):
     assert np.array_equal(index.cpu().numpy()[: N - left], order[left:])
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("L", [1, 2, 63, 64, 65, 129, 1000])
 def test_class_split_of_many_classes(rcd, L):
     # every class is its own run of steps: the order inside a class counts 0, 1, ... and the quotas are the class's own
