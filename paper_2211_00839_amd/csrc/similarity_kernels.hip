@@ -895,19 +895,13 @@ __device__ __forceinline__ void mma(f32x16 &acc, const Batch<T> &f)
     }
 }
 
+// Products of a wave's 32 x 32 rows: lane l brings row ra of the one operand and row rb of the other for row and column
+// l & 31 of the piece, the next U groups of k are under way while the matrix cores work on the last ones.
 template <typename T>
-__device__ __forceinline__ void tile(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ row_index, int n, int d,
-                                     const float *__restrict__ sq, float exp_scale, float *__restrict__ S, long long lds_out,
-                                     int ncols_pad, int ti, int tj)
+__device__ __forceinline__ f32x16 product(const T *__restrict__ X, long long ldx, int ra, int rb, int d, bool vec_ok)
 {
     constexpr int E = CHUNK / (int)sizeof(T), G = 2 * E;       // elements per lane and per k group
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i0 = ti * TILE + (wave >> 1) * 32, j0 = tj * TILE + (wave & 1) * 32;
-    if (i0 >= n || j0 >= ncols_pad) return;
-    const int r = lane & 31, half = (lane >> 5) * E;
-    const int gi = min(i0 + r, n - 1), gj = min(j0 + r, n - 1);
-    const int ra = row_index ? row_index[gi] : gi, rb = row_index ? row_index[gj] : gj;
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0) && ((ldx * (long long)sizeof(T)) % 16 == 0);
+    const int half = ((threadIdx.x & 63) >> 5) * E;
     const T *pa = X + (size_t)ra * ldx + half, *pb = X + (size_t)rb * ldx + half;
     f32x16 acc;
 #pragma unroll
@@ -949,6 +943,22 @@ __device__ __forceinline__ void tile(const T *__restrict__ X, long long ldx, con
         }
         mma<T>(acc, f);
     }
+    return acc;
+}
+
+template <typename T>
+__device__ __forceinline__ void tile(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ row_index, int n, int d,
+                                     const float *__restrict__ sq, float exp_scale, float *__restrict__ S, long long lds_out,
+                                     int ncols_pad, int ti, int tj)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = ti * TILE + (wave >> 1) * 32, j0 = tj * TILE + (wave & 1) * 32;
+    if (i0 >= n || j0 >= ncols_pad) return;
+    const int r = lane & 31;
+    const int gi = min(i0 + r, n - 1), gj = min(j0 + r, n - 1);
+    const int ra = row_index ? row_index[gi] : gi, rb = row_index ? row_index[gj] : gj;
+    const bool vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0) && ((ldx * (long long)sizeof(T)) % 16 == 0);
+    const f32x16 acc = product<T>(X, ldx, ra, rb, d, vec_ok);
     // a lane holds column lane & 31, rows 8 q + 4 (lane >> 5) + e
     const int j = j0 + r;
     const float sqj = j < n ? sq[j] * exp_scale : 0.f, scale2 = -2.f * exp_scale;

@@ -349,6 +349,24 @@ def test_recompute_route_works_on_the_bits_of_the_stored_similarity(rcd, dtype, 
         assert f[k] == float(S_gpu[:, v].astype(np.float64).sum()), (k, v)
 
 
+@pytest.mark.parametrize("dtype,n,d", [("f32", 33, 8), ("f32", 130, 60), ("f32", 64, 64), ("f32", 257, 72), ("f32", 500, 128),
+                                       ("f32", 97, 136), ("f32", 300, 192), ("f32", 129, 777), ("bf16", 33, 128),
+                                       ("bf16", 130, 144), ("bf16", 500, 256), ("bf16", 97, 272), ("bf16", 300, 520)])
+def test_recompute_coverage_columns_at_the_edges_of_their_loads(rcd, monkeypatch, dtype, n, d):
+    """The same equality where the coverage update's k loop has less than a batch of groups, exactly one, two and three
+    batches, a rest, and unaligned rows; classes that end inside a wave's 32 rows.  The matrix comes from big tiles."""
+    print(f"recompute columns, edges {dtype} n={n} d={d}", flush=True)
+    monkeypatch.setenv("RCD_SIM_FEW", "0")
+    X = si.make_class(seed=1900 + n, n=n, d=d, G=4, dtype=dtype)
+    K = 16
+    a, o, f = rcd.partition_class(X=dev(X), cap=np.ones(K, dtype=np.int64), sigma2=float(d))
+    a = a.cpu().numpy()
+    S_gpu = rcd.similarity(dev(X), float(d)).cpu().numpy()
+    for k in range(K):
+        v = int(np.flatnonzero(a == k)[0])
+        assert f[k] == float(S_gpu[:, v].astype(np.float64).sum()), (k, v)
+
+
 @pytest.mark.parametrize("dtype,n,d,r", [("f32", 600, 32, [1] * 16), ("bf16", 1000, 64, [3, 1, 2]),
                                          ("f32", 257, 96, [1, 1]), ("bf16", 90, 128, [1, 2, 1, 2, 1])])
 def test_class_greedy_recompute_fast_path_edges(rcd, dtype, n, d, r):
