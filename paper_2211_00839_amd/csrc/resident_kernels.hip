@@ -138,16 +138,26 @@ template <int NT_, int Q_, int KM_> struct Shape {
 struct Slot { unsigned hi, lo; int v, pad; };
 
 // What a wave knows about where it is.  Piece q of a lane starts at sample v0 + 128 q; pieces from nq on lie outside the
-// class's pitch (a piece is wholly in or out): their gains are INC_TAKEN, and what is read for them is not used.
+// class's pitch (a piece is wholly in or out): their gains are INC_TAKEN.  A row is read through at(): for a piece outside
+// the pitch that is the row's first 128 samples, so no read leaves the row (a class may be much smaller than the variant its
+// launch needs for the largest), and what is added to INC_TAKEN for them is finite and far below its last bit.
 template <typename S> struct Place {
     int lane, wave, nq;
     unsigned v0;
+    unsigned piece[S::Q];    // bytes from a row's start to piece q of this wave
     __device__ __forceinline__ void init(int ld)
     {
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         nq = min(max((ld - wave * S::WAVE) / 128, 0), S::Q);
         v0 = (unsigned)(wave * S::WAVE + lane * 2);
+#pragma unroll
+        for (int q = 0; q < S::Q; ++q) piece[q] = q < nq ? (unsigned)(wave * S::WAVE + 128 * q) * 4u : 0u;
+    }
+    // this lane's two samples of piece q in the row that starts `row` bytes into the buffer
+    __device__ __forceinline__ f32x2 at(__amdgpu_buffer_rsrc_t b, unsigned row, int q) const
+    {
+        return buffer_load2(b, (unsigned)lane * 8u, row + piece[q]);
     }
 };
 
@@ -411,7 +421,7 @@ rcd_k_gc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, 
         if (of[i] >= 0) apply(std::integral_constant<int, i>{});
         const unsigned row = (unsigned)(vstar * ld) * 4u;
 #pragma unroll
-        for (int q = 0; q < S::Q; ++q) m[i][q] = buffer_load2(M, pl.v0 * 4u, row + 512u * q);
+        for (int q = 0; q < S::Q; ++q) m[i][q] = pl.at(M, row, q);
         of[i] = js;
         strike<S>(G, vstar, pl);
         take(r, js, vstar, best, pl.lane);
@@ -689,7 +699,7 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
                         } else {
                             const unsigned row = (unsigned)(vstar * ld) * 4u;
 #pragma unroll
-                            for (int q = 0; q < Q; ++q) mp[u][q] = buffer_load2(M, pl.v0 * 4u, row + 512u * q);
+                            for (int q = 0; q < Q; ++q) mp[u][q] = pl.at(M, row, q);
                             strike<S>(G, vstar, pl);
                             take(r, js, vstar, best, lane);
                             busy |= 1u << js;
@@ -709,7 +719,7 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
                 if (u < B) {
                     const unsigned row = (unsigned)(pj[u] * ld) * 4u;
 #pragma unroll
-                    for (int q = 0; q < Q; ++q) c[u][q] = buffer_load2(cover, pl.v0 * 4u, row + 512u * q);
+                    for (int q = 0; q < Q; ++q) c[u][q] = pl.at(cover, row, q);
                 }
 #pragma unroll
             for (int u = 0; u < S::BM; ++u)
@@ -831,7 +841,7 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
                         } else {
                             const unsigned row = (unsigned)__builtin_amdgcn_readlane((int)row_of, e0 + i);
 #pragma unroll
-                            for (int q = 0; q < Q; ++q) m[i][q] = buffer_load2(M, pl.v0 * 4u, row + 512u * q);
+                            for (int q = 0; q < Q; ++q) m[i][q] = pl.at(M, row, q);
                         }
                     }
 #pragma unroll

@@ -87,7 +87,10 @@ def test_incremental_class(rcd, monkeypatch, n, K):
         assert sorted(order[order >= 0].tolist()) == list(range(int(cap.sum())))
 
 
-@pytest.mark.parametrize("sizes,K", [((1, 700, 256, 90), 4), ((2500, 300, 40), 8), ((4000, 5000), 3), ((300,) * 40, 16)])
+# (the later ones: classes far smaller than the variant that the largest one takes, so that whole pieces of a wave lie
+# outside their rows)
+@pytest.mark.parametrize("sizes,K", [((1, 700, 256, 90), 4), ((2500, 300, 40), 8), ((4000, 5000), 3), ((300,) * 40, 16),
+                                     ((5000, 40), 4), ((5000, 40), 1), ((8000, 60, 500), 3), ((12000, 50, 1), 2)])
 def test_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
     print(f"resident classes {sizes[:4]} K={K}", flush=True)
     rng = np.random.default_rng(K)
