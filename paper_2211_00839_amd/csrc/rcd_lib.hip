@@ -1177,7 +1177,8 @@ int split_by_label(const int32_t *labels, int64_t N, int L, int allow_unassigned
     hipLaunchKernelGGL(split::k_scan, dim3((unsigned)L), dim3(256), 0, stream, chunk_hist, nchunks, L, count_dev);
     HIP_TRY(hipMemcpyAsync(g_pinned, count_dev, back, hipMemcpyDeviceToHost, stream));
     hipLaunchKernelGGL(split::k_scatter, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels, (long long)N, L,
-                       split::bits_of(L), (const int32_t *)chunk_hist, (const int32_t *)count_dev, index_dev);
+                       split::bits_of(L), (const int32_t *)chunk_hist, (const int32_t *)count_dev, (const RcdPlan *)flag,
+                       index_dev);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(stream));
     memcpy(count_host, g_pinned, (size_t)L * 4);

@@ -69,12 +69,14 @@ k_scan(int32_t *__restrict__ chunk_hist, int nchunks, int L, int32_t *__restrict
 // One wave per chunk; every lane finds the lanes of its group of 64 that share its label with one ballot per bit of a
 // label (label_bits of them), so a group costs the same however many labels it holds (a loop over the distinct labels with
 // two barriers in each took 25 us for a million labels of eight classes, this takes 8.0), and all labels of the chunk are
-// on their way at once.
+// on their way at once.  A bad label anywhere (plan->bad, from k_hist) and nothing is written: the host reads that flag
+// only behind this launch.
 __global__ void __launch_bounds__(64)
 k_scatter(const int32_t *__restrict__ labels, long long N, int L, int label_bits, const int32_t *__restrict__ chunk_base,
-          const int32_t *__restrict__ class_count, int32_t *__restrict__ idx)
+          const int32_t *__restrict__ class_count, const RcdPlan *__restrict__ plan, int32_t *__restrict__ idx)
 {
     extern __shared__ int s_cnt[];
+    if (plan->bad) return;
     const int lane = threadIdx.x;
     const long long base = (long long)blockIdx.x * CHUNK;
     constexpr int GROUPS = CHUNK / 64;

@@ -78,6 +78,24 @@ def test_worker_shards_of_a_real_partition_and_errors(rcd):
     assert lib.rcd_worker_shards(None, 0, K, None, offp, None, 0, None) == 0 and off.tolist() == [0] * (K + 1)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,at,value", [(1, 0, 3), (5000, 4999, 3), (5000, 0, -2), (300000, 1025, 77)])
+def test_a_refused_assignment_leaves_the_lists_alone(rcd, N, at, value):
+    print(f"shards, refused N={N}", flush=True)
+    K = 3
+    a = np.random.default_rng(N).integers(-1, K, size=N).astype(np.int32)
+    a[at] = value
+    a = torch.from_numpy(a).cuda()
+    lib = rcd.load_library()
+    index = torch.full((N,), -7, dtype=torch.int32, device="cuda")
+    offset = np.full(K + 1, -7, dtype=np.int64)
+    size = lib.rcd_worker_shards_workspace_bytes(N, K)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    offp = offset.ctypes.data_as(ctypes.c_void_p)
+    assert lib.rcd_worker_shards(a.data_ptr(), N, K, index.data_ptr(), offp, ws.data_ptr(), size, None) == 2
+    assert bool((index == -7).all()) and offset.tolist() == [0] * (K + 1)
+
+
 def test_batch_sizes_match_the_oracle():
     import paper_2211_00839_amd as m
 
