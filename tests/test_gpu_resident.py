@@ -2,6 +2,8 @@
 which the oracle referees in the other files: same assignment, order and objectives to the bit, at the edges of every
 variant's sample and block range, with zero quotas and samples left over, with groups of identical samples (exact
 ties), with the state stored and loaded again in mid-run, and for classes of unequal size in one launch."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -114,3 +116,26 @@ def test_classes_without_room_for_helpers(rcd, monkeypatch):
         _, full = rcd.dataset_workspace_bytes(40 * L, L, 60, 4, rcd.MODE_STORED)
         ws = torch.empty(full, dtype=torch.uint8, device="cuda")
         both(monkeypatch, lambda: rcd.partition_dataset(X, y, L, [1, 2, 3, 1], 16.0, rcd.MODE_INCREMENTAL, ws))
+
+
+@pytest.mark.parametrize("route", ["incremental", "graph cut"])
+@pytest.mark.parametrize("n,bad", [(300, float("nan")), (3000, 1.5)])
+def test_no_step_is_taken_on_a_refused_matrix(rcd, route, n, bad):
+    print(f"refused matrix n={n} {route}", flush=True)
+    S = rcd.similarity(torch.from_numpy(si.make_class(seed=n, n=n, d=32)).cuda(), 32.0)
+    S[n - 1, n // 2] = bad
+    lib, K = rcd.load_library(), 3
+    cap, obj = rcd.quota(n, [1, 2, 1]), np.zeros(K)
+    assign = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    order = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    size = rcd.class_workspace_bytes(n, K, rcd.MODE_INCREMENTAL)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    capp, objp = cap.ctypes.data_as(ctypes.c_void_p), obj.ctypes.data_as(ctypes.c_void_p)
+    if route == "incremental":
+        status = lib.rcd_partition_class_mode(S.data_ptr(), n, None, 0, 0, 0, 1.0, n, K, capp, rcd.MODE_INCREMENTAL,
+                                              assign.data_ptr(), order.data_ptr(), objp, ws.data_ptr(), size, None)
+    else:
+        status = lib.rcd_partition_class_graph_cut(S.data_ptr(), n, n, K, capp, assign.data_ptr(), order.data_ptr(), objp,
+                                                   ws.data_ptr(), size, None)
+    assert status == 7
+    assert bool((assign < 0).all()) and bool((order < 0).all())
