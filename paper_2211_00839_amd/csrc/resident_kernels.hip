@@ -627,11 +627,12 @@ __device__ __forceinline__ bool collect(double (&G)[S::KM][S::P], int k, const L
 // Greedy steps of one class on the incremental route.  A batch: up to BM picks, each pick's row v* asked for when it is
 // made; then the rows against their blocks' coverage, and per pick the ordered list of changed j; one barrier; then the
 // rows of the lists that are short enough, all picks' lists end to end (ROWS rows in flight).  A longer list is handed out
-// to the workgroups from ncls on, `helpers` of them per class; its block waits for the sums when its turn comes.
+// to the workgroups from ncls on (helper_of says which class each of them serves; without it they take the classes one
+// after the other); its block waits for the sums when its turn comes.
 template <typename S>
 __global__ void __launch_bounds__(S::NT)
-rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, int ncls, int max_steps, int small_bytes,
-                    int launch, long long spin_ticks)
+rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, const RcdWg *__restrict__ helper_of,
+                    int ncls, int max_steps, int small_bytes, int launch, long long spin_ticks)
 {
     using namespace resident;
     constexpr int NW = S::NW, Q = S::Q, P = S::P, STAGE = S::STAGE;
@@ -639,11 +640,12 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
     __shared__ __attribute__((aligned(16))) Entry stage[S::BM * NW][STAGE];
     __shared__ int scount[S::BM * NW];
     __shared__ int s_fail;
-    RcdClass &st = classes[blockIdx.x % ncls];
+    const int wg = (int)blockIdx.x;
+    RcdClass &st = classes[wg >= ncls && helper_of ? helper_of[wg - ncls].cls : wg % ncls];
     // (1: the caller's S was refused, before this launch.  One launch runs the whole class: without this the call would
     // come back with its error only after all the steps.)
     if (st.done || plans[0].bad == 1) return;
-    if ((int)blockIdx.x >= ncls) {
+    if (wg >= ncls) {
         help<S>(st, launch, spin_ticks);
         return;
     }
@@ -944,7 +946,7 @@ namespace resident {
 // compiles without spilling in the loop.
 struct Choice {
     void (*gc)(RcdClass *, RcdPlan *, int);
-    void (*inc)(RcdClass *, RcdPlan *, int, int, int, int, long long);
+    void (*inc)(RcdClass *, RcdPlan *, const RcdWg *, int, int, int, int, long long);
     int threads;
 };
 

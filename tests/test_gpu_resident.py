@@ -107,6 +107,24 @@ def test_data_set_of_unequal_classes(rcd, monkeypatch, sizes, K):
     both(monkeypatch, lambda: rcd.partition_dataset(Xd, yd, len(sizes), r, 32.0, rcd.MODE_INCREMENTAL, ws))
 
 
+@pytest.mark.parametrize("sizes,K", [((2000,) + (90,) * 60, 4), ((30,) * 50 + (1500, 1500, 1400), 2), ((300,) * 60, 3)])
+def test_helpers_dealt_by_size(rcd, monkeypatch, sizes, K):
+    # many small classes beside a few large ones: the helpers go to the large ones, the rest get one or none; lists of more
+    # than four rows are handed out
+    print(f"helpers dealt to {len(sizes)} classes", flush=True)
+    rng = np.random.default_rng(len(sizes))
+    X = torch.from_numpy(np.concatenate([si.make_class(seed=i, n=n, d=16) for i, n in enumerate(sizes)])).cuda()
+    y = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    at = rng.permutation(len(y))
+    X, y = X[torch.from_numpy(at).cuda()].contiguous(), torch.from_numpy(y[at]).cuda()
+    r = rng.integers(1, 5, K).astype(np.int32)
+    _, full = rcd.dataset_workspace_bytes(len(at), len(sizes), max(sizes), K, rcd.MODE_STORED)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    for kb in ("", "1"):
+        monkeypatch.setenv("RCD_INC_SMALL_KB", kb)
+        both(monkeypatch, lambda: rcd.partition_dataset(X, y, len(sizes), r, 16.0, rcd.MODE_INCREMENTAL, ws))
+
+
 def test_classes_without_room_for_helpers(rcd, monkeypatch):
     # more classes than half the compute units: two lanes of 70 classes with helpers, of 140 without
     for L in (140, 280):
