@@ -360,13 +360,6 @@ bool multi_wg_wanted(int64_t max_n)
     return min_n > 0 && max_n >= min_n;
 }
 
-// Does the incremental route keep the gains of these classes in registers?  Where they fit, and as long as the device has a
-// compute unit to spare for every class's helpers.
-bool resident_incremental(int max_ld, int K, int ncls)
-{
-    return env_int("RCD_RESIDENT", 1, 0, 1) != 0 && 2 * ncls <= cu_count() && resident::choose_inc(max_ld, K).inc != nullptr;
-}
-
 // Deal `total` helper workgroups of the incremental step loop to the classes, largest first, in proportion to the work of
 // a list (rows times their length): at most `most` to one class, at least one as long as there are any.  What rounding
 // down leaves over stays idle: classes of one size end together, and some of them with one helper more end no sooner
@@ -397,6 +390,61 @@ std::vector<RcdWg> deal_helpers(const std::vector<RcdClass> &cls, int total, int
     // every class's first helper, every class's second, ...
     std::stable_sort(map.begin(), map.end(), [](const RcdWg &a, const RcdWg &b) { return a.w < b.w; });
     return map;
+}
+
+// The incremental step loop with the gains in registers, for the classes of one launch that has `cus` compute units.
+struct ResidentInc {
+    resident::Choice choice = {};          // no kernel: these classes keep their gains in memory
+    std::vector<RcdWg> helpers;            // which class each helper workgroup serves
+};
+
+// Taken where the gains fit, every class has a compute unit, and the rest of the device gives the classes the helpers they
+// need: a class that applies its long lists by itself is slower than the loop in memory with the whole device for its update
+// launches.  Needed (measured, loop in memory / this one, in ms):
+//   none up to n K = 6000    256 classes of 1000, two blocks, without helpers 9.9 / 6.9, 129 of 1500, four 15.3 / 15.1; but
+//                            200 of 1000, sixteen 16.7 / 17.4, 256 of 2000, eight 38.3 / 43.3
+//   else one                 128 of 3000, eight 51.5 / 45.4, 128 of 8000, four 227 / 218
+//   two for the variant of more than 3072 samples and four blocks, which spills
+//                            128 of 4000, eight 82.0 / 84.5, with two 85 of 4000 66.0 / 60.9
+//   and a class that does much of the work (alone it would have the update launches to itself) up to three
+//                            5000 beside 254 of 250, four blocks, one helper 37.7 / 46.2; 30 of 5000 with one 54.7 / 58.0,
+//                            with two 54.7 / 43.9
+// Classes of less than half the largest one's samples end long before it and need none.
+int plan_resident_incremental(const std::vector<RcdClass> &cls, int cus, ResidentInc &out)
+{
+    out = ResidentInc{};
+    const int ncls = (int)cls.size();
+    if (ncls < 1 || ncls > cus || env_int("RCD_RESIDENT", 1, 0, 1) == 0) return RCD_OK;
+    const int K = cls[0].K;
+    int max_n = 0;
+    double work = 0.0;
+    for (const RcdClass &c : cls) {
+        max_n = std::max(max_n, c.n);
+        work += (double)c.n * c.n;
+    }
+    const resident::Choice choice = resident::choose_inc(pitch_of(max_n), K);
+    if (!choice.inc) return RCD_OK;
+    // a compute unit holds one workgroup, or several of the small variants where there are many classes
+    int room = cus;
+    if (2 * ncls > cus) {
+        int per_cu = 0;
+        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(choice.inc), choice.threads, 0));
+        room = std::max(per_cu, 1) * cus;
+    }
+    const int most = env_int("RCD_HELPERS", 12, 1, 64);
+    std::vector<RcdWg> helpers = deal_helpers(cls, room - ncls, most);
+    std::vector<int> have(ncls, 0);
+    for (const RcdWg &h : helpers) have[h.cls] += 1;
+    for (int i = 0; i < ncls; ++i) {
+        const int n = cls[i].n;
+        if (n * K <= 6000 || 2 * n <= max_n) continue;
+        const int by_share = (int)(((double)n * n / work * cus - 1.0) / 2.0);
+        const int needed = std::max(n > 3072 && K > 4 ? 2 : 1, std::min(by_share, 3));
+        if (have[i] < std::min(needed, most)) return RCD_OK;
+    }
+    out.choice = choice;
+    out.helpers = std::move(helpers);
+    return RCD_OK;
 }
 
 // One group of classes on one stream.  The host keeps a few batches of rounds
@@ -497,7 +545,8 @@ struct Lane {
     // Upload the descriptors, reset the state, run the first step loop.
     // target_total: sweep workgroups per round this lane aims at.
     // sweep_target: workgroups the stored-S sweep launch aims at.
-    int start(Group &group, hipStream_t s, int slot_, int target_total, int sweep_target, bool profile)
+    // cus: this lane's share of the compute units.
+    int start(Group &group, hipStream_t s, int slot_, int target_total, int sweep_target, int cus, bool profile)
     {
         g = &group;
         stream = s;
@@ -582,22 +631,26 @@ struct Lane {
             }
         }
         res = resident::Choice{};
-        if ((graph_cut || incremental) && !mw) {
+        if (graph_cut && !mw) {
             int max_ld = 0;
             for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
-            if (graph_cut) {
-                if (env_int("RCD_RESIDENT", 1, 0, 1) != 0) res = resident::choose_gc(max_ld, first.K);
-            } else if (resident_incremental(max_ld, first.K, ncls)) {
-                res = resident::choose_inc(max_ld, first.K);
-                // A compute unit for every class; the others are helpers, at most twelve per class, and go where the work is
-                // (one class of 5000 samples beside a hundred of 300, four blocks: one helper each 46.4 ms, dealt by size
-                // 21.3; the loop in memory 36.8).
-                const std::vector<RcdWg> map = deal_helpers(g->host, cu_count() - ncls, env_int("RCD_HELPERS", 12, 1, 64));
-                res_helpers = (int)map.size();
+            if (env_int("RCD_RESIDENT", 1, 0, 1) != 0) res = resident::choose_gc(max_ld, first.K);
+        } else if (incremental && !mw) {
+            ResidentInc plan;
+            RCD_TRY(plan_resident_incremental(g->host, cus, plan));
+            if (plan.choice.inc) {
+                res = plan.choice;
+                // A helper for every compute unit that is left, at most twelve per class, where the work is (one class of
+                // 5000 samples beside a hundred of 300, four blocks: one helper each 46.4 ms, dealt by size 21.6; the loop
+                // in memory 36.8).
+                res_helpers = (int)plan.helpers.size();
                 // (the same number for every class: no table, whose copy is 10 us of a call on four classes of 250)
-                res_table = res_helpers != map.front().W * ncls;
+                res_table = res_helpers > 0 && res_helpers != plan.helpers.front().W * ncls;
                 if (res_table)
-                    HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
+                    HIP_TRY(hipMemcpyAsync(g->wgmap_dev, plan.helpers.data(), sizeof(RcdWg) * plan.helpers.size(),
+                                           hipMemcpyHostToDevice, stream));
+                int max_ld = 0;
+                for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
                 res_launch = 0;
                 mw_spin_ticks = (long long)env_int("RCD_MW_SPIN_MS", 2000, 0, 60000) * 100000LL;
                 inc_max_steps = env_int("RCD_INC_STEPS", 1 << 20, 1, 1 << 20);
@@ -850,7 +903,7 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream)
     int rc = RCD_OK;
     int started = 0;
     if (nl == 1) {
-        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, g_profile_on != 0);
+        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, cu_count(), g_profile_on != 0);
         started = 1;
     } else {
         RCD_TRY(ensure_side_streams(nl));
@@ -865,7 +918,7 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream)
         }
         const int per_lane = std::max(256, target_total * 2 / (nl + 1));
         for (int i = 0; i < nl && rc == RCD_OK; ++i) {
-            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, false);
+            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, cu_count() / nl, false);
             ++started;
         }
     }
@@ -1768,8 +1821,15 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
             // step loops that share classes among workgroups wait for one another inside the kernel: such
             // launches stay on one stream, so that two of them never compete for the compute units
             if (stored && (objective == 1 || incremental || auto_incremental) && multi_wg_wanted(max_count)) nl = 1;
-            // and so does a launch whose classes have helpers: it runs from start to end without the host
-            if (stored && (incremental || auto_incremental) && resident_incremental(pitch_of(max_count), K, live)) nl = 1;
+            // and so does a launch with the gains in registers: it runs from start to end without the host and has a use
+            // for every compute unit.  (Where that needs more room than there is, each lane asks again for its classes and
+            // its share of the device.)
+            if (stored && (incremental || auto_incremental) && nl > 1 && !multi_wg_wanted(max_count)) {
+                ResidentInc plan;
+                RCD_TRY(sweep_setup());
+                RCD_TRY(plan_resident_incremental(g.host, cu_count(), plan));
+                if (plan.choice.inc) nl = 1;
+            }
             std::vector<Group> lanes(nl);
             {
                 std::vector<double> cum(live + 1, 0.0);

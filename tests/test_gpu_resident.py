@@ -125,15 +125,18 @@ def test_helpers_dealt_by_size(rcd, monkeypatch, sizes, K):
         both(monkeypatch, lambda: rcd.partition_dataset(X, y, len(sizes), r, 16.0, rcd.MODE_INCREMENTAL, ws))
 
 
-def test_classes_without_room_for_helpers(rcd, monkeypatch):
-    # more classes than half the compute units: two lanes of 70 classes with helpers, of 140 without
-    for L in (140, 280):
-        rng = np.random.default_rng(L)
-        X = torch.from_numpy(rng.standard_normal((40 * L, 16)).astype(np.float32)).cuda()
-        y = torch.from_numpy(rng.permutation(np.repeat(np.arange(L), 40)).astype(np.int32)).cuda()
-        _, full = rcd.dataset_workspace_bytes(40 * L, L, 60, 4, rcd.MODE_STORED)
-        ws = torch.empty(full, dtype=torch.uint8, device="cuda")
-        both(monkeypatch, lambda: rcd.partition_dataset(X, y, L, [1, 2, 3, 1], 16.0, rcd.MODE_INCREMENTAL, ws))
+# more classes than half the compute units: with helpers because several workgroups fit one, with a few or without any
+# because the classes are small, in two lanes with the gains in memory; and more classes than compute units
+@pytest.mark.parametrize("L,n,K", [(130, 450, 16), (140, 40, 4), (200, 200, 16), (256, 30, 2), (150, 700, 16), (280, 40, 4)])
+def test_many_classes(rcd, monkeypatch, L, n, K):
+    print(f"resident, {L} classes of {n} K={K}", flush=True)
+    rng = np.random.default_rng(L)
+    X = torch.from_numpy(rng.standard_normal((n * L, 16)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.permutation(np.repeat(np.arange(L), n)).astype(np.int32)).cuda()
+    _, full = rcd.dataset_workspace_bytes(n * L, L, n, K, rcd.MODE_STORED)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    r = rng.integers(1, 4, K).astype(np.int32)
+    both(monkeypatch, lambda: rcd.partition_dataset(X, y, L, r, 16.0, rcd.MODE_INCREMENTAL, ws))
 
 
 @pytest.mark.parametrize("route", ["incremental", "graph cut"])
