@@ -794,7 +794,7 @@ struct Lane {
             launch_apply(round_no + 1);
             if (pe) (void)hipEventRecord((*pe)[3 * r + 3], stream);
         }
-        launches += (graph_cut ? 1 : !recompute || fused ? 2 : 3) * (int64_t)rounds;
+        launches += (graph_cut || res.inc ? 1 : !recompute || fused ? 2 : 3) * (int64_t)rounds;
         hipError_t le = hipGetLastError();
         if (le != hipSuccess) {
             snprintf(g_hip_err, sizeof g_hip_err, "kernel launch -> %s", hipGetErrorString(le));

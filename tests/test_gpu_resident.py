@@ -160,3 +160,17 @@ def test_no_step_is_taken_on_a_refused_matrix(rcd, route, n, bad):
                                                    ws.data_ptr(), size, None)
     assert status == 7
     assert bool((assign < 0).all()) and bool((order < 0).all())
+
+
+def test_launches_are_counted_as_made(rcd, monkeypatch):
+    # three launches to start with, a batch of step launches that the host waits for and one queued behind it, the
+    # objective; the loop in memory has an update launch beside every step launch
+    S = rcd.similarity(torch.from_numpy(si.make_class(seed=5, n=200, d=32)).cuda(), 32.0)
+    monkeypatch.setenv("RCD_ROUNDS_PER_BATCH", "5")
+    for on, per_round in (("1", 1), ("0", 2)):
+        monkeypatch.setenv("RCD_RESIDENT", on)
+        rcd.partition_class(S=S, cap=rcd.quota(200, [1, 1]), mode=rcd.MODE_INCREMENTAL)
+        launches = rcd.last_stats()["launches"] - 4
+        assert launches % (5 * per_round) == 0 and launches >= 10 * per_round
+        if on == "1":
+            assert launches == 10
