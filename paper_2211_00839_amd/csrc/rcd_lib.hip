@@ -984,23 +984,46 @@ bool mirror_wanted(int dt, int64_t d, int64_t tiles_in_flight)
 }
 
 // How often `tiles` workgroups fill the device, one per compute unit.
-int64_t tile_rounds(int64_t tiles)
+int64_t tile_rounds(int64_t tiles, int cus) { return (tiles + cus - 1) / cus; }
+
+// Time of one launch of a matrix's big tiles, in 64ths of one that fills the device once.  (The general path's half-size
+// tiles go round without a full second time: 2850 samples, d = 136, 276 tiles 57.2 us, pieces 60.1.)
+double big_tile_time(bool fast, int64_t n, int64_t ncols, int cus)
 {
-    const int64_t cus = cu_count();
-    return (tiles + cus - 1) / cus;
+    static_assert(sim::pipe::TM == 256 && sim::BM == 256, "tile rows");
+    const int64_t rows = (n + 255) / 256;
+    if (fast) return 64.0 * tile_rounds(rows * ((ncols + sim::pipe::TN - 1) / sim::pipe::TN), cus);
+    return std::max(64.0, 64.0 * rows * ((ncols + sim::BN - 1) / sim::BN) / cus);
 }
 
-// Similarity builds of few tiles: rounds = how often the 256 x 256 tiles fill the device, pieces = number of 64 x 64 ones.
-// In units of a 32 x 32 piece's multiplies, a round of big tiles takes 16 and a round of small ones 2, or 8 for
-// bf16, whose operands memory cannot feed at the multiply rate.  Measured, small against big in us: fp32 d = 512 500
-// samples 22 / 129, 1000 24 / 130, 2000 84 / 133, 3000 174 / 134; d = 64 1000 12 / 31, 3000 39 / 33; bf16 d = 2048 1000
-// 42 / 52, 1500 103 / 59; d = 512 1000 15 / 26, 1500 31 / 26.
-bool few_tiles_pay(int dt, int64_t rounds, int64_t pieces)
+// Similarity builds of few tiles: big is the time of the build in big tiles (big_tile_time), pieces the number of 64 x 64
+// ones.  `first` and `each` are the time of a launch of pieces and of each 64 x 64 piece per compute unit, measured (big
+// tiles / pieces in us):
+//   fp32, fast-path rows     d = 512 500 samples 132 / 24, 2047 133 / 83, 2400 134 / 117, 2600 133 / 134; d = 64 2400 32.4 / 29.0,
+//                            2600 32.9 / 35.4; d = 32, with hardly a k loop, 1729 25.5 / 20.8, 2047 25.3 / 26.2
+//   fp32, other aligned rows (their big tiles are 256 x 128) d = 300 601 samples 60 / 17, 1800 64 / 52, 2200 64 / 71;
+//                            d = 100 1700 33.6 / 27.2, 2047 34.2 / 37.9, but ten classes of 2000 in one launch 380 / 265
+//   fp32, unaligned rows     read an element at a time: d = 777 1200 samples 182 / 151, 1448 182 / 217, 2047 185 / 307;
+//                            d = 101 1600 38.2 / 35.9, 1773 38.5 / 42.5
+//   bf16                     one round: memory cannot feed the pieces at the multiply rate.  d = 2048 1000 samples 52 / 42,
+//                            1500 59 / 103; d = 512 1000 26 / 15, 1500 26 / 31
+bool few_tiles_pay(const void *X, int dt, int64_t d, int64_t ldx, double big, int64_t pieces, int cus)
 {
     const int mode = env_int("RCD_SIM_FEW", 1, 0, 2);
     if (mode != 1) return mode == 2;
-    if (sweep_setup() != RCD_OK) return false;
-    return (dt == RCD_F32 ? 2 : 8) * tile_rounds(pieces) < 16 * rounds;
+    if (dt != RCD_F32) return 32.0 * tile_rounds(pieces, cus) < big;
+    const bool aligned = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx * 4 % 16 == 0;
+    double first = 0.0, each;
+    if (rows_fit_fast_path(X, dt, d, ldx)) {
+        if (d < 64) { first = 18.0; each = 12.0; }
+        else each = 10.0;
+    } else if (d < 128) {
+        first = 18.0;
+        each = aligned ? 14.0 : 15.3;
+    } else {
+        each = aligned ? 15.0 : 31.0;
+    }
+    return first + each * std::max(1.0, (double)pieces / cus) < big;
 }
 
 int launch_similarity(const void *X, int dt, int64_t n, int64_t d, int64_t ldx, const int32_t *row_index,
@@ -1025,7 +1048,9 @@ int launch_similarity(const void *X, int dt, int64_t n, int64_t d, int64_t ldx, 
     // RCD_SIM_MIRROR: 0 never, 1 by that rule, 2 whenever the layout allows.
     const int64_t tm = (n + sim::pipe::TM - 1) / sim::pipe::TM;
     const int64_t small_rows = (n + sim::few::TILE - 1) / sim::few::TILE, small_cols = (ncols_pad + sim::few::TILE - 1) / sim::few::TILE;
-    if (few_tiles_pay(dt, tile_rounds(tm * tm), small_rows * small_cols)) {
+    RCD_TRY(sweep_setup());
+    const int cus = cu_count();
+    if (few_tiles_pay(X, dt, d, ldx, big_tile_time(fast, n, ncols_pad, cus), small_rows * small_cols, cus)) {
         const dim3 grid((unsigned)small_cols, (unsigned)small_rows);
         if (dt == RCD_F32)
             hipLaunchKernelGGL(sim::k_gram_rbf_few<float>, grid, dim3(256), 0, stream, (const float *)X, (long long)ldx, row_index,
@@ -1152,14 +1177,17 @@ int launch_similarity_batch(const void *X, int dt, int64_t d, int64_t ldx, float
     // (rows that do not fit the fast path would take a launch per class: 100 classes of 500 samples, d = 300 fp32,
     // 6.2 ms in launches of big tiles, 0.39 ms in two of small ones)
     const bool fast = rows_fit_fast_path(X, dt, d, ldx);
-    int64_t all_tiles = 0, pieces = 0, launches = 0;
+    RCD_TRY(sweep_setup());
+    const int cus = cu_count();
+    int64_t all_tiles = 0, pieces = 0;
+    double one_by_one = 0.0;
     for (const SimRequest &q : req) {
         const int64_t tm = (q.n + sim::pipe::TM - 1) / sim::pipe::TM;
         all_tiles += tm * tm;
-        launches += tile_rounds(tm * tm);
+        one_by_one += big_tile_time(false, q.n, q.ld, cus);
         pieces += ((q.n + sim::few::TILE - 1) / sim::few::TILE) * ((q.ld + sim::few::TILE - 1) / sim::few::TILE);
     }
-    const bool few = few_tiles_pay(dt, fast ? tile_rounds(all_tiles) : launches, pieces);
+    const bool few = few_tiles_pay(X, dt, d, ldx, fast ? 64.0 * tile_rounds(all_tiles, cus) : one_by_one, pieces, cus);
     if ((!few && !fast) || req.size() == 1 || env_int("RCD_SIM_BATCH", 1, 0, 1) == 0) {
         for (const SimRequest &q : req)
             RCD_TRY(launch_similarity(X, dt, q.n, d, ldx, q.row_index, sigma2, q.S, q.ld, (int)q.ld, q.sq, stream));

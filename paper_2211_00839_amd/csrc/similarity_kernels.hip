@@ -870,7 +870,8 @@ k_gram_rbf(const T *__restrict__ X, long long ldx, const int32_t *__restrict__ r
 // of row l & 31, lanes 32-63 the second half of a 32-byte k group, which is how the multiply wants them; 8 groups are
 // multiplied while the next 8 are on their way, no LDS, no barrier.  An operand row is read by n / 32 waves instead of n / 256
 // workgroups, which L2 can feed at the fp32 rate and at a quarter of the bf16 one: that is the limit of few_tiles_pay().
-// Any alignment and any d; k in the order of the other kernels, hence the same bits.
+// Any alignment (unaligned rows an element at a time, which that limit knows too) and any d; k in the order of the other
+// kernels, hence the same bits.
 // ---------------------------------------------------------------------------
 namespace few {
 
