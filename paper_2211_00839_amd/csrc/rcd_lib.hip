@@ -831,7 +831,8 @@ struct Lane {
         if (seen[0].bad == 2) {
             finished = true;
             snprintf(g_hip_err, sizeof g_hip_err,
-                     "a workgroup's bounded wait at a grid barrier of the multi-workgroup step loop ran out");
+                     res.inc ? "a workgroup's bounded wait for a helper workgroup's part of an update list ran out"
+                             : "a workgroup's bounded wait at a grid barrier of the multi-workgroup step loop ran out");
             return RCD_ERR_HIP;
         }
         if (seen[0].bad) { finished = true; return RCD_ERR_BAD_SIMILARITY; }

@@ -378,7 +378,7 @@ rcd_k_gc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, 
     using namespace resident;
     __shared__ Slot slots[2][4 * S::NW];
     RcdClass &st = classes[blockIdx.x];
-    if (st.done || plans[0].bad == 1) return;    // (1: the caller's S was refused, before this launch)
+    if (st.done || plans[0].bad) return;         // (bad: the caller's S was refused)
     const long long tick0 = wall_clock64();
     const int K = __builtin_amdgcn_readfirstlane(st.K), n = __builtin_amdgcn_readfirstlane(st.n);
     const int ld = __builtin_amdgcn_readfirstlane(st.ld);
@@ -642,9 +642,9 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
     __shared__ int s_fail;
     const int wg = (int)blockIdx.x;
     RcdClass &st = classes[wg >= ncls && helper_of ? helper_of[wg - ncls].cls : wg % ncls];
-    // (1: the caller's S was refused, before this launch.  One launch runs the whole class: without this the call would
-    // come back with its error only after all the steps.)
-    if (st.done || plans[0].bad == 1) return;
+    // (bad: the caller's S was refused, and one launch would run the whole class before the host hears of it; or a wait of
+    // the launch before ran out, whose state was not stored)
+    if (st.done || plans[0].bad) return;
     if (wg >= ncls) {
         help<S>(st, launch, spin_ticks);
         return;

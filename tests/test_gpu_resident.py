@@ -174,3 +174,17 @@ def test_launches_are_counted_as_made(rcd, monkeypatch):
         assert launches % (5 * per_round) == 0 and launches >= 10 * per_round
         if on == "1":
             assert launches == 10
+
+
+def test_a_wait_for_a_helper_that_runs_out_is_reported(rcd, monkeypatch):
+    # the bound set to zero from the host: helpers leave at once, and the first wave of the class that finds another one's
+    # part of a list unfinished raises the flag; every kernel exits, and the next call with the default bound works
+    S = rcd.similarity(torch.from_numpy(si.make_class(seed=6, n=2000, d=32)).cuda(), 32.0)
+    cap = rcd.quota(2000, [1, 1])
+    with monkeypatch.context() as m:
+        m.setenv("RCD_MW_SPIN_MS", "0")
+        with pytest.raises(rcd.RcdError) as e:
+            rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL)
+        assert e.value.status == 6 and "helper" in str(e.value)
+    torch.cuda.synchronize()
+    both(monkeypatch, lambda: rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL))
