@@ -482,6 +482,7 @@ struct Lane {
     int sweep_wgs = 0;       // stored S: workgroups of the sweep launch
     dim3 apply_rc_grid;
     hipEvent_t ev[RCD_SLOTS] = {};
+    hipEvent_t first_ev[2] = {};   // around the first step launch, while timing is on
     int64_t launches = 0, max_batches = 0;
     int64_t batch = 0;       // batches enqueued
     int64_t polled = 0;      // batches whose progress record has been read
@@ -696,7 +697,12 @@ struct Lane {
             // pageable source: the copy is staged before the call returns
             HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
         }
-        // step loop number 1 (the bootstrap) and its apply; step loop r+2 follows round r's sweep
+        // step loop number 1 (the bootstrap) and its apply; step loop r+2 follows round r's sweep.  On the routes whose step
+        // loops keep their gains current it may be the whole run: timed by itself.
+        if (prof && (graph_cut || incremental)) {
+            for (hipEvent_t &e : first_ev) HIP_TRY(hipEventCreate(&e));
+            HIP_TRY(hipEventRecord(first_ev[0], stream));
+        }
         if (graph_cut)
             launch_gc_steps();
         else if (recompute)
@@ -706,6 +712,7 @@ struct Lane {
         else
             hipLaunchKernelGGL(rcd_k_steps_rows, dim3(ncls), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev);
+        if (first_ev[1]) HIP_TRY(hipEventRecord(first_ev[1], stream));
 
         for (int i = 0; i < RCD_SLOTS; ++i) HIP_TRY(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
         // One launch per round (sweep + step loops fused) pays off when few classes are in
@@ -852,6 +859,13 @@ struct Lane {
         hipError_t es = hipStreamSynchronize(stream);
         if (prof && es == hipSuccess && rc == RCD_OK)
             for (int64_t b = prof_done; b < batch; ++b) read_events(b);
+        float first_ms = 0.f;
+        if (first_ev[1] && es == hipSuccess && rc == RCD_OK && hipEventElapsedTime(&first_ms, first_ev[0], first_ev[1]) == hipSuccess)
+            g_prof[0] += first_ms;
+        for (hipEvent_t &e : first_ev) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
+        }
         for (int i = 0; i < RCD_SLOTS; ++i) {
             if (ev[i]) (void)hipEventDestroy(ev[i]);
             ev[i] = nullptr;

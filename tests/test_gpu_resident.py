@@ -188,3 +188,18 @@ def test_a_wait_for_a_helper_that_runs_out_is_reported(rcd, monkeypatch):
         assert e.value.status == 6 and "helper" in str(e.value)
     torch.cuda.synchronize()
     both(monkeypatch, lambda: rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL))
+
+
+@pytest.mark.parametrize("route", ["incremental", "graph cut"])
+def test_the_timing_knows_the_first_step_launch(rcd, route):
+    # one launch makes every step: its time has to be in the sum (step_ticks: 10 ns units inside the one class's loop)
+    S = rcd.similarity(torch.from_numpy(si.make_class(seed=7, n=2000, d=32)).cuda(), 32.0)
+    cap = rcd.quota(2000, [1, 2])
+    rcd.profile(True)
+    if route == "incremental":
+        rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL)
+    else:
+        rcd.partition_class_graph_cut(S, cap)
+    ms, ticks = rcd.profile_read()["steps_ms"], rcd.last_stats()["step_ticks"]
+    rcd.profile(False)
+    assert ms >= 0.9e-5 * ticks > 0
