@@ -39,6 +39,8 @@ def run(rcd, monkeypatch, S, cap, fused, pct=50, shared=False, small_kb=None, bl
     monkeypatch.setenv("RCD_INC_FUSE_PCT", str(pct))
     monkeypatch.setenv("RCD_MW_MIN_N", "1" if shared else "0")
     monkeypatch.setenv("RCD_MW_SLICE", "256")
+    # (classes of this size keep their gains in registers unless told otherwise, and then no update launch is made)
+    monkeypatch.setenv("RCD_RESIDENT", "0")
     if small_kb is not None:
         monkeypatch.setenv("RCD_INC_SMALL_KB", str(small_kb))
     a, o, f = rcd.partition_class(S=dev(S), cap=cap, mode=rcd.MODE_INCREMENTAL)
@@ -56,8 +58,10 @@ def test_fused_pass_gives_the_list_by_list_bits(rcd, monkeypatch, shared, n, r, 
     S = mixture_S(500 + n, n)
     cap = oracle.quota(n, r)
     # lists of more than one row go to the update launches, so that the fused pass sees sparse lists too
-    a1, o1, f1, _ = run(rcd, monkeypatch, S, cap, fused=True, pct=pct, shared=shared, small_kb=1, blocks=blocks)
-    a0, o0, f0, _ = run(rcd, monkeypatch, S, cap, fused=False, shared=shared, small_kb=1)
+    a1, o1, f1, s1 = run(rcd, monkeypatch, S, cap, fused=True, pct=pct, shared=shared, small_kb=1, blocks=blocks)
+    a0, o0, f0, s0 = run(rcd, monkeypatch, S, cap, fused=False, shared=shared, small_kb=1)
+    # every block's first list is the whole class: they all wait for one update launch, and the share is met
+    assert s1["sweeps"] >= len(cap) and s0["sweeps"] >= len(cap)
     assert np.array_equal(a1, a0) and np.array_equal(o1, o0) and np.array_equal(f1, f0)
     res = oracle.lockstep(S, cap, o1, a1, rel_tol=1e-5, objective="fl")
     assert res["rc"] == 0 and res["checked"] == n, res
@@ -92,6 +96,7 @@ def test_data_set_with_fused_and_unfused_classes(rcd, monkeypatch):
     monkeypatch.setenv("RCD_INC_SMALL_KB", "1")
     monkeypatch.setenv("RCD_MW_MIN_N", "1")
     monkeypatch.setenv("RCD_MW_SLICE", "512")
+    monkeypatch.setenv("RCD_RESIDENT", "0")
     sizes = np.array([40, 1500, 0, 700, 3, 2300, 260])
     L, N, d, r = len(sizes), int(sizes.sum()), 64, [1, 2, 3, 1, 1]
     X = si.make_class(seed=402, n=N, d=d, G=5)

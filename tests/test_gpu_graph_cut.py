@@ -57,10 +57,13 @@ def check_against_oracle(S, cap, assign, order, obj, rel_tol=1e-5):
     return res
 
 
+# both step loops: gains in registers and gains in memory
+@pytest.mark.parametrize("resident", ["1", "0"])
 @pytest.mark.parametrize("n,r", [(1, [1]), (250, [1, 1]), (600, [1, 1, 2, 4]), (1000, [1, 1, 1, 2, 2, 3, 4, 6]),
                                  (520, [3, 1, 4, 1, 2, 2, 1, 3, 4, 4, 1, 2, 3, 3, 2, 1]), (257, [5]), (1300, [2, 1])])
-def test_graph_cut_class_greedy_lockstep(rcd, n, r):
-    print(f"graph-cut class greedy n={n} K={len(r)}", flush=True)
+def test_graph_cut_class_greedy_lockstep(rcd, monkeypatch, n, r, resident):
+    print(f"graph-cut class greedy n={n} K={len(r)} resident={resident}", flush=True)
+    monkeypatch.setenv("RCD_RESIDENT", resident)
     S = mixture_S(700 + n, n)
     cap = oracle.quota(n, r)
     assign, order, obj = run_class(rcd, S, cap)

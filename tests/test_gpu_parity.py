@@ -158,6 +158,29 @@ def test_similarity_sigma_scaling(rcd):
 
 
 # ------------------------------------------------------------------ gain sweep
+# 32768 floats of coverage fit a sweep workgroup: pitches on both sides of what one, two and four blocks and the most leave
+# of it, and of a row's 256-sample pieces
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 7, 12, 16])
+@pytest.mark.parametrize("n", [40, 255, 257, 2048, 2049, 4100, 9000])
+def test_every_entry_counts_in_the_sweeps_of_the_stored_route(rcd, n, K):
+    # All similarities are 1/64 but one in each of 2 K columns, all in different rows, so exactly one term of a gain decides
+    # each pick: with empty blocks the column sums (K sweeps of one), then, each block holding one sample, sums whose only
+    # other terms are zeros.  A term left out, or coverage of another block or row, gives another sample.
+    print(f"stored sweep, planted entries n={n} K={K}", flush=True)
+    rng = np.random.default_rng(n * 17 + K)
+    edges = [x for x in (0, n - 1, 1, n - 2, 63, 64, 127, 128, 254, 255, 256, 2047, 2048, n // 2) if 0 <= x < n]
+    col, row = ([*dict.fromkeys([*rng.permutation(edges).tolist(), *rng.permutation(n).tolist()])][: 2 * K] for _ in range(2))
+    value = 0.9 - 0.01 * np.arange(2 * K)
+    S = np.full((n, n), 1 / 64, dtype=np.float32)
+    S[row, col] = value
+    assign, order, _ = rcd.partition_class(S=dev(S), cap=np.full(K, 2))
+    assign, order = assign.cpu().numpy(), order.cpu().numpy()
+    # first every block in turn, then again from the block of least value up
+    assert order[col].tolist() == list(range(2 * K))
+    assert assign[col].tolist() == list(range(K)) + list(range(K - 1, -1, -1))
+    assert np.sum(assign >= 0) == 2 * K
+
+
 @pytest.mark.parametrize("n,K", [(1, 1), (64, 2), (257, 3), (700, 5), (1100, 8), (600, 16)])
 def test_gain_sweep_matches_oracle_rows(rcd, n, K):
     print(f"gain sweep n={n} K={K}", flush=True)

@@ -1,5 +1,5 @@
-"""The step loops that keep a class's gains in registers against the loops that keep them in memory (RCD_RESIDENT = 0),
-which the oracle referees in the other files: same assignment, order and objectives to the bit, at the edges of every
+"""The step loops that keep a class's gains in registers against the loops that keep them in memory (RCD_RESIDENT = 0).  The
+oracle referees both in test_gpu_incremental.py and test_gpu_graph_cut.py.  Here: same assignment, order and objectives to the bit, at the edges of every
 variant's sample and block range, with zero quotas and samples left over, with groups of identical samples (exact
 ties), with the state stored and loaded again in mid-run, and for classes of unequal size in one launch."""
 import ctypes
@@ -45,8 +45,8 @@ def quotas(rng, n, K, full):
 
 # (n, K): both sides of every variant's last sample, and its most blocks
 EDGES = [(1, 1), (2, 3), (255, 2), (256, 16), (257, 5), (512, 16), (513, 3), (1024, 16), (1025, 8), (2048, 16), (2049, 4),
-         (3072, 8), (3072, 16), (3073, 12), (4096, 9), (4097, 4), (5120, 8), (5121, 8), (6144, 5), (6145, 3), (8192, 4),
-         (8193, 2)]
+         (3072, 8), (3072, 16), (3073, 12), (4096, 9), (4096, 12), (4097, 4), (5120, 8), (5121, 8), (6144, 5), (6144, 8),
+         (6145, 3), (8192, 4), (8193, 2), (16383, 2)]
 
 
 @pytest.mark.parametrize("n,K", EDGES)
@@ -66,6 +66,7 @@ def test_graph_cut_class(rcd, monkeypatch, n, K):
         assert sorted(order[order >= 0].tolist()) == list(range(int(cap.sum())))
 
 
+# ((3072, 16), (5121, 8) and (6144, 5) lie just outside the variants: there both runs take the loop in memory)
 INC_EDGES = [(1, 1), (2, 3), (255, 2), (256, 16), (257, 5), (512, 16), (513, 3), (1024, 16), (1025, 8), (2048, 16), (2049, 4),
              (3072, 8), (3072, 16), (3073, 3), (5120, 4), (5120, 8), (5121, 8), (6144, 5), (6145, 3), (8192, 4)]
 
