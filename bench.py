@@ -482,7 +482,7 @@ def main():
         # a step reads the block's marginal values (8 B each), one row of S (4 B) and rewrites the values (16 B)
         "bytes_per_greedy_step": 28 * n_max,
         "us_per_greedy_step_in_loop": 10e-3 * gstats["step_ticks"] / max(gstats["steps"], 1) ,
-        "bound": "latency of one workgroup's step (scan, two barriers, one row): classes run side by side, one compute unit each",
+        "bound": "latency of one workgroup's step (scan, one barrier, one row): classes run side by side, one compute unit each",
     }
 
     # the same workload with nothing stored: S tiles rebuilt by the matrix cores inside every gain sweep (one timed pass)

@@ -31,8 +31,8 @@
  *   - Tuning: the partition and similarity calls read a few environment
  *     variables named RCD_* at each call (lanes, rounds per batch, workgroups
  *     per launch, steps per launch, the sizes from which large classes are
- *     shared among workgroups or their update lists fused, the bound of a
- *     wait between those workgroups).  They set launch shapes and thresholds
+ *     shared among workgroups or their update lists fused, helper workgroups
+ *     per class, the bound of a wait between workgroups).  They set launch shapes and thresholds
  *     only: none selects the algorithmic route (that is the `mode` argument),
  *     and every setting meets the contract stated at the entry point.  Unset,
  *     each has a measured default.
@@ -58,7 +58,7 @@ typedef enum {
     RCD_ERR_BAD_CAPACITY = 3, /* capacity < 1 (data set) / quota < 0 or sum of quotas > n (class) */
     RCD_ERR_UNSUPPORTED = 4,  /* K > RCD_MAX_K, unknown dtype or mode, size beyond 2^31-1 */
     RCD_ERR_WORKSPACE = 5,    /* workspace pointer null/misaligned or smaller than required */
-    RCD_ERR_HIP = 6,          /* a HIP call failed; rcd_last_hip_error() has its text */
+    RCD_ERR_HIP = 6,          /* a HIP call failed, or a bounded wait between workgroups ran out; rcd_last_hip_error() has the text */
     RCD_ERR_BAD_SIMILARITY = 7 /* a similarity outside [0, 1] (or NaN) was found in a caller-supplied S */
 } rcd_status;
 

@@ -404,7 +404,7 @@ struct ResidentInc {
 //   none up to n K = 6000    256 classes of 1000, two blocks, without helpers 9.9 / 6.9, 129 of 1500, four 15.3 / 15.1; but
 //                            200 of 1000, sixteen 16.7 / 17.4, 256 of 2000, eight 38.3 / 43.3
 //   else one                 128 of 3000, eight 51.5 / 45.4, 128 of 8000, four 227 / 218
-//   two for the variant of more than 3072 samples and four blocks, which spills
+//   two above 3072 samples with more than four blocks
 //                            128 of 4000, eight 82.0 / 84.5, with two 85 of 4000 66.0 / 60.9
 //   and a class that does much of the work (alone it would have the update launches to itself) up to three
 //                            5000 beside 254 of 250, four blocks, one helper 37.7 / 46.2; 30 of 5000 with one 54.7 / 58.0,

@@ -11,7 +11,7 @@
 //     everywhere), so the next block's argmax can be taken while row v* is still on its way, unless that block is k again.
 // The order of the steps, every sum and every tie are those of the other loops: the results are the same bits.
 // Graph cut, one class, us per step before -> after: 250 samples and 2 blocks 2.25 -> 0.90, 1000 / 8 2.28 -> 0.98,
-// 3000 / 8 2.54 -> 0.99, 5000 / 4 3.14 -> 1.14; ten classes of 5000 with 4 blocks, whole call 18.7 -> 7.2 ms.  What is left
+// 3000 / 8 2.54 -> 0.99, 5000 / 4 3.14 -> 1.14; ten classes of 5000 with 4 blocks, whole call 19.8 -> 8.0 ms.  What is left
 // of a step is about 350 instructions of one wave after the other's result, and the barrier.
 //
 // Layout: wave w owns the samples [128 Q w, 128 Q (w + 1)), in Q pieces of 128; lane l holds samples 2 l and 2 l + 1 of
@@ -942,8 +942,8 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
 namespace resident {
 
 // The variants for a group whose largest class has pitch ld (samples rounded up to 256) and K blocks: the smallest that
-// holds the class.  Graph cut: null beyond 2 P KM = 192 registers of gains per lane (of 256 with 512 threads), the most that
-// compiles without spilling in the loop.
+// holds the class.  Graph cut: null beyond 2 P KM = 192 registers of gains per lane (of 256 with 512 threads); six pieces and
+// eight blocks, the most, spill a few in the loop (8 of its accesses go to scratch memory).
 struct Choice {
     void (*gc)(RcdClass *, RcdPlan *, int);
     void (*inc)(RcdClass *, RcdPlan *, const RcdWg *, int, int, int, int, long long);
@@ -974,8 +974,9 @@ inline Choice choose_gc(int ld, int K)
 // Against rcd_k_inc_steps (whole calls, start of its launches to their end, before -> after in ms): ten classes of 5000 and
 // four blocks 44.9 -> 25.5, eight blocks 49.2 -> 40.5, one such class 38.8 -> 35.0; four classes of 3000, eight blocks
 // 22.2 -> 13.7; 8000 samples, four blocks 73.7 -> 67.6; thirty of 2000, sixteen blocks 20.7 -> 12.1; a hundred of 500
-// 8.3 -> 3.4.  Not taken, because the gains leave too few registers for the rest and the loop spills: 3072 samples and
-// sixteen blocks (22.4 -> 25.9), 6144 and eight (51.8 -> 62.7).
+// 8.3 -> 3.4.  Not taken, because the gains leave too few registers for the rest and the loop spills too much: 3072 samples
+// and sixteen blocks (22.4 -> 25.9), 6144 and eight (51.8 -> 62.7).  (5120 and eight, 8192 and four spill as well, 24 and 31
+// registers.)
 inline Choice choose_inc(int ld, int K)
 {
     if (ld <= 256) return inc_choice<128, 1, 16, 4>();
