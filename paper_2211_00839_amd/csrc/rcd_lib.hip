@@ -546,8 +546,9 @@ struct Lane {
     // Upload the descriptors, reset the state, run the first step loop.
     // target_total: sweep workgroups per round this lane aims at.
     // sweep_target: workgroups the stored-S sweep launch aims at.
-    // cus: this lane's share of the compute units.
-    int start(Group &group, hipStream_t s, int slot_, int target_total, int sweep_target, int cus, bool profile)
+    // cus: this lane's share of the compute units.  inc_plan: what plan_resident_incremental says of them, if that is known.
+    int start(Group &group, hipStream_t s, int slot_, int target_total, int sweep_target, int cus, const ResidentInc *inc_plan,
+              bool profile)
     {
         g = &group;
         stream = s;
@@ -637,8 +638,9 @@ struct Lane {
             for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
             if (env_int("RCD_RESIDENT", 1, 0, 1) != 0) res = resident::choose_gc(max_ld, first.K);
         } else if (incremental && !mw) {
-            ResidentInc plan;
-            RCD_TRY(plan_resident_incremental(g->host, cus, plan));
+            ResidentInc mine;
+            if (!inc_plan) RCD_TRY(plan_resident_incremental(g->host, cus, mine));
+            const ResidentInc &plan = inc_plan ? *inc_plan : mine;
             if (plan.choice.inc) {
                 res = plan.choice;
                 // A helper for every compute unit that is left, at most twelve per class, where the work is (one class of
@@ -902,8 +904,8 @@ struct Lane {
 // coverage updates (latency-bound, a few workgroups) overlap the other groups'
 // sweeps (bandwidth-bound, the whole chip).  Returns after all of them finished:
 // work the caller enqueues afterwards is ordered behind them.  Fills each
-// group's obj_dev and accumulates g_stats.
-int run_groups(std::vector<Group> &groups, hipStream_t stream)
+// group's obj_dev and accumulates g_stats.  inc_plan: for one group, see Lane::start.
+int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc *inc_plan = nullptr)
 {
     const int nl = (int)groups.size();
     if (nl < 1) return RCD_OK;
@@ -918,7 +920,7 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream)
     int rc = RCD_OK;
     int started = 0;
     if (nl == 1) {
-        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, cu_count(), g_profile_on != 0);
+        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, cu_count(), inc_plan, g_profile_on != 0);
         started = 1;
     } else {
         RCD_TRY(ensure_side_streams(nl));
@@ -933,7 +935,7 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream)
         }
         const int per_lane = std::max(256, target_total * 2 / (nl + 1));
         for (int i = 0; i < nl && rc == RCD_OK; ++i) {
-            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, cu_count() / nl, false);
+            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, cu_count() / nl, nullptr, false);
             ++started;
         }
     }
@@ -1867,11 +1869,11 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
             // and so does a launch with the gains in registers: it runs from start to end without the host and has a use
             // for every compute unit.  (Where that needs more room than there is, each lane asks again for its classes and
             // its share of the device.)
+            ResidentInc inc_plan;
             if (stored && (incremental || auto_incremental) && nl > 1 && !multi_wg_wanted(max_count)) {
-                ResidentInc plan;
                 RCD_TRY(sweep_setup());
-                RCD_TRY(plan_resident_incremental(g.host, cu_count(), plan));
-                if (plan.choice.inc) nl = 1;
+                RCD_TRY(plan_resident_incremental(g.host, cu_count(), inc_plan));
+                if (inc_plan.choice.inc) nl = 1;
             }
             std::vector<Group> lanes(nl);
             {
@@ -1895,7 +1897,7 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
                     a = b;
                 }
             }
-            RCD_TRY(run_groups(lanes, stream));
+            RCD_TRY(run_groups(lanes, stream, inc_plan.choice.inc ? &inc_plan : nullptr));
             if (g_profile_on) {
                 float ms = 0.f;
                 if (hipEventElapsedTime(&ms, sim_ev[0], sim_ev[1]) == hipSuccess) g_prof[4] += ms;

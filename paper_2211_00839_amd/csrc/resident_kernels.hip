@@ -138,26 +138,29 @@ template <int NT_, int Q_, int KM_> struct Shape {
 struct Slot { unsigned hi, lo; int v, pad; };
 
 // What a wave knows about where it is.  Piece q of a lane starts at sample v0 + 128 q; pieces from nq on lie outside the
-// class's pitch (a piece is wholly in or out): their gains are INC_TAKEN.  A row is read through at(): for a piece outside
-// the pitch that is the row's first 128 samples, so no read leaves the row (a class may be much smaller than the variant its
-// launch needs for the largest), and what is added to INC_TAKEN for them is finite and far below its last bit.
+// class's pitch (a piece is wholly in or out): their gains are INC_TAKEN.  A row is read through at(), which stays inside the
+// row: a class may be much smaller than the variant its launch needs for the largest.  A piece outside the pitch reads from
+// the row's start instead, and what is added to INC_TAKEN for it is finite and far below its last bit.
 template <typename S> struct Place {
+    // one or two pieces: a wave is wholly in or out too (the pitch is a multiple of 256), and v0 alone says where it reads
+    static constexpr bool WHOLE = S::Q <= 2;
     int lane, wave, nq;
     unsigned v0;
-    unsigned piece[S::Q];    // bytes from a row's start to piece q of this wave
+    unsigned piece[S::Q];    // bytes from a row's start to piece q of this wave (not WHOLE)
     __device__ __forceinline__ void init(int ld)
     {
         lane = threadIdx.x & 63;
         wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         nq = min(max((ld - wave * S::WAVE) / 128, 0), S::Q);
-        v0 = (unsigned)(wave * S::WAVE + lane * 2);
+        v0 = (unsigned)((WHOLE && nq == 0 ? 0 : wave * S::WAVE) + lane * 2);
 #pragma unroll
         for (int q = 0; q < S::Q; ++q) piece[q] = q < nq ? (unsigned)(wave * S::WAVE + 128 * q) * 4u : 0u;
     }
     // this lane's two samples of piece q in the row that starts `row` bytes into the buffer
     __device__ __forceinline__ f32x2 at(__amdgpu_buffer_rsrc_t b, unsigned row, int q) const
     {
-        return buffer_load2(b, (unsigned)lane * 8u, row + piece[q]);
+        if constexpr (WHOLE) return buffer_load2(b, v0 * 4u, row + 512u * q);
+        else return buffer_load2(b, (unsigned)lane * 8u, row + piece[q]);
     }
 };
 
@@ -378,7 +381,7 @@ rcd_k_gc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, 
     using namespace resident;
     __shared__ Slot slots[2][4 * S::NW];
     RcdClass &st = classes[blockIdx.x];
-    if (st.done || plans[0].bad) return;         // (bad: the caller's S was refused)
+    if ((st.done | plans[0].bad) != 0) return;   // (bad: the caller's S was refused.  One trip for both words.)
     const long long tick0 = wall_clock64();
     const int K = __builtin_amdgcn_readfirstlane(st.K), n = __builtin_amdgcn_readfirstlane(st.n);
     const int ld = __builtin_amdgcn_readfirstlane(st.ld);
@@ -641,10 +644,11 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
     __shared__ int scount[S::BM * NW];
     __shared__ int s_fail;
     const int wg = (int)blockIdx.x;
-    RcdClass &st = classes[wg >= ncls && helper_of ? helper_of[wg - ncls].cls : wg % ncls];
+    const int cls = wg < ncls ? wg : helper_of ? helper_of[wg - ncls].cls : wg % ncls;
+    RcdClass &st = classes[__builtin_amdgcn_readfirstlane(cls)];
     // (bad: the caller's S was refused, and one launch would run the whole class before the host hears of it; or a wait of
-    // the launch before ran out, whose state was not stored)
-    if (st.done || plans[0].bad) return;
+    // the launch before ran out, whose state was not stored.  One trip to memory for both words.)
+    if ((st.done | plans[0].bad) != 0) return;
     if (wg >= ncls) {
         help<S>(st, launch, spin_ticks);
         return;

@@ -76,7 +76,7 @@ k_scatter(const int32_t *__restrict__ labels, long long N, int L, int label_bits
           const int32_t *__restrict__ class_count, const RcdPlan *__restrict__ plan, int32_t *__restrict__ idx)
 {
     extern __shared__ int s_cnt[];
-    if (plan->bad) return;
+    const int bad = plan->bad;     // (looked at below, when it has come with the labels)
     const int lane = threadIdx.x;
     const long long base = (long long)blockIdx.x * CHUNK;
     constexpr int GROUPS = CHUNK / 64;
@@ -100,6 +100,7 @@ k_scatter(const int32_t *__restrict__ labels, long long N, int L, int label_bits
         if (l < L) s_cnt[l] = before + incl - c + chunk_base[(size_t)blockIdx.x * L + l];
         before += __shfl(incl, 63);
     }
+    if (bad) return;
     __syncthreads();
 #pragma unroll
     for (int g = 0; g < GROUPS; ++g) {
