@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -20,6 +21,7 @@
 #include "incremental_kernels.hip"
 #include "multi_wg_kernels.hip"
 #include "resident_kernels.hip"
+#include "sliced_kernels.hip"
 
 static_assert(RCD_KMAX == RCD_MAX_K, "public and internal block limits differ");
 
@@ -222,6 +224,17 @@ struct DeviceSetup {
 };
 std::mutex g_setup_mutex;
 DeviceSetup g_dev[RCD_MAX_DEVICES];
+
+// Compute units taken by launches whose workgroups wait for one another, per device.  Two such launches that together need
+// more than the device has could each hold a part of it and wait for the rest for ever: a call takes its units before its
+// first such launch, waiting for calls of other threads to give theirs back, and gives them back when its stream is drained.
+// (It holds nothing else that such a call could wait for.)
+struct SharedUnits {
+    std::mutex mutex;
+    std::condition_variable freed;
+    int taken = 0;
+};
+SharedUnits g_shared_units[RCD_MAX_DEVICES];
 
 // The current device's record, or null (and g_hip_err) if the device cannot be told.
 DeviceSetup *device_setup()
@@ -447,6 +460,53 @@ int plan_resident_incremental(const std::vector<RcdClass> &cls, int cus, Residen
     return RCD_OK;
 }
 
+// The step loop that shares classes among workgroups with the slices' gains in registers (sliced_kernels.hip): which
+// workgroups serve which class, for the classes of one launch that has the device to itself.
+struct SlicedInc {
+    sliced::Choice choice = {};            // no kernel: not for these classes
+    std::vector<RcdWg> map;
+    std::vector<int> seg;                  // samples per slice of each class
+};
+
+// Taken from 5121 samples in the largest class on, where a class no longer fits one workgroup's registers or does so with
+// too few left, and from 2561 on for a single class of more than four blocks (5120 fit then, but one pick at a time).
+// Measured, the loops taken otherwise / this one, in ms: one class of 50 000, eight blocks 587 / 383 (the whole call), of
+// 12 000, four 133 / 70, of 8000, eight 73 / 46, of 6000, three 45 / 32, of 5000, eight 33.8 / 29.4, of 3500, seven
+// 22.3 / 19.5; 20 classes of 8000, four 89 / 66, ten of 6000, six 65 / 46.  Below: 5000 and four blocks 20.0 / 28.0, 2000 and
+// twelve 8.0 / 12.2, ten classes of 5000 and eight 42.9 / 43.6.
+// Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048 (20 000 samples
+// 118 / 131, 12 000 70 / 77; of 512, 12 000 samples 73); where there are not even those, the loops in memory serve.
+SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
+{
+    SlicedInc none, out;
+    const int ncls = (int)cls.size();
+    if (ncls < 1 || env_int("RCD_RESIDENT", 1, 0, 1) == 0) return none;
+    int max_n = 0;
+    for (const RcdClass &c : cls) max_n = std::max(max_n, c.n);
+    const int min_n = env_int("RCD_MW_MIN_N", ncls == 1 && cls[0].K > 4 ? 2561 : 5121, 0, 0x7fffffff);
+    if (min_n == 0 || max_n < min_n) return none;
+    const int w_max = std::min(env_int("RCD_MW_MAX_WGS", RCD_MW_MAX, 1, RCD_MW_MAX), cus / ncls);
+    if (w_max < 2) return none;
+    const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256;
+    for (const int least : {given ? given : 1024, given ? given : 2048}) {
+        out = none;
+        int largest = 0;
+        for (int i = 0; i < ncls; ++i) {
+            const int ld = cls[i].ld;
+            int W = std::min(w_max, (ld + least - 1) / least);
+            const int seg = ((ld + W - 1) / W + 255) / 256 * 256;
+            W = (ld + seg - 1) / seg;               // no empty slice
+            largest = std::max(largest, seg);
+            out.seg.push_back(seg);
+            for (int w = 0; w < W; ++w) out.map.push_back(RcdWg{i, w, W, 0});
+        }
+        if ((int)out.map.size() > std::min(cus, RCD_MAX_SWEEP_WGS)) continue;
+        out.choice = sliced::choose(largest, cls[0].K);
+        if (out.choice.inc) return out;
+    }
+    return none;
+}
+
 // One group of classes on one stream.  The host keeps a few batches of rounds
 // queued ahead of the device: start(), then enqueue_batch() while fewer than
 // `depth` batches are unread and poll() to read the oldest one's progress record,
@@ -464,9 +524,12 @@ struct Lane {
     // several workgroups per class for the step loops of large classes (incremental gains, graph cut)
     bool mw = false;
     int mw_wgs = 0;
+    sliced::Choice slc = {};    // the same with the slices' gains in registers (incremental route, where they fit)
     resident::Choice res = {};  // the step loop with the gains in registers, where every class of the group fits one
     int res_helpers = 0, res_launch = 0;   // incremental route: helper workgroups, launches so far
     bool res_table = false;     // the helpers' classes are in g->wgmap_dev (else one after the other)
+    SharedUnits *units = nullptr;   // where this lane's units were taken, if any
+    int units_taken = 0;
     unsigned mw_epoch = 0;      // exchanges the earlier launches of this call may have used
     long long mw_spin_ticks = 200000000;   // bound of a grid-barrier wait, 100 MHz ticks (2 s)
     dim3 update_grid;
@@ -498,7 +561,10 @@ struct Lane {
         const unsigned epoch0 = mw_epoch;
         mw_epoch += 2u * (unsigned)inc_max_steps + 8u;
         (void)epoch0;
-        if (mw)
+        if (mw && slc.inc)
+            hipLaunchKernelGGL(slc.inc, dim3(mw_wgs), dim3(slc.threads), 0, stream, g->classes_dev, g->plan_dev,
+                               (const RcdWg *)g->wgmap_dev, inc_max_steps, inc_small_bytes, epoch0, mw_spin_ticks);
+        else if (mw)
             hipLaunchKernelGGL(rcd_k_inc_steps_mw, dim3(mw_wgs), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, (const RcdWg *)g->wgmap_dev, inc_max_steps, inc_small_bytes, epoch0,
                                mw_spin_ticks);
@@ -523,6 +589,31 @@ struct Lane {
         else
             hipLaunchKernelGGL(rcd_k_gc_steps, dim3(ncls), dim3(RCD_STEP_THREADS), 0, stream, g->classes_dev,
                                g->plan_dev, gc_max_steps);
+    }
+
+    // Take the compute units of `wgs` workgroups that wait for one another (at most `capacity` run at once).
+    int take_units(int wgs, int capacity)
+    {
+        int dev = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        SharedUnits &u = g_shared_units[dev];       // (device_setup() has looked at the index)
+        std::unique_lock<std::mutex> lock(u.mutex);
+        const int cus = cu_count(), want = std::min(cus, (int)(((int64_t)wgs * cus + capacity - 1) / capacity));
+        u.freed.wait(lock, [&] { return u.taken + want <= cus; });
+        u.taken += want;
+        units = &u;
+        units_taken = want;
+        return RCD_OK;
+    }
+    void give_units()
+    {
+        if (!units) return;
+        {
+            std::lock_guard<std::mutex> lock(units->mutex);
+            units->taken -= units_taken;
+        }
+        units->freed.notify_all();
+        units = nullptr;
     }
 
     void launch_apply(int rn)
@@ -590,20 +681,31 @@ struct Lane {
         inc_max_steps = env_int("RCD_INC_STEPS", ncls > 1 ? shared_steps : 4096, 1, 1 << 20);
         inc_small_bytes = env_int("RCD_INC_SMALL_KB", 512, 1, 1 << 20) * 1024;
         mw = false;
-        if ((graph_cut || incremental) && multi_wg_wanted(max_n)) {
+        slc = sliced::Choice{};
+        std::vector<RcdWg> map;
+        int capacity = cu_count();               // workgroups of the shared step loop that run at once
+        // (the device to itself: workgroups that wait for one another must all be running)
+        SlicedInc slices;
+        if (incremental && cus == cu_count()) slices = plan_sliced(g->host, cus);
+        if (slices.choice.inc) {
+            mw = true;
+            slc = slices.choice;
+            map = std::move(slices.map);
+            for (int i = 0; i < ncls; ++i) g->host[i].mwseg = slices.seg[i];
+            for (const RcdWg &m : map) g->host[m.cls].mw = m.W;
+        } else if ((graph_cut || incremental) && multi_wg_wanted(max_n)) {
             // Workgroups per class: what the device can hold at once, shared evenly, at most RCD_MW_MAX and no
             // more than one per RCD_MW_SLICE (2048) samples; classes too small to share keep one workgroup in the same launch.
             int per_cu = 0;
             const void *kfn = graph_cut ? reinterpret_cast<const void *>(rcd_k_gc_steps_mw)
                                         : reinterpret_cast<const void *>(rcd_k_inc_steps_mw);
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, RCD_STEP_THREADS, 0));
-            const int capacity = std::max(per_cu, 0) * cu_count();
+            capacity = std::max(per_cu, 0) * cu_count();
             // (measured on one 50 000-sample class: graph cut 1418 ms with one workgroup, 260 / 236 / 228 / 225 ms with
             // 12 / 16 / 24 / 32; incremental gains 627 / 599 / 586 / 590 ms)
             const int w_max = std::min(env_int("RCD_MW_MAX_WGS", 24, 1, RCD_MW_MAX), capacity / std::max(ncls, 1));
             const int mw_slice = env_int("RCD_MW_SLICE", 2048, 256, 1 << 20) / 256 * 256;    // samples a workgroup owns, at least
             if (w_max >= 2) {
-                std::vector<RcdWg> map;
                 for (int i = 0; i < ncls; ++i) {
                     RcdClass &c = g->host[i];
                     int W = std::min(w_max, std::max(1, c.ld / mw_slice));
@@ -613,24 +715,25 @@ struct Lane {
                     c.mwseg = seg;
                     for (int w = 0; w < W; ++w) map.push_back(RcdWg{i, w, W, 0});
                 }
-                if ((int)map.size() <= capacity && (int)map.size() <= RCD_MAX_SWEEP_WGS) {
-                    mw = true;
-                    mw_wgs = (int)map.size();
-                    mw_epoch = 0;
-                    mw_spin_ticks = (long long)env_int("RCD_MW_SPIN_MS", 2000, 0, 60000) * 100000LL;
-                    // a shared class steps about four times faster: four times the steps per call for the same wait
-                    if (ncls > 1)
-                        inc_max_steps = env_int("RCD_INC_STEPS", std::min(64, std::max(8, 1600000 / std::max(max_n, 1))), 1, 1 << 20);
-                    // with many classes in the launch an update launch gives each class a small share of the memory
-                    // bandwidth, and lists four times as long are better applied by the class's own workgroups
-                    // (20 classes of 50 000: 1.92 -> 1.86 s; one class alone: 774 -> 875 ms, so not there)
-                    if (ncls >= 4) inc_small_bytes = env_int("RCD_INC_SMALL_KB", 2048, 1, 1 << 20) * 1024;
-                    HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
-                    HIP_TRY(hipMemcpyAsync(g->classes_dev, g->host.data(), sizeof(RcdClass) * ncls, hipMemcpyHostToDevice, stream));
-                } else {
+                mw = (int)map.size() <= capacity && (int)map.size() <= RCD_MAX_SWEEP_WGS;
+                if (!mw)
                     for (RcdClass &c : g->host) { c.mw = 0; c.mwseg = 0; }
-                }
             }
+        }
+        if (mw) {
+            mw_wgs = (int)map.size();
+            RCD_TRY(take_units(mw_wgs, capacity));
+            mw_epoch = 0;
+            mw_spin_ticks = (long long)env_int("RCD_MW_SPIN_MS", 2000, 0, 60000) * 100000LL;
+            // a shared class steps about four times faster: four times the steps per call for the same wait
+            if (ncls > 1)
+                inc_max_steps = env_int("RCD_INC_STEPS", std::min(64, std::max(8, 1600000 / std::max(max_n, 1))), 1, 1 << 20);
+            // with many classes in the launch an update launch gives each class a small share of the memory
+            // bandwidth, and lists four times as long are better applied by the class's own workgroups
+            // (20 classes of 50 000: 1.92 -> 1.86 s; one class alone: 774 -> 875 ms, so not there)
+            if (ncls >= 4) inc_small_bytes = env_int("RCD_INC_SMALL_KB", 2048, 1, 1 << 20) * 1024;
+            HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
+            HIP_TRY(hipMemcpyAsync(g->classes_dev, g->host.data(), sizeof(RcdClass) * ncls, hipMemcpyHostToDevice, stream));
         }
         res = resident::Choice{};
         if (graph_cut && !mw) {
@@ -859,6 +962,7 @@ struct Lane {
     int finish(int rc)
     {
         hipError_t es = hipStreamSynchronize(stream);
+        give_units();
         if (prof && es == hipSuccess && rc == RCD_OK)
             for (int64_t b = prof_done; b < batch; ++b) read_events(b);
         float first_ms = 0.f;
@@ -1870,8 +1974,11 @@ static int partition_dataset_impl(int objective, const void *X_dev, int dt, int6
             // for every compute unit.  (Where that needs more room than there is, each lane asks again for its classes and
             // its share of the device.)
             ResidentInc inc_plan;
-            if (stored && (incremental || auto_incremental) && nl > 1 && !multi_wg_wanted(max_count)) {
+            if (stored && (incremental || auto_incremental) && nl > 1) {
                 RCD_TRY(sweep_setup());
+                if (plan_sliced(g.host, cu_count()).choice.inc) nl = 1;
+            }
+            if (stored && (incremental || auto_incremental) && nl > 1 && !multi_wg_wanted(max_count)) {
                 RCD_TRY(plan_resident_incremental(g.host, cu_count(), inc_plan));
                 if (inc_plan.choice.inc) nl = 1;
             }

@@ -164,8 +164,8 @@ template <typename S> struct Place {
     }
 };
 
-template <typename S>
-__device__ __forceinline__ void load_gains(double (&G)[S::KM][S::P], const double *g, int K, int n, int ld, const Place<S> &pl)
+template <typename S, typename PL>
+__device__ __forceinline__ void load_gains(double (&G)[S::KM][S::P], const double *g, int K, int n, int ld, const PL &pl)
 {
     const double RCD_GLOBAL *src = (const double RCD_GLOBAL *)g;
 #pragma unroll
@@ -185,8 +185,8 @@ __device__ __forceinline__ void load_gains(double (&G)[S::KM][S::P], const doubl
     }
 }
 
-template <typename S>
-__device__ __forceinline__ void store_gains(const double (&G)[S::KM][S::P], double *g, int K, int ld, const Place<S> &pl)
+template <typename S, typename PL>
+__device__ __forceinline__ void store_gains(const double (&G)[S::KM][S::P], double *g, int K, int ld, const PL &pl)
 {
     double RCD_GLOBAL *dst = (double RCD_GLOBAL *)g;
 #pragma unroll
@@ -261,13 +261,14 @@ __device__ __forceinline__ void best_candidate(const double (&G)[S::KM][S::P], i
     vstar = __builtin_amdgcn_readlane(s.v, src);
 }
 
-// v* is no longer a candidate of any block: the wave that owns it strikes it out of its registers.
+// v* is no longer a candidate of any block: the wave that owns it (its samples start at `first`) strikes it out of its
+// registers.
 template <typename S>
-__device__ __forceinline__ void strike(double (&G)[S::KM][S::P], int vstar, const Place<S> &pl)
+__device__ __forceinline__ void strike(double (&G)[S::KM][S::P], int vstar, int first, int lane)
 {
-    const int r = vstar - pl.wave * S::WAVE;
+    const int r = vstar - first;
     if (r < 0 || r >= S::WAVE) return;           // wave-uniform
-    const bool me = pl.lane == ((r & 127) >> 1);
+    const bool me = lane == ((r & 127) >> 1);
     update_at_index<0, S::P>((r >> 7) * 2 + (r & 1), [&](auto ic) {
         constexpr int i = decltype(ic)::value;
 #pragma unroll
@@ -329,9 +330,9 @@ __device__ __forceinline__ void take(Run &r, int js, int vstar, double best, int
 }
 
 // The caller's arrays, up to 64 picks at a time, by the last wave.
-template <typename S>
+template <typename S, typename PL>
 __device__ __forceinline__ void write_outputs(Run &r, int32_t *assign_out, int32_t *order_out, const int32_t *out_index,
-                                              const Place<S> &pl)
+                                              const PL &pl)
 {
     if (pl.wave == S::NW - 1 && pl.lane < r.held) {
         const int oi = out_index ? ((gci32)out_index)[r.held_v] : r.held_v;
@@ -426,7 +427,7 @@ rcd_k_gc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, 
 #pragma unroll
         for (int q = 0; q < S::Q; ++q) m[i][q] = pl.at(M, row, q);
         of[i] = js;
-        strike<S>(G, vstar, pl);
+        strike<S>(G, vstar, pl.wave * S::WAVE, pl.lane);
         take(r, js, vstar, best, pl.lane);
     };
     while (!r.done && !r.stop) {
@@ -708,7 +709,7 @@ rcd_k_inc_steps_res(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
                             const unsigned row = (unsigned)(vstar * ld) * 4u;
 #pragma unroll
                             for (int q = 0; q < Q; ++q) mp[u][q] = pl.at(M, row, q);
-                            strike<S>(G, vstar, pl);
+                            strike<S>(G, vstar, pl.wave * S::WAVE, pl.lane);
                             take(r, js, vstar, best, lane);
                             busy |= 1u << js;
                             pj[u] = js;

@@ -162,3 +162,60 @@ def test_thirty_two_workgroups_per_class(rcd, monkeypatch, route):
     steps = [0, 1, 4, 5, 6, 100, 2000, 4150, 8000, 8298, 8299]
     res = oracle.lockstep(S, cap, o1, a1, rel_tol=1e-5, objective=objective, check=steps)
     assert res["rc"] == 0 and res["checked"] == len(steps), res
+
+
+@pytest.mark.parametrize("K", [1, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("n,slice_", [(5121, 0), (2000, 256), (2049, 1024), (2300, 2048), (4100, 2048)])
+def test_slices_with_gains_in_registers_match_the_loop_in_memory(rcd, monkeypatch, n, slice_, K):
+    # every variant of the sliced loop (by slice and by blocks), a slice and a little, a last slice of one sample; the
+    # reference is the one-workgroup loop with the gains in memory, itself refereed above
+    print(f"sliced loop n={n} slice={slice_} K={K}", flush=True)
+    S = mixture_S(700 + n, n)
+    cap = oracle.quota(n, [1 + (3 * k) % 5 for k in range(K)])
+    results = []
+    for shared in (True, False):
+        monkeypatch.setenv("RCD_MW_MIN_N", "1" if shared else "0")
+        monkeypatch.setenv("RCD_RESIDENT", "1" if shared else "0")
+        if slice_:
+            monkeypatch.setenv("RCD_MW_SLICE", str(slice_))
+        a, o, f = rcd.partition_class(S=dev(S), cap=cap, mode=rcd.MODE_INCREMENTAL)
+        results.append((a.cpu().numpy(), o.cpu().numpy(), f))
+    for x, y in zip(*results):
+        assert np.array_equal(x, y)
+
+
+def test_shared_classes_of_two_threads_wait_for_each_other(rcd, monkeypatch):
+    # two calls whose workgroups wait for one another inside a launch need 190 compute units each: more than the device has
+    # at once, so one of them has to wait for the other's to be free; both give the answer of a call alone
+    import threading
+
+    monkeypatch.setenv("RCD_MW_MIN_N", "1")
+    monkeypatch.setenv("RCD_MW_SLICE", "256")
+    L, n, d, r = 19, 2500, 64, [1, 2, 1]
+    X = dev(si.make_class(seed=55, n=L * n, d=d, G=5))
+    labels = dev(np.repeat(np.arange(L), n).astype(np.int32))
+    size = rcd.dataset_workspace_bytes(L * n, L, n, len(r), rcd.MODE_STORED)[1]
+    spaces = [torch.empty(size, dtype=torch.uint8, device="cuda") for _ in range(2)]
+
+    def call(ws):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            a, o, f = rcd.partition_dataset(X, labels, L, r, float(d), rcd.MODE_INCREMENTAL, ws)
+            return a.cpu().numpy(), o.cpu().numpy(), f
+
+    torch.cuda.synchronize()
+    ref = call(spaces[0])
+    got = [[], []]
+
+    def work(i):
+        for _ in range(3):
+            got[i].append(call(spaces[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for res in got[0] + got[1]:
+        for x, y in zip(res, ref):
+            assert np.array_equal(x, y)
+    assert len(got[0]) == len(got[1]) == 3
