@@ -1407,28 +1407,24 @@ int check_common(int64_t n, int K)
 void reset_stats() { memset(g_stats, 0, sizeof g_stats); }
 
 // Stable counting sort of the sample indices by label: index_dev gets the classes end to end, count_host their sizes.
-// count_dev: L ints and a plan header (whose `bad` a label out of range raises), read back in one piece; nothing of the
-// sort waits for the host.  Waits for the stream.
+// count_dev: L ints and a plan header (whose `bad` a label out of range raises); the host gets both from the scan launch
+// through its pinned buffer, and nothing of the sort waits for it.  Waits for the stream.
 int split_by_label(const int32_t *labels, int64_t N, int L, int allow_unassigned, int nchunks, int32_t *chunk_hist,
                    int32_t *count_dev, int32_t *index_dev, int32_t *count_host, hipStream_t stream)
 {
     RCD_TRY(ensure_pinned());
     RcdPlan *flag = reinterpret_cast<RcdPlan *>(count_dev + L);
-    const size_t back = ((size_t)L + sizeof(RcdPlan) / 4) * 4;
-    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
+    int32_t *seen = reinterpret_cast<int32_t *>(g_pinned);
     hipLaunchKernelGGL(split::k_hist, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels, (long long)N, L, chunk_hist,
-                       flag, allow_unassigned);
-    hipLaunchKernelGGL(split::k_scan, dim3((unsigned)L), dim3(256), 0, stream, chunk_hist, nchunks, L, count_dev);
-    HIP_TRY(hipMemcpyAsync(g_pinned, count_dev, back, hipMemcpyDeviceToHost, stream));
+                       allow_unassigned);
+    hipLaunchKernelGGL(split::k_scan, dim3((unsigned)L), dim3(256), 0, stream, chunk_hist, nchunks, L, count_dev, flag, seen);
     hipLaunchKernelGGL(split::k_scatter, dim3(nchunks), dim3(64), (size_t)L * 4, stream, labels, (long long)N, L,
                        split::bits_of(L), (const int32_t *)chunk_hist, (const int32_t *)count_dev, (const RcdPlan *)flag,
                        index_dev);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(stream));
-    memcpy(count_host, g_pinned, (size_t)L * 4);
-    RcdPlan seen;
-    memcpy(&seen, reinterpret_cast<const int32_t *>(g_pinned) + L, sizeof seen);
-    return seen.bad ? RCD_ERR_BAD_LABEL : RCD_OK;
+    memcpy(count_host, seen, (size_t)L * 4);
+    return seen[L] ? RCD_ERR_BAD_LABEL : RCD_OK;
 }
 
 } // namespace

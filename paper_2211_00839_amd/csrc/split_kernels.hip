@@ -9,44 +9,71 @@ namespace split {
 
 constexpr int CHUNK = 1024;   // samples per chunk, one wave per chunk
 
-// chunk_hist[chunk][l] = number of samples with label l in the chunk; flags bad labels.
+// chunk_hist[chunk][l] = number of samples with label l in the chunk.  A bad label anywhere in the chunk is told by the
+// sign of its first count (the complement of it): no flag has to be cleared beforehand.
 // allow_unassigned: a label of -1 is not an error, the sample just belongs nowhere (worker shards of a
 // partition that left samples over).
+// Bound by the trip to memory, hence all of a wave's labels are asked for before the first is counted; up to 16 labels are
+// counted by ballots, since 64 lanes adding to eight counters in LDS take their turns.
 __global__ void __launch_bounds__(64)
-k_hist(const int32_t *__restrict__ labels, long long N, int L, int32_t *__restrict__ chunk_hist, RcdPlan *plan,
-       int allow_unassigned = 0)
+k_hist(const int32_t *__restrict__ labels, long long N, int L, int32_t *__restrict__ chunk_hist, int allow_unassigned)
 {
     extern __shared__ int s_cnt[];
     const int lane = threadIdx.x;
+    const long long base = (long long)blockIdx.x * CHUNK;
+    constexpr int GROUPS = CHUNK / 64;
+    int lab[GROUPS];
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+        const long long i = base + g * 64 + lane;
+        lab[g] = i < N ? labels[i] : -2;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        bad |= base + g * 64 + lane < N && (lab[g] < 0 || lab[g] >= L) && !(allow_unassigned && lab[g] == -1);
+    const bool any_bad = __any(bad);
+    int32_t *out = chunk_hist + (size_t)blockIdx.x * L;
+    if (L <= 16) {
+        int mine = 0;
+        for (int l = 0; l < L; ++l) {
+            int c = 0;
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) c += __popcll(__ballot(lab[g] == l));
+            mine = lane == l ? c : mine;
+        }
+        if (lane < L) out[lane] = lane == 0 && any_bad ? ~mine : mine;
+        return;
+    }
     for (int l = lane; l < L; l += 64) s_cnt[l] = 0;
     __syncthreads();
-    const long long base = (long long)blockIdx.x * CHUNK;
-    int bad = 0;
-    for (int g = 0; g < CHUNK / 64; ++g) {
-        const long long i = base + g * 64 + lane;
-        if (i < N) {
-            const int lab = labels[i];
-            if (lab >= 0 && lab < L) atomicAdd(&s_cnt[lab], 1);
-            else if (!(allow_unassigned && lab == -1)) bad = 1;
-        }
-    }
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+        if (lab[g] >= 0 && lab[g] < L) atomicAdd(&s_cnt[lab[g]], 1);
     __syncthreads();
-    for (int l = lane; l < L; l += 64) chunk_hist[(size_t)blockIdx.x * L + l] = s_cnt[l];
-    if (bad) plan->bad = 1;
+    for (int l = lane; l < L; l += 64) out[l] = l == 0 && any_bad ? ~s_cnt[l] : s_cnt[l];
 }
 
 // Per class: exclusive prefix of chunk_hist over chunks (in place) and the class total.  One workgroup per class, a run
 // of consecutive chunks per thread: with one thread per class walking all its chunks, a million labels in eight classes
 // took 128 us, 977 dependent trips to memory; here the chunks are read side by side (4.6 us).
+// Class 0's workgroup, which sees the signs, says whether a label was bad.  host (pinned memory): the class totals and behind
+// them that flag, written from here: a copy between this launch and the next cost a million labels ten of 43 us.
 __global__ void __launch_bounds__(256)
-k_scan(int32_t *__restrict__ chunk_hist, int nchunks, int L, int32_t *__restrict__ class_count)
+k_scan(int32_t *__restrict__ chunk_hist, int nchunks, int L, int32_t *__restrict__ class_count, RcdPlan *__restrict__ plan,
+       int32_t *__restrict__ host)
 {
     __shared__ int s_wave[4];
     const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int per = (nchunks + 255) / 256;
     const int c0 = min(tid * per, nchunks), c1 = min(c0 + per, nchunks);
     int sum = 0;
-    for (int c = c0; c < c1; ++c) sum += chunk_hist[(size_t)c * L + l];
+    bool bad = false;
+    for (int c = c0; c < c1; ++c) {
+        const int v = chunk_hist[(size_t)c * L + l];
+        bad |= v < 0;
+        sum += v < 0 ? ~v : v;
+    }
     int incl = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -60,16 +87,24 @@ k_scan(int32_t *__restrict__ chunk_hist, int nchunks, int L, int32_t *__restrict
     for (int c = c0; c < c1; ++c) {
         const int v = chunk_hist[(size_t)c * L + l];
         chunk_hist[(size_t)c * L + l] = run;
-        run += v;
+        run += v < 0 ? ~v : v;
     }
-    if (tid == 255) class_count[l] = run;
+    if (tid == 255) {
+        class_count[l] = run;
+        host[l] = run;
+    }
+    const int any_bad = __syncthreads_or(bad);
+    if (l == 0 && tid == 0) {
+        plan->bad = any_bad;
+        host[L] = any_bad;
+    }
 }
 
 // idx[offset of class l + rank] = i, rank = number of earlier samples with label l, the classes end to end in order.
 // One wave per chunk; every lane finds the lanes of its group of 64 that share its label with one ballot per bit of a
 // label (label_bits of them), so a group costs the same however many labels it holds (a loop over the distinct labels with
 // two barriers in each took 25 us for a million labels of eight classes, this takes 8.0), and all labels of the chunk are
-// on their way at once.  A bad label anywhere (plan->bad, from k_hist) and nothing is written: the host reads that flag
+// on their way at once.  A bad label anywhere (plan->bad, from k_scan) and nothing is written: the host reads that flag
 // only behind this launch.
 __global__ void __launch_bounds__(64)
 k_scatter(const int32_t *__restrict__ labels, long long N, int L, int label_bits, const int32_t *__restrict__ chunk_base,

@@ -146,3 +146,37 @@ def test_class_split_of_many_classes(rcd, L):
         at = np.flatnonzero(labels == c)
         assert sorted(order[at].tolist()) == list(range(len(at)))
         assert np.array_equal(np.bincount(assign[at], minlength=3), rcd.quota(len(at), r))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", [0, 1023, 1024, 4999])
+@pytest.mark.parametrize("K", [1, 4, 16])
+def test_a_bad_worker_anywhere_is_told_and_writes_nothing(rcd, K, where):
+    # the split carries a bad label in the sign of a chunk's first count (zero there or not), -1 stays nobody's
+    print(f"bad worker K={K} at {where}", flush=True)
+    assign = np.random.default_rng(where + K).integers(-1, K, 5000).astype(np.int32)
+    assign[1024:2048] = -1                       # a chunk without a single count
+    for bad in (K, -2):
+        assign[where] = bad
+        with pytest.raises(rcd.RcdError) as e:
+            rcd.worker_shards(torch.from_numpy(assign).cuda(), K)
+        assert e.value.status == 2
+    assign[where] = -1
+    _, offset = rcd.worker_shards(torch.from_numpy(assign).cuda(), K)
+    assert offset.tolist() == [int(np.sum((assign >= 0) & (assign < k))) for k in range(K + 1)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", [0, 1024, 4999])
+@pytest.mark.parametrize("L", [16, 17, 100])
+def test_a_bad_label_on_either_side_of_the_counting_by_ballots(rcd, L, where):
+    print(f"bad label L={L} at {where}", flush=True)
+    N = 5000
+    labels = np.random.default_rng(L).integers(0, L, N).astype(np.int32)
+    X = torch.zeros((N, 8), dtype=torch.float32, device="cuda")
+    ws = torch.empty(rcd.dataset_workspace_bytes(N, L, N, 2, rcd.MODE_STORED)[0], dtype=torch.uint8, device="cuda")
+    for bad in (L, -1):
+        labels[where] = bad
+        with pytest.raises(rcd.RcdError) as e:
+            rcd.partition_dataset(X, torch.from_numpy(labels).cuda(), L, np.array([1, 1], np.int32), 8.0, workspace=ws)
+        assert e.value.status == 2
