@@ -1101,41 +1101,52 @@ rcd_k_copy_check(const float *__restrict__ S, long long lds, float *__restrict__
 
 // ---------------------------------------------------------------------------
 // rcd_gain_sweep: gains[k][v] = sum_j max(0, S[j][v] - cur[k][j]) straight from the caller's matrix, whatever its pitch,
-// alignment and symmetry.  What bounds it is reading S once: copying S into the working layout first and sweeping that
-// moved it three times (5000 samples, 8 blocks: 160 us for the call, of which copy 40, sweep 40, five more launches;
-// now 57, this kernel 32; 20 000 samples 1255 -> 380, 4.2 TB/s).
-// A wave takes 256 columns, four per lane, and every fourth group of eight rows of its workgroup's chunk, those in flight
-// together; the coverage of eight rows is the same for the whole wave and comes through the scalar unit in one load.  Sums: eight rows in a tree, eight such
-// trees one after the other, those one after the other again, the four waves, the chunks in double (error against
-// 64 bits: no more than the row-wise sweep's).  Entries outside [0, 1] and NaN raise plan->bad: S + 0 makes -0 a +0, and
-// then exactly the valid entries have bits of at most 1.0f's.
+// alignment and symmetry.  What bounds it is reading S once and, from eight blocks on, the vector unit beside it (K
+// subtractions with clamp and as many additions per entry).
+// A wave takes 256 columns, four per lane, and every fourth group of four rows of its workgroup's chunk, those in flight
+// together.  Two such groups under way, one being added up, were slower (20 000 samples, four blocks: 284 us against 237).
+// The coverage of four rows is the same for the whole wave and comes through the scalar unit, four blocks at a time, asked
+// for while the four blocks before are added up: a trip of that unit is longer than one block's 36 instructions, and each
+// block's trip used to be waited for.  This kernel, before -> now in us: 5000 samples and eight blocks 32 -> 26, 20 000 and
+// eight 334 -> 257, and sixteen 766 -> 470.
+// Sums: four rows in a tree, `run` such trees one after the other, those one after the other again (up to four blocks once
+// more, `run` at a time), the four waves, the chunks in double (error against 64 bits: no more than the row-wise sweep's).  Entries outside [0, 1] and NaN are told in
+// flags[workgroup]: S + 0 makes -0 a +0, and then exactly the valid entries have bits of at most 1.0f's.
 // grid = (ceil(n / 256), chunks); part: chunks x K x n.
 // ---------------------------------------------------------------------------
+// Workgroups per compute unit that the grid aims at (measured, 20 000 samples: four blocks 3 / 4 / 5: 239 / 243 / 253 us, eight
+// 276 / 257 / 268, sixteen 2 / 3: 748 / 594; three are what their registers allow).
+constexpr int gain_columns_levels(int K) { return K <= 4 ? 3 : 2; }
+constexpr int gain_columns_per_cu(int K) { return K > 4 && K <= 8 ? 4 : 3; }
 template <int KB, bool VEC>
 __global__ void __launch_bounds__(256)
-rcd_k_gain_columns(const float *__restrict__ S, long long lds, int n, int K, const float *__restrict__ cur_, int rows,
-                   float *__restrict__ part, RcdPlan *plan)
+rcd_k_gain_columns(const float *__restrict__ S, long long lds, int n, int K, const float *__restrict__ cur_, int turns, int run,
+                   float *__restrict__ part, int32_t *__restrict__ flags)
 {
     __shared__ float red[3][KB][256];
+    __shared__ int s_bad;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j0 = blockIdx.y * rows, j1 = min(n, j0 + rows);
+    const int rows = 32 * turns, j0 = blockIdx.y * rows, j1 = min(n, j0 + rows);
     // the lane's columns: v0 .. v0 + 3 (16-byte loads), or v0, v0 + 64, v0 + 128, v0 + 192
     const int v0 = blockIdx.x * 256 + (VEC ? lane * 4 : lane);
     constexpr int VS = VEC ? 1 : 64;
     const ccf32 cur = (ccf32)cur_;
-    f32x4 hi[KB], lo[KB];
+    if (threadIdx.x == 0) s_bad = 0;
+    constexpr int LEVELS = gain_columns_levels(KB);
+    f32x4 top[LEVELS > 2 ? KB : 1], hi[KB], lo[KB];
 #pragma unroll
     for (int k = 0; k < KB; ++k) hi[k] = lo[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (f32x4 &t : top) t = (f32x4){0.f, 0.f, 0.f, 0.f};
     unsigned worst = 0;
-    constexpr int U = 8;
-    int trees = 0;
-    // Eight rows from j on.  INSIDE: all of them exist and all 256 columns of the tile; the loads then carry no conditions
+    constexpr int U = 4;
+    int trees = 0, runs = 0;
+    // Four rows from j on.  INSIDE: all of them exist and all 256 columns of the tile; the loads then carry no conditions
     // (with a test around each 16-byte load the compiler waited for every row before asking for the next: 678 us for
     // 20 000 samples and 8 blocks, the 4-byte form 376).
-    auto eight = [&](auto inside_tag, int j) {
+    auto load = [&](auto inside_tag, f32x4 (&m)[U], int j) __attribute__((always_inline)) {
         constexpr bool INSIDE = decltype(inside_tag)::value;
-        f32x4 m[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const gcf32 row = (gcf32)S + (size_t)(j + u) * lds + v0;
@@ -1149,40 +1160,96 @@ rcd_k_gain_columns(const float *__restrict__ S, long long lds, int n, int K, con
                 m[u].w = in && (INSIDE || v0 + 3 * VS < n) ? row[3 * VS] : 0.f;
             }
         }
+    };
+    auto check = [&](const f32x4 (&m)[U]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
             worst = max(max(max(__float_as_uint(m[u].x + 0.f), __float_as_uint(m[u].y + 0.f)),
                             max(__float_as_uint(m[u].z + 0.f), __float_as_uint(m[u].w + 0.f))), worst);
-        const bool flush = ++trees == 8;
-        if (flush) trees = 0;
+    };
+    auto term = [&](const f32x4 &m, float c) __attribute__((always_inline)) {
+        return (f32x4){clamp01(m.x - c), clamp01(m.y - c), clamp01(m.z - c), clamp01(m.w - c)};
+    };
+    auto flush = [&]() __attribute__((always_inline)) {
+        if (++trees < run) return;
+        trees = 0;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            hi[k] += lo[k];
+            lo[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        if constexpr (LEVELS > 2) {
+            if (++runs < run) return;
+            runs = 0;
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                top[k] += hi[k];
+                hi[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    // coverage of the four rows from j on for H blocks from k0 on
+    constexpr int H = KB < 4 ? KB : 4;
+    auto cover = [&](f32x4 (&c)[H], int j, int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const ccf32 ck = cur + (size_t)min(k0 + i, K - 1) * n + j;
+            c[i] = (f32x4){ck[0], ck[1], ck[2], ck[3]};
+        }
+    };
+    int j = j0 + wave * U;
+    if ((int)blockIdx.x * 256 + 256 <= n && j + U <= j1) {
+        f32x4 c[2][H];
+        cover(c[0], j, 0);
+        for (; j + U <= j1; j += 4 * U) {
+            f32x4 m[U];
+            load(std::true_type{}, m, j);
+            const int next = min(j + 4 * U, n - U);
+            if constexpr (KB > H) __builtin_amdgcn_sched_barrier(0);
+            static_assert(KB <= H || KB / H % 2 == 0, "the next rows' first blocks find c[0] free");
+#pragma unroll
+            for (int k0 = 0; k0 < KB; k0 += H) {
+                f32x4 (&now)[H] = c[k0 / H % 2];
+                if constexpr (KB > H) {
+                    if (k0 + H < KB) cover(c[(k0 / H + 1) % 2], j, k0 + H);
+                    else cover(c[(k0 / H + 1) % 2], next, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (k0 == 0) check(m);
+#pragma unroll
+                for (int i = 0; i < H; ++i)
+                    lo[k0 + i] += (term(m[0], now[i].x) + term(m[1], now[i].y)) + (term(m[2], now[i].z) + term(m[3], now[i].w));
+                if constexpr (KB > H) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (KB <= H) cover(c[0], next, 0);
+            flush();
+        }
+    }
+    // what is left: past the end of the rows no term
+    for (; j < j1; j += 4 * U) {
+        f32x4 m[U];
+        load(std::false_type{}, m, j);
+        check(m);
 #pragma unroll
         for (int k = 0; k < KB; ++k) {
             const ccf32 ck = cur + (size_t)min(k, K - 1) * n + j;
             f32x4 t[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // past the end: no term
-                const float c = INSIDE || j + u < j1 ? ck[INSIDE ? u : min(u, n - 1 - j)] : __builtin_inff();
-                t[u] = (f32x4){clamp01(m[u].x - c), clamp01(m[u].y - c), clamp01(m[u].z - c), clamp01(m[u].w - c)};
-            }
-            lo[k] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-            if (flush) {
-                hi[k] += lo[k];
-                lo[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
+            for (int u = 0; u < U; ++u) t[u] = term(m[u], j + u < j1 ? ck[min(u, n - 1 - j)] : __builtin_inff());
+            lo[k] += (t[0] + t[1]) + (t[2] + t[3]);
         }
-    };
-    int j = j0 + wave * U;
-    if ((int)blockIdx.x * 256 + 256 <= n)
-        for (; j + U <= j1; j += 4 * U) eight(std::true_type{}, j);
-    for (; j < j1; j += 4 * U) eight(std::false_type{}, j);
-    if (worst > 0x3f800000u) plan->bad = 1;
+        flush();
+    }
+    __syncthreads();
+    if (worst > 0x3f800000u) s_bad = 1;
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
         hi[k] += lo[k];
+        if constexpr (LEVELS > 2) hi[k] += top[k];
         if (wave > 0) *reinterpret_cast<f32x4 *>(&red[wave - 1][k][lane * 4]) = hi[k];
     }
     __syncthreads();
+    if (threadIdx.x == 0) flags[blockIdx.y * gridDim.x + blockIdx.x] = s_bad;
     if (wave > 0) return;
 #pragma unroll
     for (int k = 0; k < KB; ++k)
@@ -1197,10 +1264,18 @@ rcd_k_gain_columns(const float *__restrict__ S, long long lds, int n, int K, con
         }
 }
 
-// gains[k][v] = the chunks' sums added up in order.  grid = (ceil(n / 256), K).
+// gains[k][v] = the chunks' sums added up in order; *host_bad (pinned memory) = whether a workgroup of the launch before met
+// an entry outside [0, 1].  grid = (ceil(n / 256), K).
 extern "C" __global__ void __launch_bounds__(256)
-rcd_k_gain_total(const float *__restrict__ part, int chunks, int n, int K, float *__restrict__ gains)
+rcd_k_gain_total(const float *__restrict__ part, int chunks, int n, int K, float *__restrict__ gains,
+                 const int32_t *__restrict__ flags, int nflags, int32_t *__restrict__ host_bad)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        int bad = 0;
+        for (int i = threadIdx.x; i < nflags; i += 256) bad |= flags[i];
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) *host_bad = bad;
+    }
     const int v = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;
     if (v >= n) return;
     double g = 0.0;

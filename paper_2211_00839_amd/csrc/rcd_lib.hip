@@ -1714,32 +1714,35 @@ int rcd_gain_sweep(const float *S_dev, int64_t ld_s, int64_t n, int K, const flo
     RCD_TRY(sweep_setup());
     RCD_TRY(ensure_pinned());
     Carver cv(workspace_dev, workspace_bytes);
-    RcdPlan *flag = cv.take<RcdPlan>(1);
-    // Chunks of rows: about three workgroups per compute unit, at least 32 rows each (8 per wave); no more than the
-    // workspace's matrix has room for (n / K of them; a class of fewer than 32 K samples has the partial sums' 32).
+    // Chunks of rows: as many as fill the device once, every wave of a full chunk taking eight rows the same number of
+    // times.  From five blocks on, where that makes long chunks, a whole number of times as many: a chunk's sums are fp32 and the
+    // chunks' are added in double (20 000 samples, sixteen blocks: 27 chunks 486 us, nine 618; up to four blocks, which are bound
+    // by memory alone, 284 against 266, so those take a third level of sums instead).  No more chunks than the workspace's
+    // matrix has room for (n / K of them; a class of fewer than 32 K samples has the partial sums' 32).
+    const bool vec = (reinterpret_cast<uintptr_t>(S_dev) & 15) == 0 && ld_s % 4 == 0;
     const int tiles = (int)((n + 255) / 256);
-    int chunks = std::max(1, 3 * cu_count() / tiles);
-    chunks = (int)std::min<int64_t>(chunks, (n + 31) / 32);
-    chunks = std::max(1, (int)std::min<int64_t>(chunks, std::max<int64_t>(RCD_CMAX, n / K)));
-    const int rows = (int)((n + chunks - 1) / chunks);
-    chunks = (int)((n + rows - 1) / rows);
+    const int64_t room = std::max<int64_t>(RCD_CMAX, n / K), fill = std::max(1, gain_columns_per_cu(K) * cu_count() / tiles);
+    const int levels = gain_columns_levels(K);
+    const int64_t most = std::min(room, levels > 2 ? fill : fill * std::max<int64_t>(1, (n + 1024 * fill - 1) / (1024 * fill)));
+    const int turns = (int)((n + 32 * most - 1) / (32 * most));
+    const int chunks = (int)((n + 32 * turns - 1) / (32 * turns));
+    const int run = (int)std::ceil(std::pow(2.0 * turns, 1.0 / levels));      // the levels of a wave's sums equally long
+    int32_t *flags = cv.take<int32_t>((size_t)chunks * tiles);
     float *part = cv.take<float>((size_t)chunks * K * n);
     if (cv.fail) return RCD_ERR_WORKSPACE;
-    HIP_TRY(hipMemsetAsync(flag, 0, sizeof(RcdPlan), stream));
-    const bool vec = (reinterpret_cast<uintptr_t>(S_dev) & 15) == 0 && ld_s % 4 == 0;
-    void (*kernel)(const float *, long long, int, int, const float *, int, float *, RcdPlan *) =
+    void (*kernel)(const float *, long long, int, int, const float *, int, int, float *, int32_t *) =
         K <= 2 ? (vec ? rcd_k_gain_columns<2, true> : rcd_k_gain_columns<2, false>)
         : K <= 4 ? (vec ? rcd_k_gain_columns<4, true> : rcd_k_gain_columns<4, false>)
         : K <= 8 ? (vec ? rcd_k_gain_columns<8, true> : rcd_k_gain_columns<8, false>)
                  : (vec ? rcd_k_gain_columns<16, true> : rcd_k_gain_columns<16, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles, (unsigned)chunks), dim3(256), 0, stream, S_dev, (long long)ld_s, (int)n,
-                       K, cur_dev, rows, part, flag);
+                       K, cur_dev, turns, run, part, flags);
+    int32_t *host_bad = reinterpret_cast<int32_t *>(g_pinned);
     hipLaunchKernelGGL(rcd_k_gain_total, dim3((unsigned)((n + 255) / 256), (unsigned)K), dim3(256), 0, stream,
-                       (const float *)part, chunks, (int)n, K, gains_dev);
+                       (const float *)part, chunks, (int)n, K, gains_dev, (const int32_t *)flags, chunks * tiles, host_bad);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(g_pinned, flag, sizeof(RcdPlan), hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    return g_pinned->bad ? RCD_ERR_BAD_SIMILARITY : RCD_OK;
+    return *host_bad ? RCD_ERR_BAD_SIMILARITY : RCD_OK;
 }
 
 // objective: 0 = facility location, 1 = graph cut (stored S only)

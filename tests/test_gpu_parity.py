@@ -223,6 +223,26 @@ def test_gain_sweep_columns_of_any_matrix(rcd, n, K, pitch, shift):
         assert e.value.status == 7
 
 
+@pytest.mark.parametrize("K", [2, 6, 16])
+def test_gain_sweep_of_long_chunks(rcd, K):
+    # chunks of many turns: the third level of sums (up to four blocks), a whole number of times the chunks (more blocks)
+    n = 20011
+    print(f"gain sweep long chunks n={n} K={K}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    S = torch.rand(n, n + 1, generator=g, device="cuda")[:, :n]
+    cur = torch.rand(K, n, generator=g, device="cuda")
+    got = rcd.gain_sweep(S, cur).double()
+    for k in range(K):
+        ref = sum((S[a:a + 4096].double() - cur[k, a:a + 4096, None].double()).clamp_(min=0).sum(0) for a in range(0, n, 4096))
+        # the bound of the columns above: additions of a chunk of at most 2560 rows, 640 to a wave, one per term besides
+        assert bool(((got[k] - ref).abs() <= (15 + 2560 / 16) * 2.0 ** -24 * ref).all()), k
+    S[n - 1, n - 1] = 1.5
+    with pytest.raises(rcd.RcdError) as e:
+        rcd.gain_sweep(S, cur)
+    assert e.value.status == 7
+
+
 def test_gain_sweep_rejects_similarity_outside_unit_interval(rcd):
     S = mixture_S(5, 40)
     S[3, 4] = 1.5
