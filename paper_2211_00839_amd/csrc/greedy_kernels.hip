@@ -478,7 +478,9 @@ __device__ __forceinline__ void class_steps(RcdClass &st, StepShared &sh)
         }
         dev_store((gi32)&st.nneed, nneed);
         if (nneed > 0) {
-            const int tiles = (nR + st.tw - 1) / st.tw;
+            // (the pieces' chunks are those of the wide tiles: the same sums)
+            const int wide = st.tw == RCD_TILE_FEW ? RCD_TILE_FAST : st.tw;
+            const int tiles = (nR + wide - 1) / wide;
             int C = (st.target_items + tiles - 1) / tiles;
             C = C < 1 ? 1 : (C > RCD_CMAX ? RCD_CMAX : C);
             int rpc = (n + C - 1) / C;
@@ -1041,7 +1043,7 @@ extern "C" __global__ void rcd_k_init(const RcdClass *__restrict__ classes)
     const size_t ncur = (size_t)st.K * st.ld;
     for (size_t i = i0; i < ncur; i += stride) st.cur[i] = 0.f;
     for (int i = i0; i < st.ld; i += stride) st.perm[i] = i;
-    for (int i = i0; i < st.ld / RCD_TILE_RC; i += stride) st.tilecnt[i] = 0;
+    for (int i = i0; i < st.ld / min(st.tw, RCD_TILE_RC); i += stride) st.tilecnt[i] = 0;
     for (int i = i0; i < RCD_MW_INTS; i += stride) st.mwbuf[i] = 0;
     for (int i = i0; i < st.n && st.assign_out; i += stride) {
         const int oi = st.out_index ? st.out_index[i] : i;

@@ -171,6 +171,8 @@ bool carve_class(Carver &cv, RcdClass &c, int64_t n, int K, const int64_t *cap, 
 int sweep_items_bound(const RcdClass &c)
 {
     const int tiles0 = (c.n + c.tw - 1) / c.tw;
+    // (pieces: up to four tiles where the chunks were counted for one)
+    if (c.tw == RCD_TILE_FEW) return std::min(RCD_CMAX * tiles0, 4 * (c.target_items + (c.n + RCD_TILE_FAST - 1) / RCD_TILE_FAST));
     return std::min(RCD_CMAX * tiles0, c.target_items + tiles0);
 }
 
@@ -507,6 +509,22 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     return none;
 }
 
+// Whether a recompute sweep over these classes is better cut into pieces of 64 candidates than into the fast path's 256 x 256
+// tiles: while the wide tiles of a first sweep go round the device at most twice (they get fewer as candidates are taken).
+// Wide / pieces, whole calls in ms, d = 512: 100 classes of 500, sixteen blocks (400 tiles) 17.9 / 16.1, 50 of 700 (450) 88 / 77,
+// ten of 1000, four (160) 85 / 57, two of 1500 (72) 163 / 88, two of 3000 (288) 359 / 299; six of 2500 (600) 406 / 408.  bf16
+// multiplies are sixteen times as fast and leave nothing to share out.
+bool recompute_pieces_pay(const std::vector<RcdClass> &cls, int cus)
+{
+    int64_t tiles = 0;
+    for (const RcdClass &c : cls) {
+        if (c.mode != RCD_MODE_RECOMPUTE || c.tw != RCD_TILE_FAST || c.dt != RCD_F32 || c.ld > RCD_TILE_FEW_LD) return false;
+        tiles += (int64_t)(c.ld / 256) * (c.ld / 256);
+    }
+    const int mode = env_int("RCD_RC_PIECES", 1, 0, 2);
+    return mode == 2 || (mode == 1 && tiles <= 2 * cus);
+}
+
 // One group of classes on one stream.  The host keeps a few batches of rounds
 // queued ahead of the device: start(), then enqueue_batch() while fewer than
 // `depth` batches are unread and poll() to read the oldest one's progress record,
@@ -646,6 +664,8 @@ struct Lane {
         slot = slot_;
         prof = profile;
         ncls = (int)g->host.size();
+        if (recompute_pieces_pay(g->host, cus))
+            for (RcdClass &c : g->host) c.tw = RCD_TILE_FEW;
         const int per_class = std::max(1, target_total / ncls);
         items_ub = 0;
         int max_n = 0;
@@ -826,7 +846,10 @@ struct Lane {
         if (recompute) {
             const bool fast = first.tw == RCD_TILE_FAST;
             const bool f32 = first.dt == RCD_F32;
-            if (fast) {
+            if (first.tw == RCD_TILE_FEW) {
+                round_rc_lds = 0;
+                round_rc = fused ? rcd_k_round_rc_pieces<true> : rcd_k_round_rc_pieces<false>;
+            } else if (fast) {
                 RCD_TRY(fast_setup());
                 round_rc_lds = RCD_RC_FAST_LDS;
                 round_rc = f32 ? (fused ? rcd_k_round_rc_fast<float, true> : rcd_k_round_rc_fast<float, false>)

@@ -12,6 +12,8 @@
 #define RCD_TILE 256         // pitch granule of a stored matrix row (one wave reads 64 lanes x 4 floats at a time)
 #define RCD_TILE_RC 128      // candidate columns per sweep tile when S is recomputed, general path
 #define RCD_TILE_FAST 256    // the same on the fast path (aligned feature rows, a multiple of 128 bytes long)
+#define RCD_TILE_FEW 64      // the same where the fast path's tiles would leave the chip idle (fp32)
+#define RCD_TILE_FEW_LD 4096 // largest pitch for that: its tiles' counters fit where a wider tile's are (tilecnt, 256 bytes)
 #define RCD_ROWS_RC 256      // rows of one recomputed tile
 #define RCD_CMAX 32          // most row chunks a class's sweep is split into
 #define RCD_SWEEP_WAVES 16    // waves of a stored-S sweep workgroup: each streams one candidate row at a time

@@ -393,6 +393,156 @@ rcd_k_round_rc_fast(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans,
     round_tail<256, RCD_TILE_FAST, FUSE>(st, classes, plans, buf, tile, tiles, sh, s_flag);
 }
 
+namespace {
+
+// Few tiles: one (class, 64-candidate tile, row chunk) item, fp32 features on the fast path's conditions.  Four waves as
+// 2 x 2, a wave owns 128 rows x 32 candidates and goes down the chunk 256 rows at a time, straight from memory: lane l
+// reads 16 bytes of one candidate's row and of four rows, lanes 32-63 the second half of a 32-byte k group, as few::product does for
+// 32 x 32; two groups are multiplied while the next two are on their way.  k in the order of the other kernels, hence the
+// same similarities bit for bit; rows, halves, waves and chunks of a gain's sum in the order of recompute_body_fast, hence
+// the same gains.
+// What bounds the fast path on small classes is that a tile of 256 x 256 takes 112 us of a compute unit at d = 512 however few
+// there are; pieces a quarter as wide share the chip better.  Which classes: recompute_pieces_pay().
+template <int KS>
+__device__ __forceinline__ void recompute_pieces(const RcdClass &st, int tile, int chunk, float *red /* 2 x KS x 64 */)
+{
+    using namespace sim;
+    constexpr int TW = RCD_TILE_FEW, U = 2, A = 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1;
+    const int n = st.n, ld = st.ld, nneed = st.nneed;
+    const long long ldx = st.ldx64;
+    const gcf32 X = (gcf32) reinterpret_cast<const float *>(st.X);
+    const gci32 xi = (gci32)st.x_index;
+    const gcf32 sq = (gcf32)st.sq;
+    const int half = (lane >> 5) * 4, groups = st.d / 8;
+    int kb[KS];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) kb[i] = st.need[i < nneed ? i : nneed - 1];
+    const float exp_scale = st.exp_scale, scale2 = -2.f * exp_scale;
+    const int vcol = min(max(((gci32)st.perm)[tile * TW + wc * 32 + (lane & 31)], 0), n - 1);
+    const float sqv = sq[vcol] * exp_scale;
+    const gcf32 pb = X + (size_t)(xi ? xi[vcol] : vcol) * ldx + half;
+    float gsum[KS];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) gsum[i] = 0.f;
+    const int row_begin = chunk * st.rpc, row_end = min(n, row_begin + st.rpc);
+    for (int i0 = row_begin + wr * 128; i0 < row_end; i0 += RCD_ROWS_RC) {
+        gcf32 pa[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            const int i = min(i0 + a * 32 + (lane & 31), n - 1);
+            pa[a] = X + (size_t)(xi ? xi[i] : i) * ldx + half;
+        }
+        f32x16 acc[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a)
+#pragma unroll
+            for (int x = 0; x < 16; ++x) acc[a][x] = 0.f;
+        struct Batch { f32x4 a[U][A], b[U]; };
+        auto load = [&](Batch &f, int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                f.b[u] = *(gcf32x4)(pb + (g + u) * 8);
+#pragma unroll
+                for (int a = 0; a < A; ++a) f.a[u][a] = *(gcf32x4)(pa[a] + (g + u) * 8);
+            }
+        };
+        auto multiply = [&](const Batch &f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int a = 0; a < A; ++a)
+                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[u][a][e], f.b[u][e], acc[a], 0, 0, 0);
+        };
+        // (a row is a multiple of 128 bytes: the groups come in fours)
+        Batch f0, f1;
+        load(f0, 0);
+        for (int g = 0; g < groups; g += 2 * U) {
+            load(f1, g + U);
+            multiply(f0);
+            load(f0, min(g + 2 * U, groups - U));
+            multiply(f1);
+        }
+        // a lane holds column wc * 32 + (lane & 31), rows i0 + a * 32 + 8 rq + 4 (lane >> 5) + e
+        const bool edge = i0 + 128 > n;
+        const bool maybe_diag = __any(vcol >= i0 && vcol < i0 + 128);
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            if (i0 + a * 32 >= n) break;           // nobody's rows: no term
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                const int i = i0 + a * 32 + rq * 8 + half;
+                float q[4], s[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    q[e] = sq[edge ? min(i + e, n - 1) : i + e] * exp_scale;
+                    // a row past the end is nobody's: similarity 0, below every coverage
+                    if (edge && i + e >= n) q[e] = -__builtin_inff();
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s[e] = rbf_value(acc[a][rq * 4 + e], q[e], sqv, scale2);
+                    if (maybe_diag && i + e == vcol) s[e] = 1.f;
+                }
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    const f32x4 c = *(gcf32x4)((gcf32)st.cur + (size_t)kb[k] * ld + i);
+                    gsum[k] += clamp01(s[0] - c.x);
+                    gsum[k] += clamp01(s[1] - c.y);
+                    gsum[k] += clamp01(s[2] - c.z);
+                    gsum[k] += clamp01(s[3] - c.w);
+                }
+            }
+        }
+    }
+    // the two halves of a wave hold the same columns over different rows, and so do the waves wr = 0 and 1
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+        const float other = __shfl_xor(gsum[k], 32);
+        const float tot = lane < 32 ? gsum[k] + other : other + gsum[k];
+        if (lane < 32) red[(wr * KS + k) * TW + wc * 32 + lane] = tot;
+    }
+    __syncthreads();
+    const gf32 part = (gf32)st.part + (size_t)chunk * st.K * ld + (size_t)tile * TW;
+    for (int e = tid; e < KS * TW; e += 256) {
+        const int k = e / TW, c = e % TW;
+        if (k < nneed) dev_store(part + (size_t)st.need[k] * ld + c, red[k * TW + c] + red[(KS + k) * TW + c]);
+    }
+}
+
+} // namespace
+
+template <bool FUSE>
+__global__ void __launch_bounds__(256, 2)
+rcd_k_round_rc_pieces(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, int buf)
+{
+    __shared__ float red[2 * RCD_KMAX * RCD_TILE_FEW];
+    __shared__ StepShared sh;
+    __shared__ int s_flag;
+    const RcdPlan *plan = plans + buf;
+    const int item = blockIdx.x;
+    if (item >= plan->items) return;
+    const int ncls = plans[0].ncls;
+    const int32_t *prefix = plan_prefix(plans, buf);
+    const int c = ncls > 1 ? find_class(prefix, ncls, item) : 0;
+    RcdClass &st = classes[c];
+    const int local = item - prefix[c];
+    const int tiles = (st.nR + RCD_TILE_FEW - 1) / RCD_TILE_FEW;
+    const int tile = local % tiles;
+    const int chunk = local / tiles;
+    const int nneed = st.nneed;
+    if (nneed <= 1) recompute_pieces<1>(st, tile, chunk, red);
+    else if (nneed == 2) recompute_pieces<2>(st, tile, chunk, red);
+    else if (nneed <= 4) recompute_pieces<4>(st, tile, chunk, red);
+    else if (nneed <= 8) recompute_pieces<8>(st, tile, chunk, red);
+    else recompute_pieces<16>(st, tile, chunk, red);
+    round_tail<256, RCD_TILE_FEW, FUSE>(st, classes, plans, buf, tile, tiles, sh, &s_flag);
+}
+
 // Apply kernel of the recompute mode: there is no stored matrix, so the coverage
 // update cur_js(j) = max(cur_js(j), S(j, v*)) rebuilds the similarity columns it needs
 // from the features.  The sweep that follows subtracts these coverage values from tiles

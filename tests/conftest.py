@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -15,3 +16,11 @@ def pytest_configure(config):
 @pytest.fixture(scope="session")
 def golden_dir():
     return os.path.join(ROOT, "tests", "golden")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def nothing_left_over():
+    """Device memory that earlier modules' reference cycles still hold (a caught exception and its frames) is given back
+    before a module starts, not in the middle of a test that counts allocations."""
+    gc.collect()
+    yield

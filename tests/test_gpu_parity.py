@@ -424,6 +424,28 @@ def test_class_greedy_recompute_fast_path_edges(rcd, dtype, n, d, r):
     check_against_oracle(S_gpu, cap, assign.cpu().numpy(), order.cpu().numpy(), obj)
 
 
+@pytest.mark.parametrize("n,d,r", [(1, 32, [1]), (31, 32, [1, 1]), (64, 64, [2, 1, 1]), (65, 96, [1] * 16), (127, 32, [1, 3]),
+                                   (129, 512, [1] * 5), (256, 32, [1, 2]), (257, 64, [1] * 9), (640, 32, [1, 1, 2, 3]),
+                                   (4096, 32, [1, 1])])
+def test_recompute_pieces_give_the_wide_tiles_bits(rcd, monkeypatch, n, d, r):
+    # 64-candidate pieces against the 256 x 256 tiles: edges of waves, pieces and tiles, every number of blocks, the
+    # largest class that takes them; same gains, hence the same steps and objectives bit for bit
+    print(f"recompute pieces n={n} d={d} K={len(r)}", flush=True)
+    X = dev(si.make_class(seed=2600 + n, n=n, d=d, G=8, dtype="f32"))
+    cap = oracle.quota(n, r)
+    if n > 1000:
+        cap = np.minimum(cap, 20)                # the first rounds are enough
+    results = []
+    for mode in ("0", "2"):
+        monkeypatch.setenv("RCD_RC_PIECES", mode)
+        a, o, f = rcd.partition_class(X=X, cap=cap, sigma2=float(d))
+        results.append((a.cpu().numpy(), o.cpu().numpy(), f))
+    for x, y in zip(*results):
+        assert np.array_equal(x, y)
+    if n <= 1000:
+        check_against_oracle(rcd.similarity(X, float(d)).cpu().numpy(), cap, *results[1])
+
+
 def test_dataset_recompute_mode(rcd):
     ds = si.make_dataset(si.WORKLOADS["large"], L=3, n_c=400, d=128)
     N = ds.X.shape[0]
