@@ -15,8 +15,14 @@
  *     which groups of classes advance side by side) and the events of
  *     rcd_profile; per device, a record of one-time set-up (kernel attributes,
  *     the compute-unit count, the address of the static scratch array of
- *     rcd_similarity_static), guarded by a mutex.  Calls from different threads
- *     are independent as long as their buffers are.
+ *     rcd_similarity_static), guarded by a mutex, and a count of the compute
+ *     units that running calls have taken.  Calls from different threads
+ *     are independent as long as their buffers are, with one exception: the
+ *     partition calls that share a class among workgroups (incremental gains,
+ *     graph cut) need their workgroups to run at once, so such a call takes
+ *     compute units for as long as its greedy runs and, where not enough of
+ *     them are left, waits on the host, in order of arrival, until other
+ *     threads' calls give theirs back.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *   - Inputs are never modified.  The return value is an rcd_status; on any
  *     value other than RCD_OK the contents of output buffers are unspecified.

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cmath>
-#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -14,6 +13,7 @@
 
 #include "../../include/rcd.h"
 #include "rcd_state.h"
+#include "shared_units.h"
 #include "greedy_kernels.hip"
 #include "similarity_kernels.hip"
 #include "split_kernels.hip"
@@ -227,16 +227,7 @@ struct DeviceSetup {
 std::mutex g_setup_mutex;
 DeviceSetup g_dev[RCD_MAX_DEVICES];
 
-// Compute units taken by launches whose workgroups wait for one another, per device.  Two such launches that together need
-// more than the device has could each hold a part of it and wait for the rest for ever: a call takes its units before its
-// first such launch, waiting for calls of other threads to give theirs back, and gives them back when its stream is drained.
-// (It holds nothing else that such a call could wait for.)
-struct SharedUnits {
-    std::mutex mutex;
-    std::condition_variable freed;
-    int taken = 0;
-};
-SharedUnits g_shared_units[RCD_MAX_DEVICES];
+SharedUnits g_shared_units[RCD_MAX_DEVICES];   // per device
 
 // The current device's record, or null (and g_hip_err) if the device cannot be told.
 DeviceSetup *device_setup()
@@ -614,23 +605,15 @@ struct Lane {
     {
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev));
-        SharedUnits &u = g_shared_units[dev];       // (device_setup() has looked at the index)
-        std::unique_lock<std::mutex> lock(u.mutex);
         const int cus = cu_count(), want = std::min(cus, (int)(((int64_t)wgs * cus + capacity - 1) / capacity));
-        u.freed.wait(lock, [&] { return u.taken + want <= cus; });
-        u.taken += want;
-        units = &u;
+        g_shared_units[dev].take(want, cus);        // (device_setup() has looked at the index)
+        units = &g_shared_units[dev];
         units_taken = want;
         return RCD_OK;
     }
     void give_units()
     {
-        if (!units) return;
-        {
-            std::lock_guard<std::mutex> lock(units->mutex);
-            units->taken -= units_taken;
-        }
-        units->freed.notify_all();
+        if (units) units->give(units_taken);
         units = nullptr;
     }
 

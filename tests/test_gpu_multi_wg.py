@@ -185,13 +185,14 @@ def test_slices_with_gains_in_registers_match_the_loop_in_memory(rcd, monkeypatc
 
 
 def test_shared_classes_of_two_threads_wait_for_each_other(rcd, monkeypatch):
-    # two calls whose workgroups wait for one another inside a launch need 190 compute units each: more than the device has
-    # at once, so one of them has to wait for the other's to be free; both give the answer of a call alone
+    # two calls whose workgroups wait for one another inside a launch need 190 compute units each (with more than four blocks a
+    # unit holds one workgroup): more than the device has at once, so one of them has to wait for the other's to be free; both
+    # give the answer of a call alone.  The waiting itself is tested in test_shared_units.py
     import threading
 
     monkeypatch.setenv("RCD_MW_MIN_N", "1")
     monkeypatch.setenv("RCD_MW_SLICE", "256")
-    L, n, d, r = 19, 2500, 64, [1, 2, 1]
+    L, n, d, r = 19, 2500, 64, [1, 2, 1, 1, 2]
     X = dev(si.make_class(seed=55, n=L * n, d=d, G=5))
     labels = dev(np.repeat(np.arange(L), n).astype(np.int32))
     size = rcd.dataset_workspace_bytes(L * n, L, n, len(r), rcd.MODE_STORED)[1]
