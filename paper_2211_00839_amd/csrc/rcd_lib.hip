@@ -600,9 +600,12 @@ struct Lane {
                                g->plan_dev, gc_max_steps);
     }
 
-    // Take the compute units of `wgs` workgroups that wait for one another (at most `capacity` run at once).
+    // Take the compute units of `wgs` workgroups that wait for one another (at most `capacity` run at once).  What the caller
+    // has on the stream comes first: units taken before that is done would lie idle, and a caller whose stream waits for
+    // something that another thread does after a call of its own would wait for ever.
     int take_units(int wgs, int capacity)
     {
+        HIP_TRY(hipStreamSynchronize(stream));
         int dev = 0;
         HIP_TRY(hipGetDevice(&dev));
         const int cus = cu_count(), want = std::min(cus, (int)(((int64_t)wgs * cus + capacity - 1) / capacity));

@@ -220,3 +220,76 @@ def test_shared_classes_of_two_threads_wait_for_each_other(rcd, monkeypatch):
         for x, y in zip(res, ref):
             assert np.array_equal(x, y)
     assert len(got[0]) == len(got[1]) == 3
+
+
+def test_a_call_waiting_for_its_own_stream_keeps_no_other_call_waiting(rcd, monkeypatch):
+    # one call takes 21 compute units, another 240: not together.  The first one's stream is busy with the caller's own long
+    # kernel, so it cannot use any unit yet, and the second one has to get through meanwhile
+    import threading
+    import time
+
+    monkeypatch.setenv("RCD_MW_MIN_N", "1")
+    monkeypatch.setenv("RCD_MW_SLICE", "256")
+    L, n, d, r = 24, 2500, 64, [1, 2, 1, 1, 2]
+    X = dev(si.make_class(seed=56, n=L * n, d=d, G=5))
+    labels = dev(np.repeat(np.arange(L), n).astype(np.int32))
+    ws = torch.empty(rcd.dataset_workspace_bytes(L * n, L, n, len(r), rcd.MODE_STORED)[1], dtype=torch.uint8, device="cuda")
+    m = 5200
+    S = rcd.similarity(X[:m], float(d))
+    ws_class = torch.empty(rcd.class_workspace_bytes(m, len(r), rcd.MODE_INCREMENTAL), dtype=torch.uint8, device="cuda")
+
+    def one_class():
+        a, o, f = rcd.partition_class(S=S, cap=oracle.quota(m, r), mode=rcd.MODE_INCREMENTAL, workspace=ws_class)
+        return a.cpu().numpy(), o.cpu().numpy(), f
+
+    def data_set():
+        a, o, f = rcd.partition_dataset(X, labels, L, r, float(d), rcd.MODE_INCREMENTAL, ws)
+        return a.cpu().numpy(), o.cpu().numpy(), f
+
+    ref_class, ref_set = one_class(), data_set()
+    # how many cycles of torch's sleep make two seconds
+    t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    t[0].record()
+    torch.cuda._sleep(10_000_000)
+    t[1].record()
+    torch.cuda.synchronize()
+    cycles = int(10_000_000 * 2000.0 / t[0].elapsed_time(t[1]))
+    # a stream that gets on while `busy` sleeps (streams share a few hardware queues)
+    busy, free = torch.cuda.Stream(), None
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(cycles // 4)
+        slept = torch.cuda.Event()
+        slept.record()
+    for s in [torch.cuda.Stream() for _ in range(3)]:
+        with torch.cuda.stream(s):
+            torch.zeros(1, device="cuda")
+            done = torch.cuda.Event()
+            done.record()
+        time.sleep(0.02)
+        if done.query() and not slept.query():
+            free = s
+            break
+    assert free is not None
+    torch.cuda.synchronize()
+
+    got, queued = [], threading.Event()
+
+    def first():
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(cycles)
+            slept.record()
+            queued.set()
+            got.append(one_class())
+
+    thread = threading.Thread(target=first)
+    thread.start()
+    queued.wait()
+    time.sleep(0.3)                              # the first call is waiting by now
+    with torch.cuda.stream(free):
+        second = data_set()
+    still_asleep = not slept.query()
+    thread.join()
+    for res, ref in ((got[0], ref_class), (second, ref_set)):
+        for x, y in zip(res, ref):
+            assert np.array_equal(x, y)
+    assert still_asleep
