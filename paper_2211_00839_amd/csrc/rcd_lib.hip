@@ -527,6 +527,7 @@ struct Lane {
     int slot = 0;            // which pinned progress slots are this lane's
     int ncls = 0, rounds = 16, items_ub = 0, round_no = 0;
     bool recompute = false, fused = false, prof = false, finished = false;
+    bool again = false;      // a wait of the slices' workgroups ran out where others can do the work: run without slices
     bool incremental = false;   // stored S with incrementally maintained gains
     bool graph_cut = false;     // graph-cut function: stored S, the step loop keeps its own gains current
     int gc_max_steps = 4096;    // steps per class and launch (bounds a launch's duration)
@@ -642,8 +643,9 @@ struct Lane {
     // target_total: sweep workgroups per round this lane aims at.
     // sweep_target: workgroups the stored-S sweep launch aims at.
     // cus: this lane's share of the compute units.  inc_plan: what plan_resident_incremental says of them, if that is known.
+    // slices_allowed: classes may be cut into slices (not when that has been tried, see poll()).
     int start(Group &group, hipStream_t s, int slot_, int target_total, int sweep_target, int cus, const ResidentInc *inc_plan,
-              bool profile)
+              bool profile, bool slices_allowed)
     {
         g = &group;
         stream = s;
@@ -669,7 +671,11 @@ struct Lane {
         RcdPlan plan0;
         memset(&plan0, 0, sizeof plan0);
         plan0.ncls = ncls;
-        // the validation kernels may already have raised plans[0].bad: keep it
+        // the validation kernels may already have raised plans[0].bad: keep it (but a wait of the slices' that ran out is over)
+        if (!slices_allowed) {
+            for (RcdClass &c : g->host) c.mw = c.mwseg = 0;
+            HIP_TRY(hipMemcpyAsync(&g->plan_dev[0].bad, &plan0.bad, sizeof plan0.bad, hipMemcpyHostToDevice, stream));
+        }
         HIP_TRY(hipMemcpyAsync(&g->plan_dev[0].ncls, &plan0.ncls, sizeof(int32_t) * 5, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipMemcpyAsync(&g->plan_dev[1], &plan0, sizeof plan0, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipMemcpyAsync(g->classes_dev, g->host.data(), sizeof(RcdClass) * ncls, hipMemcpyHostToDevice, stream));
@@ -692,7 +698,7 @@ struct Lane {
         int capacity = cu_count();               // workgroups of the shared step loop that run at once
         // (the device to itself: workgroups that wait for one another must all be running)
         SlicedInc slices;
-        if (incremental && cus == cu_count()) slices = plan_sliced(g->host, cus);
+        if (incremental && cus == cu_count() && slices_allowed) slices = plan_sliced(g->host, cus);
         if (slices.choice.inc) {
             mw = true;
             slc = slices.choice;
@@ -951,6 +957,11 @@ struct Lane {
         ++polled;
         if (seen[0].bad == 2) {
             finished = true;
+            // Classes of these sizes can also be run where nobody waits for a workgroup that has not begun, and are, if the
+            // device has no room for all of a class's workgroups at once (another process, a long kernel of the caller's).
+            int max_n = 0;
+            for (const RcdClass &c : g->host) max_n = std::max(max_n, c.n);
+            again = mw && slc.inc && !multi_wg_wanted(max_n);
             snprintf(g_hip_err, sizeof g_hip_err,
                      res.inc ? "a workgroup's bounded wait for a helper workgroup's part of an update list ran out"
                              : "a workgroup's bounded wait at a grid barrier of the multi-workgroup step loop ran out");
@@ -1017,8 +1028,8 @@ struct Lane {
 // coverage updates (latency-bound, a few workgroups) overlap the other groups'
 // sweeps (bandwidth-bound, the whole chip).  Returns after all of them finished:
 // work the caller enqueues afterwards is ordered behind them.  Fills each
-// group's obj_dev and accumulates g_stats.  inc_plan: for one group, see Lane::start.
-int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc *inc_plan = nullptr)
+// group's obj_dev and accumulates g_stats.  inc_plan, slices_allowed: for one group, see Lane::start.
+int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc *inc_plan = nullptr, bool slices_allowed = true)
 {
     const int nl = (int)groups.size();
     if (nl < 1) return RCD_OK;
@@ -1033,7 +1044,8 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc
     int rc = RCD_OK;
     int started = 0;
     if (nl == 1) {
-        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, cu_count(), inc_plan, g_profile_on != 0);
+        rc = lanes[0].start(groups[0], stream, 0, target_total, sweep_target, cu_count(), inc_plan, g_profile_on != 0,
+                            slices_allowed);
         started = 1;
     } else {
         RCD_TRY(ensure_side_streams(nl));
@@ -1048,7 +1060,7 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc
         }
         const int per_lane = std::max(256, target_total * 2 / (nl + 1));
         for (int i = 0; i < nl && rc == RCD_OK; ++i) {
-            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, cu_count() / nl, nullptr, false);
+            rc = lanes[i].start(groups[i], g_side[i], i, per_lane, sweep_target, cu_count() / nl, nullptr, false, true);
             ++started;
         }
     }
@@ -1078,6 +1090,8 @@ int run_groups(std::vector<Group> &groups, hipStream_t stream, const ResidentInc
         const int r = lanes[i].finish(rc);
         if (rc == RCD_OK) rc = r;
     }
+    // (from the start: S is as it was, everything else is set anew)
+    if (nl == 1 && lanes[0].again) return run_groups(groups, stream, nullptr, false);
     return rc;
 }
 

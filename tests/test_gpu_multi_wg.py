@@ -293,3 +293,25 @@ def test_a_call_waiting_for_its_own_stream_keeps_no_other_call_waiting(rcd, monk
         for x, y in zip(res, ref):
             assert np.array_equal(x, y)
     assert still_asleep
+
+
+@pytest.mark.parametrize("sizes", [[5500], [700, 5200]])
+def test_sliced_classes_whose_workgroups_do_not_all_run_end_on_the_loops_that_need_no_other(rcd, monkeypatch, sizes):
+    # the bound of the wait set to zero from the host stands for a device that others hold: classes below the sizes of the older
+    # shared loop give the answer of one workgroup each instead of an error
+    print(f"slices that do not all run: {sizes}", flush=True)
+    d, r = 32, [1, 2, 1, 3, 1, 1, 2, 1]
+    X = dev(si.make_class(seed=57, n=sum(sizes), d=d, G=5))
+    labels = dev(np.repeat(np.arange(len(sizes)), sizes).astype(np.int32))
+    size = rcd.dataset_workspace_bytes(sum(sizes), len(sizes), max(sizes), len(r), rcd.MODE_STORED)[1]
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+
+    def call():
+        a, o, f = rcd.partition_dataset(X, labels, len(sizes), r, float(d), rcd.MODE_INCREMENTAL, ws)
+        return a.cpu().numpy(), o.cpu().numpy(), f
+
+    ref = call()
+    monkeypatch.setenv("RCD_MW_SPIN_MS", "0")
+    got = call()
+    for x, y in zip(got, ref):
+        assert np.array_equal(x, y)
