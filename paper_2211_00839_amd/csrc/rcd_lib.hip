@@ -13,6 +13,7 @@
 
 #include "../../include/rcd.h"
 #include "rcd_state.h"
+#include "launch_rules.h"
 #include "shared_units.h"
 #include "greedy_kernels.hip"
 #include "similarity_kernels.hip"
@@ -462,7 +463,7 @@ struct SlicedInc {
 };
 
 // Taken from 5121 samples in the largest class on, where a class no longer fits one workgroup's registers or does so with
-// too few left, and from 2561 on for a single class of more than four blocks (5120 fit then, but one pick at a time).
+// too few left; single classes of more than four blocks from where rules::sliced_from() says.
 // Measured, the loops taken otherwise / this one, in ms: one class of 50 000, eight blocks 587 / 383 (the whole call), of
 // 12 000, four 133 / 70, of 8000, eight 73 / 46, of 6000, three 45 / 32, of 5000, eight 33.8 / 29.4, of 3500, seven
 // 22.3 / 19.5; 20 classes of 8000, four 89 / 66, ten of 6000, six 65 / 46.  Below: 5000 and four blocks 20.0 / 28.0, 2000 and
@@ -476,7 +477,7 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     if (ncls < 1 || env_int("RCD_RESIDENT", 1, 0, 1) == 0) return none;
     int max_n = 0;
     for (const RcdClass &c : cls) max_n = std::max(max_n, c.n);
-    const int min_n = env_int("RCD_MW_MIN_N", ncls == 1 && cls[0].K > 4 ? 2561 : 5121, 0, 0x7fffffff);
+    const int min_n = env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, cls[0].K), 0, 0x7fffffff);
     if (min_n == 0 || max_n < min_n) return none;
     const int w_max = std::min(env_int("RCD_MW_MAX_WGS", RCD_MW_MAX, 1, RCD_MW_MAX), cus / ncls);
     if (w_max < 2) return none;
