@@ -501,20 +501,15 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     return none;
 }
 
-// Whether a recompute sweep over these classes is better cut into pieces of 64 candidates than into the fast path's 256 x 256
-// tiles: while the wide tiles of a first sweep go round the device at most twice (they get fewer as candidates are taken).
-// Wide / pieces, whole calls in ms, d = 512: 100 classes of 500, sixteen blocks (400 tiles) 17.9 / 16.1, 50 of 700 (450) 88 / 77,
-// ten of 1000, four (160) 85 / 57, two of 1500 (72) 163 / 88, two of 3000 (288) 359 / 299; six of 2500 (600) 406 / 408.  bf16
-// multiplies are sixteen times as fast and leave nothing to share out.
+// Whether a recompute sweep over these classes is cut into pieces of 64 candidates instead of the fast path's 256 x 256 tiles:
+// where rules::recompute_in_pieces() says.  bf16 multiplies are sixteen times as fast and leave nothing to share out.
 bool recompute_pieces_pay(const std::vector<RcdClass> &cls, int cus)
 {
-    int64_t tiles = 0;
-    for (const RcdClass &c : cls) {
+    for (const RcdClass &c : cls)
         if (c.mode != RCD_MODE_RECOMPUTE || c.tw != RCD_TILE_FAST || c.dt != RCD_F32 || c.ld > RCD_TILE_FEW_LD) return false;
-        tiles += (int64_t)(c.ld / 256) * (c.ld / 256);
-    }
     const int mode = env_int("RCD_RC_PIECES", 1, 0, 2);
-    return mode == 2 || (mode == 1 && tiles <= 2 * cus);
+    return mode == 2 || (mode == 1 && rules::recompute_in_pieces([&](int i) { return cls[i].n; }, (int)cls.size(), cls[0].d,
+                                                                 cls[0].K, cus));
 }
 
 // One group of classes on one stream.  The host keeps a few batches of rounds
