@@ -255,12 +255,14 @@ def test_large_class_one_full_class_incremental(rcd, monkeypatch):
     assert stats["steps"] == w.n_c
     assert np.bincount(a, minlength=8).tolist() == cap.tolist()
     assert np.array_equal(np.sort(o), np.arange(w.n_c))
-    # a class this size is shared among several workgroups: the one-workgroup loop must give the same bits
-    monkeypatch.setenv("RCD_MW_MIN_N", "0")
-    a1, o1, f1 = rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL)
-    monkeypatch.delenv("RCD_MW_MIN_N")
-    print(f"  one workgroup: stats {rcd.last_stats()}", flush=True)
-    assert np.array_equal(a1.cpu().numpy(), a) and np.array_equal(o1.cpu().numpy(), o) and np.array_equal(f1, f)
+    # a class this size is cut into slices with their gains in registers: the shared loop that keeps them in memory (which
+    # serves twenty such classes at once) and the one-workgroup loop must give the same bits
+    for switch, what in (("RCD_RESIDENT", "gains in memory"), ("RCD_MW_MIN_N", "one workgroup")):
+        monkeypatch.setenv(switch, "0")
+        a1, o1, f1 = rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL)
+        monkeypatch.delenv(switch)
+        print(f"  {what}: stats {rcd.last_stats()}", flush=True)
+        assert np.array_equal(a1.cpu().numpy(), a) and np.array_equal(o1.cpu().numpy(), o) and np.array_equal(f1, f)
     # objectives from the definition, on the device (max over the block's columns, summed in double)
     for k in (0, 7):
         members = torch.from_numpy(np.flatnonzero(a == k)).cuda()

@@ -3,7 +3,8 @@ facility-location function of Section 4, gains kept current by differences).  Wh
 a class's blocks overlap, one pass applies them all and reads a row of S once; the library does that for
 classes from 16 384 samples on.  Here the tuning switches RCD_INC_FUSE_MIN_N / RCD_INC_FUSE_PCT bring it down
 to classes the oracle referees at every step: the fused pass must give the list-by-list update's results bit
-for bit (same terms, same order), in the one-workgroup step loop and in the shared one."""
+for bit (same terms, same order), in the one-workgroup step loop, in the shared one and in the one that cuts classes into
+slices with their gains in registers."""
 import numpy as np
 import pytest
 
@@ -33,14 +34,15 @@ def mixture_S(seed, n, d=16):
     return oracle.similarity(si.make_class(seed=seed, n=n, d=d), float(d))
 
 
-def run(rcd, monkeypatch, S, cap, fused, pct=50, shared=False, small_kb=None, blocks=8):
+def run(rcd, monkeypatch, S, cap, fused, pct=50, shared=False, small_kb=None, blocks=8, sliced=False):
     monkeypatch.setenv("RCD_INC_FUSE_MIN_N", "1" if fused else "0")
     monkeypatch.setenv("RCD_INC_FUSE_BLOCKS", str(blocks))     # waiting blocks per workgroup of the fused pass
     monkeypatch.setenv("RCD_INC_FUSE_PCT", str(pct))
-    monkeypatch.setenv("RCD_MW_MIN_N", "1" if shared else "0")
+    monkeypatch.setenv("RCD_MW_MIN_N", "1" if shared or sliced else "0")
     monkeypatch.setenv("RCD_MW_SLICE", "256")
-    # (classes of this size keep their gains in registers unless told otherwise, and then no update launch is made)
-    monkeypatch.setenv("RCD_RESIDENT", "0")
+    # (classes of this size keep their gains in registers unless told otherwise, and then no update launch is made, except by
+    # slices)
+    monkeypatch.setenv("RCD_RESIDENT", "1" if sliced else "0")
     if small_kb is not None:
         monkeypatch.setenv("RCD_INC_SMALL_KB", str(small_kb))
     a, o, f = rcd.partition_class(S=dev(S), cap=cap, mode=rcd.MODE_INCREMENTAL)
@@ -48,18 +50,19 @@ def run(rcd, monkeypatch, S, cap, fused, pct=50, shared=False, small_kb=None, bl
     return a.cpu().numpy(), o.cpu().numpy(), f, stats
 
 
-@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("loop", ["one workgroup", "shared", "sliced"])
 @pytest.mark.parametrize("n,r,pct,blocks", [(1500, [1, 1, 2, 4], 50, 8), (2100, [1, 1, 1, 2, 2, 3, 4, 6], 50, 8),
                                             (2100, [1, 1, 1, 2, 2, 3, 4, 6], 1, 3), (2100, [1, 1, 1, 2, 2, 3, 4, 6], 30, 2),
                                             (1000, [3, 1, 4, 1, 2, 2, 1, 3, 4, 4, 1, 2], 1, 4), (257, [5, 5], 1, 8),
                                             (3000, [1, 2, 3], 10, 2)])
-def test_fused_pass_gives_the_list_by_list_bits(rcd, monkeypatch, shared, n, r, pct, blocks):
-    print(f"fused update: n={n} K={len(r)} pct={pct} blocks per workgroup={blocks} shared={shared}", flush=True)
+def test_fused_pass_gives_the_list_by_list_bits(rcd, monkeypatch, loop, n, r, pct, blocks):
+    print(f"fused update: n={n} K={len(r)} pct={pct} blocks per workgroup={blocks} loop={loop}", flush=True)
+    which = dict(shared=loop == "shared", sliced=loop == "sliced")
     S = mixture_S(500 + n, n)
     cap = oracle.quota(n, r)
     # lists of more than one row go to the update launches, so that the fused pass sees sparse lists too
-    a1, o1, f1, s1 = run(rcd, monkeypatch, S, cap, fused=True, pct=pct, shared=shared, small_kb=1, blocks=blocks)
-    a0, o0, f0, s0 = run(rcd, monkeypatch, S, cap, fused=False, shared=shared, small_kb=1)
+    a1, o1, f1, s1 = run(rcd, monkeypatch, S, cap, fused=True, pct=pct, small_kb=1, blocks=blocks, **which)
+    a0, o0, f0, s0 = run(rcd, monkeypatch, S, cap, fused=False, small_kb=1, **which)
     # every block's first list is the whole class: they all wait for one update launch, and the share is met
     assert s1["sweeps"] >= len(cap) and s0["sweeps"] >= len(cap)
     assert np.array_equal(a1, a0) and np.array_equal(o1, o0) and np.array_equal(f1, f0)

@@ -1,8 +1,10 @@
 """GPU parity of the step loops that share a class among several workgroups (incremental-gain route and
-graph-cut function, Algorithm 1's inner loop for large classes).  The library takes them from 16 384 samples
-on; here the tuning switches RCD_MW_MIN_N / RCD_MW_SLICE bring them down to classes the oracle referees at
-every step.  They must give the one-workgroup loops' results bit for bit, and a barrier wait that runs out
-must come back as an error with every kernel finished."""
+graph-cut function, Algorithm 1's inner loop for large classes).  The incremental route cuts classes into slices whose
+gains sit in registers ("inc"), from 5121 samples on and single classes of many blocks earlier; where the slices would be
+too large for that, and with the graph-cut function ("gc"), classes of 16 384 samples and more are shared by loops that
+keep the gains in memory ("inc-memory").  Here the tuning switches RCD_MW_MIN_N / RCD_MW_SLICE / RCD_RESIDENT bring all
+three to classes the oracle referees at every step.  They must give the one-workgroup loops' results bit for bit, and a
+barrier wait that runs out must come back as an error with every kernel finished."""
 import numpy as np
 import pytest
 
@@ -34,8 +36,12 @@ def mixture_S(seed, n, d=16):
     return oracle.similarity(si.make_class(seed=seed, n=n, d=d), float(d))
 
 
+ROUTES = ["inc", "inc-memory", "gc"]
+
+
 def run(rcd, monkeypatch, S, cap, route, shared, slice_=256):
     monkeypatch.setenv("RCD_MW_MIN_N", "1" if shared else "0")
+    monkeypatch.setenv("RCD_RESIDENT", "0" if route == "inc-memory" else "1")
     monkeypatch.setenv("RCD_MW_SLICE", str(slice_))
     if route == "gc":
         a, o, f = rcd.partition_class_graph_cut(dev(S), cap)
@@ -44,7 +50,7 @@ def run(rcd, monkeypatch, S, cap, route, shared, slice_=256):
     return a.cpu().numpy(), o.cpu().numpy(), f
 
 
-@pytest.mark.parametrize("route", ["inc", "gc"])
+@pytest.mark.parametrize("route", ROUTES)
 @pytest.mark.parametrize("n,r,slice_", [(600, [1, 1, 2, 4], 256), (1300, [2, 1], 256), (2100, [1, 1, 1, 2, 2, 3, 4, 6], 512),
                                         (1000, [3, 1, 4, 1, 2, 2, 1, 3, 4, 4, 1, 2, 3, 3, 2, 1], 256), (257, [5], 256),
                                         (3000, [1, 2, 3], 256)])
@@ -63,7 +69,7 @@ def test_shared_class_matches_one_workgroup_and_the_oracle(rcd, monkeypatch, rou
         assert abs(f1[k] - ref) <= 1e-4 * abs(ref) + 1e-9
 
 
-@pytest.mark.parametrize("route", ["inc", "gc"])
+@pytest.mark.parametrize("route", ROUTES)
 def test_shared_class_exact_ties_zero_quotas_and_leftovers(rcd, monkeypatch, route):
     # constant similarity: every candidate ties at every step, the lowest index must win whichever workgroup owns it
     n, c = 1500, 0.25
@@ -87,11 +93,13 @@ def test_shared_class_exact_ties_zero_quotas_and_leftovers(rcd, monkeypatch, rou
     assert res["rc"] == 0 and res["checked"] == 1200, res
 
 
-@pytest.mark.parametrize("graph_cut", [False, True])
-def test_data_set_with_shared_and_unshared_classes(rcd, monkeypatch, graph_cut):
+@pytest.mark.parametrize("route", ROUTES)
+def test_data_set_with_shared_and_unshared_classes(rcd, monkeypatch, route):
     # classes of very different sizes in one launch: the large ones are shared, the small ones keep one workgroup
+    graph_cut = route == "gc"
     monkeypatch.setenv("RCD_MW_MIN_N", "1")
     monkeypatch.setenv("RCD_MW_SLICE", "256")
+    monkeypatch.setenv("RCD_RESIDENT", "0" if route == "inc-memory" else "1")
     sizes = np.array([40, 1500, 0, 700, 3, 2300, 260])
     L, N, d, r = len(sizes), int(sizes.sum()), 64, [1, 2, 3, 1, 1]
     X = si.make_class(seed=401, n=N, d=d, G=5)
@@ -129,7 +137,7 @@ def test_data_set_with_shared_and_unshared_classes(rcd, monkeypatch, graph_cut):
     assert np.array_equal(a0.cpu().numpy(), assign) and np.array_equal(o0.cpu().numpy(), order) and np.array_equal(f0, obj)
 
 
-@pytest.mark.parametrize("route", ["inc", "gc"])
+@pytest.mark.parametrize("route", ROUTES)
 def test_a_barrier_wait_that_runs_out_is_reported_and_every_kernel_exits(rcd, monkeypatch, route):
     # the bound of a barrier wait set to zero from the host: the first workgroup to arrive finds the others
     # missing, raises the flag, every workgroup falls through and the call returns an error; the next call,
@@ -147,11 +155,12 @@ def test_a_barrier_wait_that_runs_out_is_reported_and_every_kernel_exits(rcd, mo
     assert res["rc"] == 0 and res["checked"] == 2000, res
 
 
-@pytest.mark.parametrize("route", ["inc", "gc"])
+@pytest.mark.parametrize("route", ROUTES)
 def test_thirty_two_workgroups_per_class(rcd, monkeypatch, route):
     # the most workgroups a class can have (the polling wave holds one post per lane, 32 of them here), on a class
-    # of 33 slices of 256 samples; same bits as one workgroup, sampled steps refereed by the oracle
-    n = 8300
+    # of 32 slices of 256 samples (one more sample and its pitch would make slices of 512, 17 of them); same bits as one
+    # workgroup, sampled steps refereed by the oracle
+    n = 8192
     S = mixture_S(33, n)
     cap = oracle.quota(n, [1, 2, 1, 3, 1])
     monkeypatch.setenv("RCD_MW_MAX_WGS", "32")
@@ -159,7 +168,7 @@ def test_thirty_two_workgroups_per_class(rcd, monkeypatch, route):
     a0, o0, f0 = run(rcd, monkeypatch, S, cap, route, shared=False)
     assert np.array_equal(a1, a0) and np.array_equal(o1, o0) and np.array_equal(f1, f0)
     objective = "gc" if route == "gc" else "fl"
-    steps = [0, 1, 4, 5, 6, 100, 2000, 4150, 8000, 8298, 8299]
+    steps = [0, 1, 4, 5, 6, 100, 2000, 4150, 8000, 8190, 8191]
     res = oracle.lockstep(S, cap, o1, a1, rel_tol=1e-5, objective=objective, check=steps)
     assert res["rc"] == 0 and res["checked"] == len(steps), res
 
