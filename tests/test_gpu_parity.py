@@ -235,8 +235,18 @@ def test_gain_sweep_of_long_chunks(rcd, K):
     got = rcd.gain_sweep(S, cur).double()
     for k in range(K):
         ref = sum((S[a:a + 4096].double() - cur[k, a:a + 4096, None].double()).clamp_(min=0).sum(0) for a in range(0, n, 4096))
-        # the bound of the columns above: additions of a chunk of at most 2560 rows, 640 to a wave, one per term besides
-        assert bool(((got[k] - ref).abs() <= (15 + 2560 / 16) * 2.0 ** -24 * ref).all()), k
+        # fp32 sums of non-negative terms, each addition rounding by 2^-24 of its result: the term 1, four rows 2, the levels of
+        # a wave 6 + 6 + 4 (140 fours, six at a time) or at most 8 + 7 (54), joining them 2, the waves 3, the result 1
+        assert bool(((got[k] - ref).abs() <= 25 * 2.0 ** -24 * ref).all()), k
+    # One number to a column makes the roundings of all waves and chunks the same, so that they do not average out.  Root mean
+    # square of the relative error, by these sums taken on the host (numpy, columns as here): 7.5e-8 with three levels, 8.3e-8
+    # with two where they are meant; a level left out 1.8e-7 and 4.0e-7, levels three times as long 1.5e-7 and 1.6e-7, a third
+    # as long 2.7e-7 and 2.0e-7.  (Four equal terms add up without rounding.)
+    column = torch.rand(n, generator=g, device="cuda")
+    S[:] = column
+    got = rcd.gain_sweep(S, torch.zeros(K, n, device="cuda")).double()
+    error = (got - n * column.double()) / (n * column.double()).clamp_(min=1e-30)
+    assert bool((error.square().mean(1).sqrt() <= 1.2e-7).all()), error.square().mean(1).sqrt()
     S[n - 1, n - 1] = 1.5
     with pytest.raises(rcd.RcdError) as e:
         rcd.gain_sweep(S, cur)
