@@ -464,9 +464,11 @@ struct SlicedInc {
 
 // Taken from 5121 samples in the largest class on, where a class no longer fits one workgroup's registers or does so with
 // too few left; single classes of more than four blocks from where rules::sliced_from() says.
-// Measured, the loops taken otherwise / this one, in ms: one class of 50 000, eight blocks 587 / 383 (the whole call), of
-// 12 000, four 133 / 70, of 8000, eight 73 / 46, of 6000, three 45 / 32, of 5000, eight 33.8 / 29.4, of 3500, seven
-// 22.3 / 19.5; 20 classes of 8000, four 89 / 66, ten of 6000, six 65 / 46.  Below: 5000 and four blocks 20.0 / 28.0, 2000 and
+// Measured, the loops taken otherwise / this one, in ms: one class of 50 000, eight blocks 586 / 385 (the whole call), of
+// 20 000, one block 194 / 144, sixteen 263 / 160, of 12 000, four 133 / 70, of 8000, eight 73 / 46, of 6000, one 43 / 38, three 45 / 32,
+// sixteen 56 / 42, of 5000, eight 33.8 / 29.4, of 3500, seven 22.3 / 19.5; 20 classes of 8000, one block 74 / 65, four 89 / 66,
+// sixteen 147 / 114, ten of 6000, six 65 / 46, ten of 5121, sixteen 63 / 58; one of 6000 beside thirty of 500, four 49 / 36, sixteen
+// 55 / 53.  Below: 5000 and four blocks 20.0 / 28.0, 2000 and
 // twelve 8.0 / 12.2, ten classes of 5000 and eight 42.9 / 43.6.
 // Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048 (20 000 samples
 // 118 / 131, 12 000 70 / 77; of 512, 12 000 samples 73); where there are not even those, the loops in memory serve.

@@ -5,14 +5,15 @@
 // What bounds a step of a shared class is waiting: the workgroups tell each other their best candidates, fetch row v* of
 // S, tell each other which coverage values rose, fetch the rows of that list.  rcd_k_inc_steps_mw walks this chain once per
 // step, with the gains in L2.  Here
-//   - the slice's gains sit in registers (512 threads hold 2048 samples x 16 blocks or 4096 x 8), so the scan is
-//     arithmetic (as in resident_kernels.hip, whose helpers this loop uses);
+//   - the slice's gains sit in registers (512 threads hold up to 2048 samples x 16 blocks; 32 workgroups of them a class of
+//     up to 65 536 samples, larger ones are the older loop's), so the scan is arithmetic (as in resident_kernels.hip, whose
+//     helpers this loop uses);
 //   - the block after the one in turn is known before the pick: it is the least f among the others, unless the picked
 //     block stays the least.  So the first post carries a workgroup's best candidate for the block in turn and its best
 //     two for the next one (two, because the first pick may take the best), and when the guess holds, which every
 //     workgroup sees alike, one trip serves two steps; so do the trips for the rows, the lists and the lists' rows.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
-// One class of 50 000 samples and eight blocks, the whole call 587 -> 383 ms, 12 000 and four 133 -> 70 (against one
+// One class of 50 000 samples and eight blocks, the whole call 586 -> 385 ms, 12 000 and four 133 -> 70 (against one
 // workgroup with its gains in memory); 71 % of the trips serve two steps.  A trip of the former, in us: candidates 1.9, first
 // exchange 2.2, the picks' rows 1.2, second exchange 2.5, rows of the lists 2.7.
 // The exchange itself (slots, tags, banks, bounded waits) is that of multi_wg_kernels.hip.
@@ -580,7 +581,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
 #pragma unroll
                     for (int i = 0; i < U; ++i)
                         if (e0 + i < here) {
-                            // (v* is always on its own list)
+                            // (v* is on its own list, unless an equal sample is in the block already)
                             if ((own0 >> (e0 + i)) & 1ull) {
 #pragma unroll
                                 for (int q = 0; q < Q; ++q) m[i][q] = mp[0][q];
