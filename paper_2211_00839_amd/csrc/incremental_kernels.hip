@@ -34,6 +34,10 @@ __device__ __forceinline__ double *inc_gains(const RcdClass &st) { return reinte
 __device__ __forceinline__ float *inc_dold(const RcdClass &st) { return st.part + 2 * (size_t)st.K * st.ld; }
 __device__ __forceinline__ int32_t *inc_dlist(const RcdClass &st) { return reinterpret_cast<int32_t *>(st.gain); }
 
+// the exchange area of the sliced step loop, behind the gains, the lists and the helpers' sums (6 of the part buffer's 32)
+__device__ __forceinline__ int32_t *inc_slices(const RcdClass &st) { return reinterpret_cast<int32_t *>(st.part + 8 * (size_t)st.K * st.ld); }
+static_assert((RCD_CMAX - 8) * RCD_TILE >= RCD_SLICE_INTS, "a slice is at least RCD_TILE samples");
+
 // One term of the update, in double: max(0, s - new) - max(0, s - old) with old < new, written as
 // -min(clamp(s - old, 0, 1), new - old) (s <= old: 0; old < s <= new: old - s; s > new: old - new; the upper
 // clamp never bites because the similarities lie in [0, 1]).  Every kernel of this route takes its terms from here,
@@ -79,6 +83,8 @@ rcd_k_inc_init(const RcdClass *__restrict__ classes)
     const RcdClass &st = classes[blockIdx.y];
     const int lane = threadIdx.x & 63;
     const int v = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < st.mw * RCD_SLICE_INTS; i += 256) inc_slices(st)[i] = 0;
     if (v >= st.n) return;
     const int ld = st.ld, K = st.K;
     const gcf32 row = (gcf32)st.M + (size_t)v * ld + lane * 4;
@@ -116,7 +122,7 @@ rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int f
     // segment per workgroup at the offset of its slice of the samples (ascending j across the segments).
     const int nseg = st.mw > 1 ? st.mw : 1;
     for (int sg = 0; sg < nseg; ++sg) {
-        const int nd = st.mw > 1 ? st.mwbuf[MW_PEND + k * RCD_MW_MAX + sg] : st.dcount[k];
+        const int nd = st.mw > 1 ? st.mwbuf[MW_PEND + k * RCD_SLICES_MAX + sg] : st.dcount[k];
         const size_t off = (size_t)k * ld + (st.mw > 1 ? (size_t)sg * st.mwseg : 0);
         const cci32 dl = (cci32)(inc_dlist(st) + off);
         const ccf32 dold = (ccf32)(inc_dold(st) + off);
@@ -244,7 +250,7 @@ rcd_k_inc_update_fused(const RcdClass *__restrict__ classes, RcdPlan *__restrict
     for (int s = 0; s < nmine; ++s) {
         const int k = st.need[s_base + s];
         for (int sg = 0; sg < nseg; ++sg) {
-            const int nd = shared ? st.mwbuf[MW_PEND + k * RCD_MW_MAX + sg] : st.dcount[k];
+            const int nd = shared ? st.mwbuf[MW_PEND + k * RCD_SLICES_MAX + sg] : st.dcount[k];
             const cci32 dl = (cci32)(inc_dlist(st) + (size_t)k * ld + (shared ? (size_t)sg * seg_len : 0));
             for (int e = tid; e < nd; e += 256) {
                 const int j = dl[e];

@@ -424,7 +424,7 @@ rcd_k_inc_steps_mw(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plans, 
             if (tid == 0) {
                 d.valid[js] = 0;
                 d.dcount[js] = nd;
-                mwbuf[MW_PEND + js * RCD_MW_MAX + w] = mine;
+                mwbuf[MW_PEND + js * RCD_SLICES_MAX + w] = mine;
             }
             sweeps += 1;
         } else if (nd > 0) {

@@ -23,6 +23,7 @@
 #include "multi_wg_kernels.hip"
 #include "resident_kernels.hip"
 #include "sliced_kernels.hip"
+#include "sliced_pairs_kernels.hip"
 
 static_assert(RCD_KMAX == RCD_MAX_K, "public and internal block limits differ");
 
@@ -464,17 +465,15 @@ struct SlicedInc {
 
 // Taken from 5121 samples in the largest class on, where a class no longer fits one workgroup's registers or does so with
 // too few left; single classes of more than four blocks from where rules::sliced_from() says.
-// Measured, the loops taken otherwise / this one, in ms: one class of 50 000, eight blocks 586 / 385 (the whole call), of
-// 20 000, one block 194 / 144, sixteen 263 / 160, of 12 000, four 133 / 70, of 8000, eight 73 / 46, of 6000, one 43 / 38, three 45 / 32,
-// sixteen 56 / 42, of 5000, eight 33.8 / 29.4, of 3500, seven 22.3 / 19.5; 20 classes of 8000, one block 74 / 65, four 89 / 66,
-// sixteen 147 / 114, ten of 6000, six 65 / 46, ten of 5121, sixteen 63 / 58; one of 6000 beside thirty of 500, four 49 / 36, sixteen
-// 55 / 53.  Below: 5000 and four blocks 20.0 / 28.0, 2000 and
-// twelve 8.0 / 12.2, ten classes of 5000 and eight 42.9 / 43.6.
-// (Mixtures and single clouds of 4 to 512 features gain alike.  A class of a few points repeated loses, since no coverage rises once
-// each has been taken, there is no list to share and a pick without gain leaves the block in turn the least: 50 points, 6000 samples and
-// eight blocks 33.7 / 36.7, 3500 and sixteen 16.5 / 25.3.  Nothing on the host can tell.)
-// Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048 (20 000 samples
-// 118 / 131, 12 000 70 / 77; of 512, 12 000 samples 73); where there are not even those, the loops in memory serve.
+// Measured, the loops taken otherwise / this one with two picks to a trip / with up to eight, in ms: one class of 50 000, eight blocks
+// 586 / 387 / 251 (the whole call), of 20 000, one block 194 / 140 / 86, sixteen 263 / 152 / 121, of 12 000, four 133 / 76 / 55, of 6000, one
+// 43 / 38 / 28, three 45 / 36 / 28, sixteen 56 / 40 / 36, of 3500, seven 22.3 / 19.3 / 18.5; 20 classes of 8000, one block 74 / 64 /
+// 58, four 89 / 71 / 60, sixteen 147 / 110 / 95, ten of 6000, six 65 / 45 / 39, ten of 5121, sixteen 63 / 56 / 40; one of 6000 beside
+// thirty of 500, four 49 / 40 / 33, sixteen 55 / 53 / 36.
+// (Mixtures and single clouds of 4 to 512 features gain alike.  A class of a few points repeated gains least: no coverage rises once each
+// has been taken, and there is no list to share.)
+// Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048; where there are not even
+// those, the loops in memory serve.  Slices of more than 1024 with more than eight blocks keep two picks to a trip (choose()).
 SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
 {
     SlicedInc none, out;
@@ -484,23 +483,28 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     for (const RcdClass &c : cls) max_n = std::max(max_n, c.n);
     const int min_n = env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, cls[0].K), 0, 0x7fffffff);
     if (min_n == 0 || max_n < min_n) return none;
-    const int w_max = std::min(env_int("RCD_MW_MAX_WGS", RCD_MW_MAX, 1, RCD_MW_MAX), cus / ncls);
-    if (w_max < 2) return none;
-    const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256;
+    if (cus / ncls < 2 || max_n > 1024 * RCD_SLICES_MAX) return none;
+    const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256, K = cls[0].K;
     for (const int least : {given ? given : 1024, given ? given : 2048}) {
+        // (large slices with many blocks are the loop's whose exchange area holds fewer workgroups)
+        const int most = least > 1024 && K > 8 ? RCD_MW_MAX : RCD_SLICES_MAX;
+        const int w_max = std::min(env_int("RCD_MW_MAX_WGS", most, 1, most), cus / ncls);
+        if (w_max < 2) return none;
         out = none;
-        int largest = 0;
+        int largest = 0, widest = 0;
         for (int i = 0; i < ncls; ++i) {
             const int ld = cls[i].ld;
             int W = std::min(w_max, (ld + least - 1) / least);
             const int seg = ((ld + W - 1) / W + 255) / 256 * 256;
             W = (ld + seg - 1) / seg;               // no empty slice
             largest = std::max(largest, seg);
+            widest = std::max(widest, W);
             out.seg.push_back(seg);
             for (int w = 0; w < W; ++w) out.map.push_back(RcdWg{i, w, W, 0});
         }
         if ((int)out.map.size() > std::min(cus, RCD_MAX_SWEEP_WGS)) continue;
-        out.choice = sliced::choose(largest, cls[0].K);
+        if (largest > 1024 && K > 8 && widest > RCD_MW_MAX) continue;
+        out.choice = sliced::choose(largest, K);
         if (out.choice.inc) return out;
     }
     return none;
@@ -745,6 +749,17 @@ struct Lane {
             // bandwidth, and lists four times as long are better applied by the class's own workgroups
             // (20 classes of 50 000: 1.92 -> 1.86 s; one class alone: 774 -> 875 ms, so not there)
             if (ncls >= 4) inc_small_bytes = env_int("RCD_INC_SMALL_KB", 2048, 1, 1 << 20) * 1024;
+            // Where up to eight picks share a trip an update launch costs more trips.  One class: 512 KB (128 rows of a class in
+            // slices of 1024).  Several: an update launch serves all of them at once, so the smaller ones leave more to it, unless
+            // the class has few blocks and nothing to do until then (128 / 256 / 512 / 1024 / 2048 KB: ten of 5121, sixteen blocks 40.6 /
+            // 43.1 / 45.9 / 51.4 / 59; one of 6000 beside thirty of 500 36.0 / 40.1 / 43.2 / 49.5 / 54.5; sixteen of 16 000, twelve blocks
+            // 233 / 226 / 222 / 223 / -; ten of 6000, one block - / 48.2 / 47.7 / 43.3 / 37.4, three - / 39.1 / 39.7 / 39.1 / 39.5).
+            // Slices of 2048: twenty of 15 000, five blocks, 512 / 1024 / 2048 KB 172 / 174 / 182; forty of 12 000, eight 218 / 215 / 216.
+            if (slc.inc && slc.several) {
+                const int largest = *std::max_element(slices.seg.begin(), slices.seg.end());
+                const int kb = ncls == 1 ? 512 : largest > 1024 ? 1024 : first.K <= 3 ? 2048 : std::min(512, std::max(128, max_n / 40));
+                inc_small_bytes = env_int("RCD_INC_SMALL_KB", kb, 1, 1 << 20) * 1024;
+            }
             HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));
             HIP_TRY(hipMemcpyAsync(g->classes_dev, g->host.data(), sizeof(RcdClass) * ncls, hipMemcpyHostToDevice, stream));
         }

@@ -1,22 +1,27 @@
 // Step loop of the incremental-gain route for classes that are too large for one workgroup's registers (gfx950): W
-// workgroups share a class, each with its slice of the samples, whose gains it holds in registers, and up to two picks
+// workgroups share a class, each with its slice of the samples, whose gains it holds in registers, and up to eight picks
 // share the trips between the workgroups.
 //
 // What bounds a step of a shared class is waiting: the workgroups tell each other their best candidates, fetch row v* of
 // S, tell each other which coverage values rose, fetch the rows of that list.  rcd_k_inc_steps_mw walks this chain once per
 // step, with the gains in L2.  Here
-//   - the slice's gains sit in registers (512 threads hold up to 2048 samples x 16 blocks; 32 workgroups of them a class of
-//     up to 65 536 samples, larger ones are the older loop's), so the scan is arithmetic (as in resident_kernels.hip, whose
+//   - the slice's gains sit in registers (512 threads hold up to 2048 samples x 8 blocks or 1024 x 16; up to 64 workgroups to a
+//     class of up to 65 536 samples, larger ones are the older loop's), so the scan is arithmetic (as in resident_kernels.hip, whose
 //     helpers this loop uses);
-//   - the block after the one in turn is known before the pick: it is the least f among the others, unless the picked
-//     block stays the least.  So the first post carries a workgroup's best candidate for the block in turn and its best
-//     two for the next one (two, because the first pick may take the best), and when the guess holds, which every
-//     workgroup sees alike, one trip serves two steps; so do the trips for the rows, the lists and the lists' rows.
+//   - a trip makes up to eight picks, all on the gains as they are at its start.  f never falls, so the u-th pick goes to one of the
+//     u least blocks: every workgroup posts its best candidates of the eight least blocks (two of each, four or eight where fewer
+//     blocks are left), and Algorithm 1 runs on the class's best of them, alike in every workgroup, until a list ends;
+//   - a block may be picked again in the same trip.  A gain only falls, so the best of the old gains is the best of the
+//     new ones if its own has not fallen, and it has not if no coverage that the block's earlier picks of the trip raise is below
+//     its similarity.  That is looked up once the lists are known; the first guess that does not hold and the picks behind it
+//     are dropped, and nothing has been written for them.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
-// One class of 50 000 samples and eight blocks, the whole call 586 -> 385 ms, 12 000 and four 133 -> 70 (against one
-// workgroup with its gains in memory); 71 % of the trips serve two steps.  A trip of the former, in us: candidates 1.9, first
-// exchange 2.2, the picks' rows 1.2, second exchange 2.5, rows of the lists 2.7.
-// The exchange itself (slots, tags, banks, bounded waits) is that of multi_wg_kernels.hip.
+// On mixtures a trip makes 7.8 steps.  With two picks to a trip (sliced_pairs_kernels.hip, for all sizes before) -> now, whole calls in
+// ms: 50 000 samples and eight blocks 387 -> 251, sixteen 480 -> 367, 40 000 and two 305 -> 190, 20 000 and eight 128 -> 92, one
+// 140 -> 86, 12 000 and four 76 -> 55, 6000 and three 36 -> 28.  A trip at 50 000 takes 21 us: candidates 2.4, first exchange 4.3, the
+// picks 2.9, their rows and lists 2.8, second exchange 3.3, the lists' rows 4.5, the rest 1; an instruction of a wave
+// takes some seven cycles here, so the picks' and the exchanges' arithmetic counts as much as the trips through memory.
+// The tags, banks and bounded waits of the exchanges are those of multi_wg_kernels.hip; a post has sixteen pieces.
 // Included by rcd_lib.hip after resident_kernels.hip.
 #include <hip/hip_runtime.h>
 #include "rcd_state.h"
@@ -31,9 +36,10 @@ using resident::f32x2;
 using resident::lds_barrier;
 using resident::off;
 
-// 512 threads, Q pieces of two samples each, at most KM blocks, ROWS rows of the lists in flight.
-template <int Q, int KM, int ROWS_> struct SliceShape : Shape<512, Q, KM> {
-    static constexpr int ROWS = ROWS_;
+// 512 threads, Q pieces of two samples each, at most KM blocks, twice ROWS rows of the lists in flight, at most PICKS picks to a
+// trip.  (Q = 2: eight rows and two sets of them would spill the picks' rows, which makes a wait of each spill.)
+template <int Q, int KM, int ROWS_, int PICKS_> struct SliceShape : Shape<512, Q, KM> {
+    static constexpr int ROWS = ROWS_, PICKS = PICKS_;
 };
 
 // Where a wave is: it owns the class's samples [first, first + 128 Q), pieces from nq on lie outside the slice.  A row is
@@ -58,18 +64,129 @@ template <typename S> struct SlicePlace {
     }
 };
 
+constexpr int BM = 8;              // most picks of a trip
+constexpr int POST = 16;           // 16-byte pieces of a workgroup's post
+constexpr int POST_INTS = 4 * POST;
+constexpr int ENTRIES = 1024;      // list entries that are applied in one trip, at most
+static_assert(2 * POST_INTS == RCD_SLICE_INTS && ENTRIES >= INC_SMALL && RCD_SLICES_MAX <= 64, "exchange area, a lane per workgroup");
+// An entry on its way carries its pick and its place in the pick's segment above the sample's number.
+constexpr int J_BITS = 17;
+static_assert(RCD_SLICES_MAX * 2048 <= 1 << J_BITS, "samples of the largest class that is cut into slices");
+
+// High words of keys: a candidate's is above KEY_LIVE (of -1e299: 0x01FCE302); KEY_UNKNOWN where a list of the best ends.
+constexpr unsigned KEY_LIVE = 0x02000000u, KEY_UNKNOWN = 0xFFFFFFFFu;
+
 template <typename S> struct SliceShared {
-    Slot slots[3][4 * S::NW];      // per 16 lanes: the best for the block in turn; the best and the second for the next
-    Slot won[3];                   // the class's best of the block in turn, its best two of the next
-    Entry stage[2 * S::NW][MW_INLINE];
-    int count[2 * S::NW];          // entries of wave w's part of pick u's list
-    Entry mine[MW_INLINE];         // what travels in my post
-    Entry list[2 * INC_SMALL];     // the lists that are applied here, end to end
-    int len[2][RCD_MW_MAX], pre[2][RCD_MW_MAX];   // what is applied here of workgroup i's segments, and where it goes
-    int fetch[RCD_MW_MAX];         // workgroup i's segments did not travel in its post
-    int nd[2];
-    int ok[2], any_long;
+    Slot slots[S::KM][2][4 * S::NW];         // per block and 16 lanes: the best candidate and the second
+    Slot list[BM][BM];                       // per block of this trip: the class's best, in order
+    int listed[BM];                          // how many of them are known
+    Entry stage[BM * S::NW][POST - 1];
+    int count[BM * S::NW];                   // entries of wave w's part of pick u's list
+    Entry mine[POST];                        // what travels in my post
+    Entry entries[ENTRIES];                  // the lists that are applied here, end to end
+    int len[BM][RCD_SLICES_MAX], at[BM][RCD_SLICES_MAX];     // of workgroup i's segments: the lengths, and where they go
+    int fetch[RCD_SLICES_MAX];                   // workgroup i's segments did not travel in its post
+    int nd[BM];                              // the lists' lengths
+    int kept, sure, any_long;                // bit u: list u is applied here; picks that fit into this trip
+    int ok[BM];
 };
+
+// Every row of 16 lanes puts its best candidate and its second for block k into the slots.  They stay from trip to trip: a wave
+// writes a block's anew when one of the two was taken or has lost gain (mine: the blocks for which this lane holds one of the two).
+// Decided by the high words of the keys; a tie there takes the long way.
+template <typename S>
+__device__ __forceinline__ void row_candidates(const double (&G)[S::KM][S::P], int k, const SlicePlace<S> &pl, Slot (*slots)[4 * S::NW],
+                                               unsigned &mine)
+{
+    double t[S::P];
+    resident::at_index<0, S::KM>(k, [&](auto kc) {
+#pragma unroll
+        for (int i = 0; i < S::P; ++i) t[i] = G[decltype(kc)::value][i];
+    });
+    mine &= ~(1u << k);
+#pragma unroll
+    for (int round = 0; round < 2; ++round) {
+        double s[S::P];
+#pragma unroll
+        for (int i = 0; i < S::P; ++i) s[i] = t[i];
+#pragma unroll
+        for (int w = 1; w < S::P; w *= 2)
+#pragma unroll
+            for (int i = 0; i + w < S::P; i += 2 * w) s[i] = resident::max_f64(s[i], s[i + w]);
+        // the lowest of the lane's samples that has it: pieces ascending, then the lane's two
+        int at = 0;
+#pragma unroll
+        for (int i = S::P - 1; i >= 1; --i) at = t[i] == s[0] ? i : at;
+        at = t[0] == s[0] ? 0 : at;
+        unsigned hi, lo;
+        resident::key_words(s[0], hi, lo);
+        const int v = (int)pl.v0 + (at >> 1) * 128 + (at & 1);
+        bool win = hi == resident::row_max_u32(hi);
+        if (__popcll(__ballot(win)) != 4) {
+            const unsigned low = resident::row_max_u32(win ? lo : 0u);
+            win = win & (lo == low);
+            const unsigned first = resident::row_max_u32(win ? ~(unsigned)v : 0u);
+            win = win & (~(unsigned)v == first);
+        }
+        if (win) {
+            slots[round][pl.wave * 4 + (pl.lane >> 4)] = Slot{hi, lo, v, 0};
+            mine |= 1u << k;
+        }
+#pragma unroll
+        for (int i = 0; i < S::P; ++i) t[i] = (win & (at == i)) ? INC_TAKEN : t[i];
+    }
+}
+
+// ob[i]: the block that is i-th least in f of those with room (lowest index on ties), -1 where there are fewer.
+template <int N> __device__ __forceinline__ void order_one_by_one(double f, int room, int lane, int (&ob)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        ob[i] = resident::choose_block(f, room);
+        if ((lane & 15) == ob[i]) room = 0;
+    }
+}
+// The same by counting, for every block, the blocks before it: no chain from one to the next.  Equal f take the long way.
+// Blocks sit in the lanes 0 .. KM - 1 (those past K have no room).
+template <int KM, int N> __device__ __forceinline__ void order_blocks(double f, int room, int lane, int (&ob)[N])
+{
+    using resident::dpp;
+    unsigned hi, lo;
+    resident::key_words(-f, hi, lo);
+    hi = room <= 0 ? 0u : hi;
+    lo = room <= 0 ? 0u : lo;
+    const unsigned long long me = ((unsigned long long)hi << 32) | lo;
+    int before = 0;
+    unsigned long long equal = 0ull;
+    auto against = [&](unsigned h, unsigned l) __attribute__((always_inline)) {
+        const unsigned long long it = ((unsigned long long)h << 32) | l;
+        before += it > me ? 1 : 0;
+        equal |= __ballot(it == me);
+    };
+    auto quad = [&](unsigned h, unsigned l, bool self) __attribute__((always_inline)) {
+        if (!self) against(h, l);
+        against((unsigned)dpp<0xB1>((int)h), (unsigned)dpp<0xB1>((int)l));        // the lanes 1, 2, 3 away (exclusive or)
+        against((unsigned)dpp<0x4E>((int)h), (unsigned)dpp<0x4E>((int)l));
+        against((unsigned)dpp<0x1B>((int)h), (unsigned)dpp<0x1B>((int)l));
+    };
+    quad(hi, lo, true);
+    if constexpr (KM > 4) quad((unsigned)dpp<0x141>((int)hi), (unsigned)dpp<0x141>((int)lo), false);     // 7 away, 6, 5, 4
+    if constexpr (KM > 8) {
+        const unsigned h = (unsigned)dpp<0x140>((int)hi), l = (unsigned)dpp<0x140>((int)lo);             // 15 away, 14, 13, 12
+        quad(h, l, false);
+        quad((unsigned)dpp<0x141>((int)h), (unsigned)dpp<0x141>((int)l), false);                         // 8 away, 9, 10, 11
+    }
+    const bool open = lane < KM && room > 0;
+    if ((equal & __ballot(open)) != 0ull) {
+        order_one_by_one(f, room, lane, ob);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const unsigned long long it = __ballot(open && before == i);
+        ob[i] = it ? (int)__builtin_ctzll(it) : -1;
+    }
+}
 
 // A lane per candidate: the lane that holds the best (largest key, lowest sample on ties).
 __device__ __forceinline__ int best_lane(unsigned hi, unsigned lo, int v)
@@ -84,68 +201,31 @@ __device__ __forceinline__ int best_lane(unsigned hi, unsigned lo, int v)
     return (int)__builtin_ctzll(who);
 }
 
-// The best of a lane's samples: its key, and which of them it is (the first that has it).
-template <typename S> struct LaneBest {
-    unsigned hi, lo;
-    int at;
-    __device__ __forceinline__ void of(const double (&t)[S::P])
-    {
-        double s[S::P];
-#pragma unroll
-        for (int i = 0; i < S::P; ++i) s[i] = t[i];
-#pragma unroll
-        for (int w = 1; w < S::P; w *= 2)
-#pragma unroll
-            for (int i = 0; i + w < S::P; i += 2 * w) s[i] = resident::max_f64(s[i], s[i + w]);
-        at = 0;
-#pragma unroll
-        for (int i = S::P - 1; i >= 1; --i) at = t[i] == s[0] ? i : at;
-        at = t[0] == s[0] ? 0 : at;
-        resident::key_words(s[0], hi, lo);
-    }
-    __device__ __forceinline__ int sample(const SlicePlace<S> &pl) const { return (int)pl.v0 + (at >> 1) * 128 + (at & 1); }
-    // of the lanes of a row that tie in the high word, the one with the best candidate
-    __device__ __forceinline__ bool settle(bool win, const SlicePlace<S> &pl) const
-    {
-        const unsigned low = resident::row_max_u32(win ? lo : 0u);
-        win = win && lo == low;
-        const unsigned v = ~(unsigned)sample(pl), first = resident::row_max_u32(win ? v : 0u);      // (by all lanes)
-        return win && v == first;
-    }
-};
-
-// Every row of 16 lanes puts its best candidate of the block in turn (t0) into slots[0] and, if there is a next block, its
-// best two of that one (t1) into slots[1] and slots[2].  One chain without branches decides all three by the high words of
-// the keys; a tie there takes the long way.
-template <typename S>
-__device__ __forceinline__ void row_candidates(const double (&t0)[S::P], const double (&t1)[S::P], bool two, const SlicePlace<S> &pl,
-                                               Slot (*slots)[4 * S::NW])
+// f(integral_constant u) for every pick of a trip
+template <typename F> __device__ __forceinline__ void each_pick(F &&f)
 {
-    LaneBest<S> a, b, c;
-    double t2[S::P];
-    a.of(t0);
-    bool wa = a.hi == resident::row_max_u32(a.hi), wb = false, wc = false;
-    if (two) {
-        b.of(t1);
-        wb = b.hi == resident::row_max_u32(b.hi);
-#pragma unroll
-        for (int i = 0; i < S::P; ++i) t2[i] = wb && b.at == i ? INC_TAKEN : t1[i];
-        c.of(t2);
-        wc = c.hi == resident::row_max_u32(c.hi);
-    }
-    // (in a row that ties, every lane of the tie has given its best away: the second is found again)
-    if (__popcll(__ballot(wa)) != 4) wa = a.settle(wa, pl);
-    if (two && (__popcll(__ballot(wb)) != 4 || __popcll(__ballot(wc)) != 4)) {
-        wb = b.settle(wb, pl);
-#pragma unroll
-        for (int i = 0; i < S::P; ++i) t2[i] = wb && b.at == i ? INC_TAKEN : t1[i];
-        c.of(t2);
-        wc = c.settle(c.hi == resident::row_max_u32(c.hi), pl);
-    }
-    const int row = pl.wave * 4 + (pl.lane >> 4);
-    if (wa) slots[0][row] = Slot{a.hi, a.lo, a.sample(pl), 0};
-    if (wb) slots[1][row] = Slot{b.hi, b.lo, b.sample(pl), 0};
-    if (wc) slots[2][row] = Slot{c.hi, c.lo, c.sample(pl), 0};
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+    f(std::integral_constant<int, 4>{});
+    f(std::integral_constant<int, 5>{});
+    f(std::integral_constant<int, 6>{});
+    f(std::integral_constant<int, 7>{});
+}
+
+__device__ __forceinline__ float max2(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+__device__ __forceinline__ double lane_double(double x, int l)
+{
+    const long long b = __double_as_longlong(x);
+    return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(b >> 32), l) << 32) |
+                                (unsigned)__builtin_amdgcn_readlane((int)b, l));
 }
 
 // inclusive sum over the lanes
@@ -171,45 +251,28 @@ __device__ __forceinline__ void dev_load4x2(const int32_t *p, i32x4 &a, i32x4 &b
                  : "memory");
 }
 
+__device__ __forceinline__ int32_t *slot_of(const MwExchange &x, int w)
+{
+    return x.banks + RCD_SLICE_INTS * w + POST_INTS * (x.epoch & 1u);
+}
 // The pieces first, first + 1, ... of this workgroup's post, one per lane from lane 0 on.  One wave.
 __device__ __forceinline__ void put(const MwExchange &x, int lane, int first, int pieces, int a, int b, int c)
 {
-    int32_t *slot = x.banks + (x.epoch & 1u) * (MW_SLOT_INTS * RCD_MW_MAX) + MW_SLOT_INTS * x.w;
     const unsigned piece = (unsigned)(first + lane);
     if (lane < pieces)
-        dev_store4i(slot + 4 * piece, a, b, c, (int)mw_tag(x.epoch + 0x01000000u * piece, (unsigned)a, (unsigned)b, (unsigned)c));
+        dev_store4i(slot_of(x, x.w) + 4 * piece, a, b, c, (int)mw_tag(x.epoch + 0x01000000u * piece, (unsigned)a, (unsigned)b, (unsigned)c));
 }
 __device__ __forceinline__ bool fits(const MwExchange &x, int piece, const i32x4 &s)
 {
     return (unsigned)s.w == mw_tag(x.epoch + 0x01000000u * (unsigned)piece, (unsigned)s.x, (unsigned)s.y, (unsigned)s.z);
 }
 
-// Pieces of everybody's posts, a workgroup per lane: piece 0; pieces 1 and 2; or piece 0 = {length, length} and, where the
-// lengths' sum is at most MW_INLINE, as many more.  One wave.  False when the bounded wait has run out or the flag is up.
-enum { GET_FIRST = 0, GET_NEXT_TWO = 1, GET_LIST = 2 };
-template <int KIND> __device__ __forceinline__ bool get(const MwExchange &x, int lane, i32x4 (&s)[4])
+// Looks at posts (`look` asks for what it needs and says whether all of it is there) until they have come.  One wave.  False when
+// the bounded wait has run out or the flag is up.
+template <typename F> __device__ __forceinline__ bool wait_for(const MwExchange &x, F &&look)
 {
-    const int32_t *slot = x.banks + (x.epoch & 1u) * (MW_SLOT_INTS * RCD_MW_MAX) + MW_SLOT_INTS * lane;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) s[g] = (i32x4){0, 0, 0, 0};
     for (int it = 1;; ++it) {
-        bool good = true;
-        if (lane < x.W) {
-            if constexpr (KIND == GET_FIRST) {
-                s[0] = dev_load4(slot);
-                good = fits(x, 0, s[0]);
-            } else if constexpr (KIND == GET_NEXT_TWO) {
-                dev_load4x2(slot + 4, s[0], s[1]);
-                good = fits(x, 1, s[0]) && fits(x, 2, s[1]);
-            } else {
-                dev_load4x4(slot, s[0], s[1], s[2], s[3]);
-                good = fits(x, 0, s[0]);
-                const int more = s[0].x + s[0].y <= MW_INLINE ? s[0].x + s[0].y : 0;
-#pragma unroll
-                for (int g = 1; g <= MW_INLINE; ++g) good = good && (g > more || fits(x, g, s[g]));
-            }
-        }
-        if (__all(good)) return true;
+        if (__all(look())) return true;
         // (now and then: the flag is a trip of its own between two looks at the posts)
         if ((it & 15) == 0 && __hip_atomic_load(x.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2) return false;
         if ((it & 15) <= 1) {
@@ -219,6 +282,51 @@ template <int KIND> __device__ __forceinline__ bool get(const MwExchange &x, int
             }
         }
     }
+}
+
+// N candidates of a block, this workgroup's best in order (lane g of `p` holds the g-th), to everybody, as pieces from `first` on;
+// then the class's best, in order and as far as they are known, into `list`: at most `need`.  Returns how many, -1 when the wait
+// has run out.  One wave.
+template <int N>
+__device__ __forceinline__ int class_best(const MwExchange &x, int lane, int first, const Slot &p, int need, Slot *list)
+{
+    static_assert(N == 2 || N == 4 || N == 8, "loads");
+    i32x4 s[N];                                  // lane w: workgroup w's
+    if (x.W > 1) {
+        put(x, lane, first, N, (int)p.hi, (int)p.lo, p.v);
+        const int32_t *src = slot_of(x, lane) + 4 * first;
+        const bool ok = wait_for(x, [&]() {
+            bool good = true;
+            if (lane < x.W) {
+                if constexpr (N == 2) dev_load4x2(src, s[0], s[1]);
+                else dev_load4x4(src, s[0], s[1], s[2], s[3]);
+                if constexpr (N == 8) dev_load4x4(src + 16, s[4], s[5], s[6], s[7]);
+#pragma unroll
+                for (int g = 0; g < N; ++g) good = good && fits(x, first + g, s[g]);
+            }
+            return good;
+        });
+        if (!ok) return -1;
+    } else {
+#pragma unroll
+        for (int g = 0; g < N; ++g)
+            s[g] = (i32x4){__builtin_amdgcn_readlane((int)p.hi, g), __builtin_amdgcn_readlane((int)p.lo, g), __builtin_amdgcn_readlane(p.v, g), 0};
+    }
+#pragma unroll
+    for (int g = 0; g < N; ++g) s[g].x = lane < x.W ? s[g].x : 0;       // (the key 0 is below every number's)
+    int n = 0;
+    for (; n < need; ++n) {
+        const int src = best_lane((unsigned)s[0].x, (unsigned)s[0].y, s[0].z);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane(s[0].x, src);
+        if (hi - KEY_LIVE >= KEY_UNKNOWN - KEY_LIVE) break;
+        if (lane == src) {
+            list[n] = Slot{hi, (unsigned)s[0].y, s[0].z, 0};
+#pragma unroll
+            for (int g = 0; g + 1 < N; ++g) s[g] = s[g + 1];
+            s[N - 1].x = (int)KEY_UNKNOWN;       // behind a workgroup's last nothing is known
+        }
+    }
+    return n;
 }
 
 } // namespace sliced
@@ -233,7 +341,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
 {
     using namespace sliced;
     constexpr int NW = S::NW, Q = S::Q, P = S::P;
-    static_assert(NW == 8, "counts of two picks in 16 lanes, candidates of 32 rows in a wave");
+    static_assert(NW == BM && BM == 8, "a wave per block, a lane per pick and wave");
     __shared__ __attribute__((aligned(16))) SliceShared<S> sh;
     const RcdWg wg = wgmap[blockIdx.x];
     RcdClass &st = classes[__builtin_amdgcn_readfirstlane(wg.cls)];
@@ -262,7 +370,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     double G[S::KM][P];
     resident::load_gains<S>(G, inc_gains(st), K, n, ld, pl);
     MwExchange x;
-    x.banks = mwbuf + MW_SLOT;
+    x.banks = mw_uniform(inc_slices(st));
     x.abort_flag = &plans[0].bad;
     x.W = W;
     x.w = w;
@@ -275,8 +383,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         __syncthreads();
         if (pl.wave == 0) {
             put(x, lane, 0, 1, 0, 0, 0);
-            i32x4 s[4];
-            const bool ok = get<GET_FIRST>(x, lane, s);
+            const bool ok = wait_for(x, [&]() { return lane >= W || fits(x, 0, dev_load4(slot_of(x, lane))); });
             if (lane == 0) sh.ok[0] = ok;
         }
         lds_barrier();
@@ -285,356 +392,561 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     auto write_held = [&]() {
         const RcdClass *c = rarely();
         if (w == 0) resident::write_outputs<S>(r, c->assign_out, c->order_out, c->out_index, pl);
+        r.held = 0;
     };
+    int ob[BM];                                  // the least blocks, in order
+    order_blocks<S::KM>(r.f, r.room, lane, ob);
+    unsigned calm = 0;                           // bit k: block k's last list was applied here, its next pick's may be guessed to be
+    unsigned dirty = 0xFFFFu, mine = 0;          // bit k: this wave's entries of block k in the slots are not current; see row_candidates()
     while (alive) {
-        const int j0 = resident::block_in_turn(r);
-        if (j0 < 0 || !((r.valid >> j0) & 1u)) break;
-        // the block that is next if j0's pick does not leave it the least again
-        int j1 = resident::choose_block(r.f, (lane & 15) == j0 ? 0 : r.room);
-        if (j1 >= 0 && (!((r.valid >> j1) & 1u) || r.t + 1 >= r.total || r.t + 1 - r.t0 >= r.max_steps)) j1 = -1;
-
+        if (r.t >= r.total || ob[0] < 0) { r.done = 1; break; }
+        if (r.t - r.t0 >= r.max_steps) { r.stop = 1; break; }
+        if (!((r.valid >> ob[0]) & 1u)) break;
+        // ---- the blocks: the u-th pick goes to one of the u least (f never falls)
+        const int most = min(min(r.total - r.t, r.max_steps - (r.t - r.t0)), S::PICKS);
+        int nb = 0, pos = -1, order = -1;        // how many; lane k: block k's place among them; lane i: the i-th of them
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+            if (nb == i && i < most && ob[i] >= 0 && ((r.valid >> (ob[i] & 15)) & 1u)) {
+                nb = i + 1;
+                pos = (lane & 15) == ob[i] ? i : pos;
+                order = lane == i ? ob[i] : order;
+            }
         // ---- candidates of this slice
-        {
-            double t0[P], t1[P];
-            resident::at_index<0, S::KM>(j0, [&](auto kc) {
 #pragma unroll
-                for (int i = 0; i < P; ++i) t0[i] = G[decltype(kc)::value][i];
-            });
-            if (j1 >= 0)
-                resident::at_index<0, S::KM>(j1, [&](auto kc) {
-#pragma unroll
-                    for (int i = 0; i < P; ++i) t1[i] = G[decltype(kc)::value][i];
-                });
-            row_candidates<S>(t0, t1, j1 >= 0, pl, sh.slots);
-        }
-        // the coverage the picks' rows will be held against, on its way during the exchange
-        f32x2 c[2][Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            c[0][q] = pl.at((gcf32)(cur_all + (size_t)j0 * ld), q);
-            c[1][q] = pl.at((gcf32)(cur_all + (size_t)max(j1, 0) * ld), q);
-        }
+        for (int i = 0; i < BM; ++i)
+            if (i < nb && ((dirty >> ob[i]) & 1u)) {
+                row_candidates<S>(G, ob[i], pl, sh.slots[ob[i]], mine);
+                dirty &= ~(1u << ob[i]);
+            }
         lds_barrier();
         x.epoch += 1;
-        if (pl.wave == 0) {
-            const Slot a = sh.slots[0][lane & 31];
-            const int mine = best_lane(lane < 32 ? a.hi : 0u, a.lo, a.v);
-            i32x4 s[4];
-            bool ok = true;
-            const int hi = __builtin_amdgcn_readlane((int)a.hi, mine), lo = __builtin_amdgcn_readlane((int)a.lo, mine);
-            const int v = __builtin_amdgcn_readlane(a.v, mine);
-            if (W > 1) {
-                put(x, lane, 0, 1, hi, lo, v);
-                ok = get<GET_FIRST>(x, lane, s);
-            } else {
-                s[0] = lane == 0 ? (i32x4){hi, lo, v, 0} : (i32x4){0, 0, 0, 0};
+        if (pl.wave < nb) {
+            // a wave per block: this workgroup's best, and with everybody's the class's
+            const int k = __builtin_amdgcn_readlane(order, pl.wave);
+            const int share = nb > 4 ? 2 : nb > 2 ? 4 : 8;
+            Slot a = sh.slots[k][lane >> 5][lane & 31], p = Slot{0u, 0u, -1, 0};
+            bool known = true;
+            for (int g = 0; g < share; ++g) {
+                const int src = best_lane(a.hi, a.lo, a.v);
+                const unsigned hi = known ? (unsigned)__builtin_amdgcn_readlane((int)a.hi, src) : KEY_UNKNOWN;
+                const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)a.lo, src);
+                const int v = __builtin_amdgcn_readlane(a.v, src);
+                if (lane == g) p = Slot{hi, lo, v, 0};
+                if (lane == src) a.hi = 0u;
+                known = known && src < 32;       // (a row's second is gone: its third is not known)
             }
-            // (lanes without a workgroup hold the key 0, below every number's)
-            const int src = best_lane((unsigned)s[0].x, (unsigned)s[0].y, s[0].z);
-            if (lane == src) sh.won[0] = Slot{(unsigned)s[0].x, (unsigned)s[0].y, s[0].z, 0};
-            if (lane == 0) sh.ok[0] = ok;
-        } else if (pl.wave == 1) {
-            bool ok = true;
-            if (j1 >= 0) {
-                const Slot b = sh.slots[1 + (lane >> 5)][lane & 31];
-                const int one = best_lane(b.hi, b.lo, b.v);
-                const int two = best_lane(lane == one ? 0u : b.hi, b.lo, b.v);
-                const i32x4 p1 = {__builtin_amdgcn_readlane((int)b.hi, one), __builtin_amdgcn_readlane((int)b.lo, one),
-                                  __builtin_amdgcn_readlane(b.v, one), 0};
-                const i32x4 p2 = {__builtin_amdgcn_readlane((int)b.hi, two), __builtin_amdgcn_readlane((int)b.lo, two),
-                                  __builtin_amdgcn_readlane(b.v, two), 0};
-                i32x4 s[4];
-                if (W > 1) {
-                    const i32x4 p = lane == 0 ? p1 : p2;
-                    put(x, lane, 1, 2, p.x, p.y, p.z);
-                    ok = get<GET_NEXT_TWO>(x, lane, s);
-                } else {
-                    s[0] = lane == 0 ? p1 : (i32x4){0, 0, 0, 0};
-                    s[1] = lane == 0 ? p2 : (i32x4){0, 0, 0, 0};
-                }
-                const int src = best_lane((unsigned)s[0].x, (unsigned)s[0].y, s[0].z);
-                if (lane == src) {
-                    sh.won[1] = Slot{(unsigned)s[0].x, (unsigned)s[0].y, s[0].z, 0};
-                    s[0] = s[1];
-                }
-                const int src2 = best_lane((unsigned)s[0].x, (unsigned)s[0].y, s[0].z);
-                if (lane == src2) sh.won[2] = Slot{(unsigned)s[0].x, (unsigned)s[0].y, s[0].z, 0};
+            const int need = nb == 1 ? 8 : nb == 2 ? 6 : nb <= 4 ? 4 : 3;
+            int got;
+            if (share == 2) got = class_best<2>(x, lane, pl.wave * 2, p, need, sh.list[pl.wave]);
+            else if (share == 4) got = class_best<4>(x, lane, pl.wave * 4, p, need, sh.list[pl.wave]);
+            else got = class_best<8>(x, lane, pl.wave * 8, p, need, sh.list[pl.wave]);
+            if (lane == 0) {
+                sh.listed[pl.wave] = got;
+                sh.ok[pl.wave] = got >= 0;
             }
-            if (lane == 0) sh.ok[1] = ok;
         }
         lds_barrier();
-        if ((sh.ok[0] & sh.ok[1]) == 0) { alive = false; break; }
+        if (__ballot(lane < nb && sh.ok[lane & (BM - 1)] == 0) != 0ull) { alive = false; break; }
 
-        // ---- the picks (every wave of every workgroup alike)
-        int pj[2] = {j0, j1}, pv[2] = {0, -1};
-        f32x2 mp[2][Q];                          // their rows
-        int B = 1;
-        {
-            const Slot a = sh.won[0], first = sh.won[1], second = sh.won[2];
-            const Slot b = first.v == a.v ? second : first;
-            const double best0 = inc_value(((unsigned long long)a.hi << 32) | a.lo);
-            pv[0] = __builtin_amdgcn_readfirstlane(a.v);
-            // no candidate left (cannot happen while t < total <= n; a test of values that are the same in every lane)
-            if (__ballot(best0 > INC_LIVE_ABOVE) == 0ull || pv[0] >= n) { r.done = 1; break; }
-            const gcf32 row = M + (size_t)pv[0] * ld;
+        // ---- the picks, on the gains as they are (every wave of every workgroup alike): lane 8 i + g holds the g-th best candidate
+        //      of the i-th block
+        int B = 0;
+        int of_j = 0, of_v = 0, of_same = 0;     // lane u: pick u's block, its sample, the picks before it for the same block
+        double of_gain = 0.0;
+        unsigned guess = 0;                      // the picks that have such
+        unsigned picked = 0;                     // lane k: the picks for block k
+        auto pj = [&](int u) { return __builtin_amdgcn_readlane(of_j, u); };
+        auto pv = [&](int u) { return __builtin_amdgcn_readlane(of_v, u); };
+        auto same = [&](int u) { return (unsigned)__builtin_amdgcn_readlane(of_same, u); };
+        f32x2 mp[S::PICKS][Q], two[2][Q];              // their rows, and the coverage that two of them are held against
+        auto ask_cover = [&](auto uc) __attribute__((always_inline)) {
+            constexpr int u = decltype(uc)::value;
+            if (u < B) {
+                const gcf32 row = (gcf32)(cur_all + (size_t)pj(u) * ld);
 #pragma unroll
-            for (int q = 0; q < Q; ++q) mp[0][q] = pl.at(row, q);
-            resident::take(r, j0, pv[0], best0, lane);
-            resident::strike<S>(G, pv[0], pl.first, lane);
-            const double best1 = inc_value(((unsigned long long)b.hi << 32) | b.lo);
-            const int v1 = __builtin_amdgcn_readfirstlane(b.v);
-            if (j1 >= 0 && r.next == j1 && __ballot(best1 > INC_LIVE_ABOVE) != 0ull && v1 < n) {
-                B = 2;
-                pv[1] = v1;
-                const gcf32 row1 = M + (size_t)v1 * ld;
-#pragma unroll
-                for (int q = 0; q < Q; ++q) mp[1][q] = pl.at(row1, q);
-                resident::take(r, j1, v1, best1, lane);
-                resident::strike<S>(G, v1, pl.first, lane);
+                for (int q = 0; q < Q; ++q) two[u & 1][q] = pl.at(row, q);
             }
+        };
+        int next[BM];
+        double ft = r.f;                         // f and room with the picks made
+        int roomt = r.room;
+        {
+            const Slot cand = sh.list[lane >> 3][lane & 7];
+            unsigned long long avail = __ballot((lane >> 3) < nb && (lane & 7) < sh.listed[lane >> 3]);
+            int at = 0, js = ob[0], turn = 1;    // the next of the blocks in order that has no pick yet
+            unsigned before = 0;                 // the picks for block js
+            double least = INFINITY;             // f among the blocks that have one
+#pragma unroll
+            for (int u = 0; u < S::PICKS; ++u)
+                if (B == u && u < most && js >= 0) {
+                    const unsigned some = at >= 0 ? (unsigned)(avail >> (at & 63)) & 0xFFu : 0u;
+                    if (some != 0u && (before == 0u || ((calm >> js) & 1u))) {
+                        const int src = at + (int)__builtin_ctz(some);
+                        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)cand.hi, src), lo = (unsigned)__builtin_amdgcn_readlane((int)cand.lo, src);
+                        const double gain = inc_value(((unsigned long long)hi << 32) | lo);
+                        const int vstar = __builtin_amdgcn_readlane(cand.v, src);
+                        const gcf32 row = M + (size_t)(unsigned)vstar * (unsigned)ld;
+#pragma unroll
+                        for (int q = 0; q < Q; ++q) mp[u][q] = pl.at(row, q);
+                        of_j = lane == u ? js : of_j;
+                        of_v = lane == u ? vstar : of_v;
+                        of_same = lane == u ? (int)before : of_same;
+                        of_gain = lane == u ? gain : of_gain;
+                        guess |= before ? 1u << u : 0u;
+                        B = u + 1;
+                        const bool it = (lane & 15) == js;
+                        const double more = ft + gain;
+                        ft = it ? more : ft;
+                        roomt = it ? roomt - 1 : roomt;
+                        picked = it ? picked | 1u << u : picked;
+                        avail &= ~__ballot(cand.v == vstar);
+                        if (u + 1 < S::PICKS) {
+                            // the next block: the next in order, unless one that has a pick is at most that much
+                            least = fmin(least, lane_double(ft, js));
+                            const int k = __builtin_amdgcn_readlane(order, turn);
+                            if (turn < nb && __ballot(!(lane_double(r.f, k & 15) < least)) == 0ull) {
+                                js = k;
+                                at = 8 * turn;
+                                before = 0;
+                                ++turn;
+                            } else {
+                                js = resident::choose_block(ft, roomt);
+                                at = 8 * __builtin_amdgcn_readlane(pos, js & 15);
+                                before = (unsigned)__builtin_amdgcn_readlane((int)picked, js & 15);
+                                turn = BM;
+                            }
+                        }
+                    }
+                }
+            if (B == 0) { r.done = 1; break; }   // no candidate left (cannot happen while t < total <= n)
+            ask_cover(std::integral_constant<int, 0>{});
+            ask_cover(std::integral_constant<int, 1>{});
+            // (while these are on their way: the blocks' order after the picks)
+            order_blocks<S::KM>(ft, roomt, lane, next);
+            __builtin_amdgcn_sched_barrier(0);
         }
 
         // ---- coverage: the j of this slice with S(j, v*) > cur_k(j), ascending
-        // f(position in the wave's part of the list, j, old, new) for every entry of pick u
-        auto each_entry = [&](auto uc, auto &&f) {
-            constexpr int u = decltype(uc)::value;
+        // f(position in the wave's part of the list, j, old, new) for every entry
+        auto each_entry = [&](const f32x2 (&row)[Q], const f32x2 (&c)[Q], auto &&f) {
             int cnt = 0;
 #pragma unroll
             for (int q = 0; q < Q; ++q)
                 if (q < pl.nq) {
-                    const bool ch0 = mp[u][q].x > c[u][q].x, ch1 = mp[u][q].y > c[u][q].y;
+                    const bool ch0 = row[q].x > c[q].x, ch1 = row[q].y > c[q].y;
                     const unsigned long long b0 = __ballot(ch0), b1 = __ballot(ch1);
                     if ((b0 | b1) != 0ull) {
                         const int pos = cnt + __popcll(b0 & below) + __popcll(b1 & below);
                         const int v = (int)pl.v0 + 128 * q;
-                        if (ch0) f(pos, v, c[u][q].x, mp[u][q].x);
-                        if (ch1) f(pos + (ch0 ? 1 : 0), v + 1, c[u][q].y, mp[u][q].y);
+                        if (ch0) f(pos, v, c[q].x, row[q].x);
+                        if (ch1) f(pos + (ch0 ? 1 : 0), v + 1, c[q].y, row[q].y);
                         cnt += __popcll(b0) + __popcll(b1);
                     }
                 }
             return cnt;
         };
-        auto stage_entries = [&](auto uc) {
+        each_pick([&](auto uc) {
             constexpr int u = decltype(uc)::value;
-            Entry *held = sh.stage[u * NW + pl.wave];
-            const int cnt = each_entry(uc, [&](int pos, int j, float o, float nw) {
-                if (pos < MW_INLINE) held[pos] = Entry{j, o, nw, 0};
-            });
+            int cnt = 0;
+            if constexpr (u < S::PICKS) if (u < B) {
+                f32x2 (&c)[Q] = two[u & 1];
+                if (u > 0 && ((guess >> u) & 1u)) {
+                    // (what the block's picks before it leave)
+                    const unsigned before = same(u);
+#pragma unroll
+                    for (int p = 0; p < u; ++p)
+                        if ((before >> p) & 1u) {
+#pragma unroll
+                            for (int q = 0; q < Q; ++q) c[q] = (f32x2){max2(c[q].x, mp[p][q].x), max2(c[q].y, mp[p][q].y)};
+                        }
+                }
+                Entry *held = sh.stage[u * NW + pl.wave];
+                cnt = each_entry(mp[u], c, [&](int pos, int j, float o, float nw) {
+                    if (pos < POST - 1) held[pos] = Entry{j, o, nw, 0};
+                });
+            }
+            if constexpr (u + 2 < S::PICKS) ask_cover(std::integral_constant<int, u + 2>{});
             if (lane == 0) sh.count[u * NW + pl.wave] = cnt;
-        };
-        stage_entries(std::integral_constant<int, 0>{});
-        if (B == 2) stage_entries(std::integral_constant<int, 1>{});
-        else if (lane == 0) sh.count[NW + pl.wave] = 0;
+        });
         lds_barrier();
 
         // ---- the lists: lane u NW + i holds the length of wave i's part for pick u
-        const int found = lane < 2 * NW ? sh.count[lane] : 0;
+        const int found = sh.count[lane];
         const int incl = wave_prefix(found, lane);
-        const int len0 = __builtin_amdgcn_readlane(incl, NW - 1), both = __builtin_amdgcn_readlane(incl, 2 * NW - 1);
-        const int len1 = both - len0;
-        // this wave's place in the segments
-        const int base0 = __builtin_amdgcn_readlane(incl - found, pl.wave);
-        const int base1 = __builtin_amdgcn_readlane(incl - found, NW + pl.wave) - len0;
-        auto write_segment = [&](auto uc, int base) {
-            const size_t at = (size_t)pj[decltype(uc)::value] * ld + s0 + base;
-            const RcdClass *c = rarely();
-            const gi32 dlist = (gi32)inc_dlist(*c);
-            const gf32 dold = (gf32)inc_dold(*c), dnew = (gf32)inc_dnew(*c);
-            each_entry(uc, [&](int pos, int j, float o, float nw) {
+        const int all = __builtin_amdgcn_readlane(incl, 63);
+        // the segments' lengths, and this wave's place in them
+        auto before = [&](int u) { return u > 0 ? __builtin_amdgcn_readlane(incl, u * NW - 1) : 0; };
+        auto len = [&](int u) { return __builtin_amdgcn_readlane(incl, u * NW + NW - 1) - before(u); };
+        auto base = [&](int u) { return __builtin_amdgcn_readlane(incl - found, u * NW + pl.wave) - before(u); };
+        // Pick u's part of this wave to memory: its segment and, where asked for, the new coverage.  (Coverage in memory is what the
+        // pick found: nothing has been written for the block, or only for the picks before it.)
+        auto write_segment = [&](int u, bool coverage) {
+            const int k = pj(u);
+            f32x2 row[Q], c[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                row[q] = pl.at(M + (size_t)pv(u) * ld, q);
+                c[q] = pl.at((gcf32)(cur_all + (size_t)k * ld), q);
+            }
+            const size_t at = (size_t)k * ld + s0 + base(u);
+            const RcdClass *d = rarely();
+            const gi32 dlist = (gi32)inc_dlist(*d);
+            const gf32 dold = (gf32)inc_dold(*d), dnew = (gf32)inc_dnew(*d);
+            each_entry(row, c, [&](int pos, int j, float o, float nw) {
                 dev_store(dlist + at + pos, j);
                 dev_store(dold + at + pos, o);
                 dev_store(dnew + at + pos, nw);
+                if (coverage) *off<float>(cur_all + (size_t)k * ld, (unsigned)j * 4u) = nw;
             });
         };
-        const bool in_memory = both > MW_INLINE;    // too many entries for the post
+        // Too many entries for the post: they go to memory.  (There is one segment per block, so of a block's picks the first one's:
+        // a guess behind it does not hold then.)
+        const bool in_memory = all > POST - 1;
         if (in_memory) {
-            write_segment(std::integral_constant<int, 0>{}, base0);
-            if (B == 2) write_segment(std::integral_constant<int, 1>{}, base1);
+            for (int u = 0; u < B; ++u)
+                if (!((guess >> u) & 1u)) write_segment(u, false);
             wait_for_my_stores();
             lds_barrier();
         }
         x.epoch += 1;
         if (pl.wave == 0) {
-            if (!in_memory && found > 0)
-                for (int g = 0; g < found; ++g) sh.mine[incl - found + g] = sh.stage[lane][g];
+            if (!in_memory) {
+                const int start = __builtin_amdgcn_ds_bpermute(4 * (lane & ~(NW - 1)), incl - found);      // of the pick's
+                for (int g = 0; g < found; ++g) {
+                    Entry e = sh.stage[lane][g];
+                    e.j |= (lane / NW) << J_BITS | (incl - found + g - start) << (J_BITS + 3);
+                    sh.mine[1 + incl - found + g] = e;
+                }
+            }
             __builtin_amdgcn_wave_barrier();
-            int a = len0, b = len1, d = 0;
-            if (lane > 0 && lane <= MW_INLINE) {
-                const Entry e = sh.mine[lane - 1];
+            // piece 0: eight lengths of 12 bits
+            int a = len(0) | len(1) << 12 | len(2) << 24, b = len(2) >> 8 | len(3) << 4 | len(4) << 16 | len(5) << 28;
+            int d = len(5) >> 4 | len(6) << 8 | len(7) << 20;
+            if (lane > 0 && lane < POST) {
+                const Entry e = sh.mine[lane];
                 a = e.j;
                 b = __float_as_int(e.o);
                 d = __float_as_int(e.n);
             }
+            const int pieces = in_memory ? 1 : 1 + all;
             i32x4 s[4];
             bool ok = true;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) s[g] = (i32x4){0, 0, 0, 0};
+            auto lengths = [&](int (&l)[BM]) {
+                const unsigned X = (unsigned)s[0].x, Y = (unsigned)s[0].y, Z = (unsigned)s[0].z;
+                l[0] = X & 0xFFF;
+                l[1] = X >> 12 & 0xFFF;
+                l[2] = X >> 24 | (Y & 0xF) << 8;
+                l[3] = Y >> 4 & 0xFFF;
+                l[4] = Y >> 16 & 0xFFF;
+                l[5] = Y >> 28 | (Z & 0xFF) << 4;
+                l[6] = Z >> 8 & 0xFFF;
+                l[7] = Z >> 20;
+            };
+            int l[BM], more = 0;                 // a workgroup per lane: its segments' lengths, the entries in its post
             if (W > 1) {
-                put(x, lane, 0, in_memory ? 1 : 1 + both, a, b, d);
-                ok = get<GET_LIST>(x, lane, s);
+                put(x, lane, 0, pieces, a, b, d);
+                ok = wait_for(x, [&]() {
+                    bool good = true;
+                    if (lane < W) {
+                        dev_load4x4(slot_of(x, lane), s[0], s[1], s[2], s[3]);
+                        good = fits(x, 0, s[0]);
+                        lengths(l);
+                        more = l[0] + l[1] + l[2] + l[3] + l[4] + l[5] + l[6] + l[7];
+                        more = more < POST ? more : 0;
+#pragma unroll
+                        for (int g = 1; g < 4; ++g) good = good && (g > more || fits(x, g, s[g]));
+                    }
+                    return good;
+                });
             } else {
 #pragma unroll
                 for (int g = 0; g < 4; ++g)
-                    s[g] = lane == 0 ? (i32x4){__builtin_amdgcn_readlane(a, g), __builtin_amdgcn_readlane(b, g),
-                                               __builtin_amdgcn_readlane(d, g), 0}
-                                     : (i32x4){0, 0, 0, 0};
+                    if (lane == 0) s[g] = (i32x4){__builtin_amdgcn_readlane(a, g), __builtin_amdgcn_readlane(b, g), __builtin_amdgcn_readlane(d, g), 0};
+                more = lane == 0 && !in_memory ? all : 0;
             }
-            const int l0 = lane < W ? s[0].x : 0, l1 = lane < W ? s[0].y : 0;
-            const int i0 = wave_prefix(l0, lane), i1 = wave_prefix(l1, lane);
-            const int nd0 = __builtin_amdgcn_readlane(i0, 63), nd1 = __builtin_amdgcn_readlane(i1, 63);
-            const int keep0 = nd0 > small ? 0 : nd0, keep1 = nd1 > small ? 0 : nd1;
-            // list 0 from entry 0 on, list 1 behind what of list 0 is applied here
-            const int at0 = i0 - l0, at1 = keep0 + i1 - l1;
-            if (lane < W) {
-                sh.len[0][lane] = keep0 > 0 ? l0 : 0;
-                sh.len[1][lane] = keep1 > 0 ? l1 : 0;
-                sh.pre[0][lane] = at0;
-                sh.pre[1][lane] = at1;
-                sh.fetch[lane] = l0 + l1 > MW_INLINE;
-                if (l0 + l1 <= MW_INLINE) {
+            lengths(l);
 #pragma unroll
-                    for (int g = 0; g < MW_INLINE; ++g) {
-                        const Entry e = {s[g + 1].x, __int_as_float(s[g + 1].y), __int_as_float(s[g + 1].z), 0};
-                        if (g < l0 ? keep0 > 0 : g < l0 + l1 && keep1 > 0) sh.list[g < l0 ? at0 + g : at1 + g - l0] = e;
-                    }
+            for (int u = 0; u < BM; ++u) l[u] = lane < W ? l[u] : 0;
+            // places of the segments in the lists; a list that is too long stays so if its segments' lengths are cut here
+            int kept = 0, total = 0, sure = 0;
+            int nd[BM], ahead[BM];
+            bool room = true;
+#pragma unroll
+            for (int u = 0; u < BM; u += 2) {
+                const int x0 = min(l[u], 1023), x1 = min(l[u + 1], 1023), both = x0 | x1 << 16;
+                const int in = wave_prefix(both, lane), sum = __builtin_amdgcn_readlane(in, 63);
+                nd[u] = sum & 0xFFFF;
+                nd[u + 1] = (int)((unsigned)sum >> 16);
+                ahead[u] = (in - both) & 0xFFFF;
+                ahead[u + 1] = (int)((unsigned)(in - both) >> 16);
+            }
+#pragma unroll
+            for (int u = 0; u < BM; ++u) {
+                const int n_u = nd[u] > small ? 0 : nd[u];
+                room = room && u < B && total + n_u <= ENTRIES;
+                if (room) {
+                    sure = u + 1;
+                    if (nd[u] <= small) kept |= 1 << u;
+                    sh.at[u][lane] = total + ahead[u];
+                    total += n_u;
                 }
             }
-            const unsigned long long lng = __ballot(l0 + l1 > MW_INLINE && (l0 > 0 && keep0 > 0 || l1 > 0 && keep1 > 0));
-            if (lane == 0) { sh.nd[0] = nd0; sh.nd[1] = nd1; sh.any_long = lng != 0ull; sh.ok[0] = ok; }
+            if (__ballot(l[0] > 1023 || l[1] > 1023 || l[2] > 1023 || l[3] > 1023 || l[4] > 1023 || l[5] > 1023 || l[6] > 1023 ||
+                         l[7] > 1023) != 0ull) {
+#pragma unroll
+                for (int u = 0; u < BM; ++u) nd[u] = __builtin_amdgcn_readlane(wave_prefix(l[u], lane), 63);
+            }
+            if (lane == 0) {
+#pragma unroll
+                for (int u = 0; u < BM; ++u) sh.nd[u] = nd[u];
+                sh.kept = kept;
+                sh.sure = sure;
+            }
+            __builtin_amdgcn_wave_barrier();
+            auto place = [&](const i32x4 &e, int g) {
+                const int u = (e.x >> J_BITS) & (BM - 1), i = (unsigned)e.x >> (J_BITS + 3);
+                if (g <= more && ((kept >> u) & 1)) {
+                    const int at = sh.at[u][lane] + i;
+                    sh.entries[at] = Entry{e.x & ((1 << (J_BITS + 3)) - 1), __int_as_float(e.y), __int_as_float(e.z), 0};
+                }
+            };
+#pragma unroll
+            for (int g = 1; g < 4; ++g) place(s[g], g);
+            // entries beyond the first three of a post
+            for (int first = 4; ok && __ballot(more >= first) != 0ull; first += 4) {
+                if (W > 1) {
+                    ok = wait_for(x, [&]() {
+                        bool good = true;
+                        if (more >= first) {
+                            dev_load4x4(slot_of(x, lane) + 4 * first, s[0], s[1], s[2], s[3]);
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) good = good && (first + g > more || fits(x, first + g, s[g]));
+                        }
+                        return good;
+                    });
+                } else {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        if (lane == 0)
+                            s[g] = (i32x4){__builtin_amdgcn_readlane(a, first + g), __builtin_amdgcn_readlane(b, first + g),
+                                           __builtin_amdgcn_readlane(d, first + g), 0};
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) place(s[g], first + g);
+            }
+            // segments that did not travel in the posts
+            bool fetch = false;
+#pragma unroll
+            for (int u = 0; u < BM; ++u) fetch = fetch || (l[u] > 0 && ((kept >> u) & 1));
+            fetch = fetch && more == 0 && lane < W;
+            const bool lng = __ballot(fetch) != 0ull;
+            if (lng) {
+                sh.fetch[lane] = fetch;
+#pragma unroll
+                for (int u = 0; u < BM; ++u) sh.len[u][lane] = (kept >> u) & 1 ? l[u] : 0;
+            }
+            if (lane == 0) {
+                sh.any_long = lng;
+                sh.ok[0] = ok;
+            }
         }
         lds_barrier();
         if (sh.ok[0] == 0) { alive = false; break; }
-        const int nd0 = __builtin_amdgcn_readfirstlane(sh.nd[0]), nd1 = __builtin_amdgcn_readfirstlane(sh.nd[1]);
-        const bool pend0 = nd0 > small, pend1 = nd1 > small;
-        const int n0 = pend0 ? 0 : nd0, total = n0 + (pend1 ? 0 : nd1);
-        entries += nd0 + nd1;
-        if (sh.any_long) {
-            // segments that did not travel in the posts: a wave per segment
-            const RcdClass *c = rarely();
-            const gi32 dlist = (gi32)inc_dlist(*c);
-            const gf32 dold = (gf32)inc_dold(*c), dnew = (gf32)inc_dnew(*c);
+        const int kept = __builtin_amdgcn_readfirstlane(sh.kept);
+        const bool any_long = __builtin_amdgcn_readfirstlane(sh.any_long) != 0;
+        // the picks below `sure` hold, so far: a guess does not behind a list that is left to the update launch, or where segments are
+        // in memory
+        int sure = __builtin_amdgcn_readfirstlane(sh.sure);
+        if (guess) {
+#pragma unroll
+            for (int u = BM - 1; u >= 1; --u)
+                if (same(u) != 0u && ((same(u) & ~(unsigned)kept) != 0u || any_long)) sure = min(sure, u);
+        }
+        const int lengths = sh.nd[lane & (BM - 1)];
+        auto nd = [&](int u) { return __builtin_amdgcn_readlane(lengths, u); };
+        int total = 0;
+#pragma unroll
+        for (int u = 0; u < BM; ++u) total += u < sure && ((kept >> u) & 1) ? nd(u) : 0;
+        if (any_long) {
+            // a wave per workgroup's segments
+            const RcdClass *d = rarely();
+            const gi32 dlist = (gi32)inc_dlist(*d);
+            const gf32 dold = (gf32)inc_dold(*d), dnew = (gf32)inc_dnew(*d);
             for (int i = pl.wave; i < W; i += NW) {
-                const int a = sh.len[0][i], b = sh.len[1][i];
-                if (sh.fetch[i] == 0 || a + b == 0) continue;
-                const int pa = sh.pre[0][i], pb = sh.pre[1][i];
-                const size_t at0 = (size_t)pj[0] * ld + (size_t)i * mwseg, at1 = (size_t)max(pj[1], 0) * ld + (size_t)i * mwseg;
-                for (int e = lane; e < a + b; e += 64) {
-                    const size_t at = e < a ? at0 + e : at1 + (e - a);
-                    sh.list[e < a ? pa + e : pb + (e - a)] = Entry{dev_load(dlist + at), dev_load(dold + at), dev_load(dnew + at), 0};
-                }
+                if (sh.fetch[i] == 0) continue;
+                each_pick([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    if (u >= sure) return;
+                    const int n_u = sh.len[u][i], to = sh.at[u][i];
+                    const size_t from = (size_t)pj(u) * ld + (size_t)i * mwseg;
+                    for (int e = lane; e < n_u; e += 64)
+                        sh.entries[to + e] = Entry{dev_load(dlist + from + e) | u << J_BITS, dev_load(dold + from + e), dev_load(dnew + from + e), 0};
+                });
             }
             lds_barrier();
         }
 
-        // ---- gains: the lists' terms, both lists end to end, added up per pick in list order, then onto the block's gains
+        // ---- gains: the lists' terms, all lists end to end, added up per pick in list order, then onto the block's gains
         {
             double acc[P];
+            int of = -1;                         // pick the sums are for
+            unsigned long long touched = 0ull;   // lanes that have a term
+            auto flush = [&]() {
+                if (touched == 0ull) return;
+                int k = pj(0);
 #pragma unroll
-            for (int i = 0; i < P; ++i) acc[i] = 0.0;
-            auto flush = [&](int k) {
+                for (int u = 1; u < BM; ++u) k = of == u ? pj(u) : k;
                 resident::update_at_index<0, S::KM>(k, [&](auto kc) {
 #pragma unroll
                     for (int i = 0; i < P; ++i) G[decltype(kc)::value][i] += acc[i];
                 });
+                if ((touched & __ballot((mine >> k) & 1u)) != 0ull) dirty |= 1u << k;
             };
             constexpr int U = S::ROWS;           // rows in flight
             for (int first = 0; first < total; first += 64) {
-                const Entry en = sh.list[min(first + lane, total - 1)];
-                const int here = min(64, total - first);
-                const unsigned long long own0 = __ballot(first + lane < n0 && en.j == pv[0]);
-                const unsigned long long own1 = __ballot(first + lane >= n0 && en.j == pv[1]);
-                f32x2 m[U][Q];
-                auto fetch = [&](int i, int e) __attribute__((always_inline)) {
-                    const gcf32 row = M + (size_t)__builtin_amdgcn_readlane(en.j, e) * ld;
+                const Entry en = sh.entries[min(first + lane, total - 1)];
+                const int there = min(64, total - first), j = en.j & ((1 << J_BITS) - 1), pick = en.j >> J_BITS;
+                // U rows at a time, the next ones under way; behind the end the last one again
+                f32x2 m[2][U][Q];
+                auto ask = [&](f32x2 (&rows)[U][Q], int e0) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int q = 0; q < Q; ++q) m[i][q] = pl.at(row, q);
-                };
-                // (the boundary between the lists is looked at entry by entry: as a place of its own behind the loops the
-                // update of the gains took fewer instructions and more registers than there are)
-                auto use = [&](int i, int e) __attribute__((always_inline)) {
-                    if (first + e == n0 && n0 > 0) {
-                        flush(pj[0]);
+                    for (int i = 0; i < U; ++i) {
+                        const gcf32 row = M + (size_t)(unsigned)__builtin_amdgcn_readlane(j, min(e0 + i, there - 1)) * (unsigned)ld;
 #pragma unroll
-                        for (int a = 0; a < P; ++a) acc[a] = 0.0;
-                    }
-                    const float cn = inc_lane_value(en.n, e), co = inc_lane_value(en.o, e);
-#pragma unroll
-                    for (int q = 0; q < Q; ++q) {
-                        acc[2 * q] += inc_term(m[i][q].x, cn, co);
-                        acc[2 * q + 1] += inc_term(m[i][q].y, cn, co);
+                        for (int q = 0; q < Q; ++q) rows[i][q] = pl.at(row, q);
                     }
                 };
-                int e0 = 0;
-                if (here >= 2 * U) {
-                    // a long list: U rows in flight all the time, no condition between the loads
+                // Which of the rows have a sample nearer to j than j's old coverage (late in a run few have one in a wave), and these
+                // rows' terms.
+                int here = there;
+                auto use = [&](const f32x2 (&rows)[U][Q], int e0) __attribute__((always_inline)) {
+                    unsigned hit = 0;
 #pragma unroll
-                    for (int i = 0; i < U; ++i) fetch(i, i);
-                    for (; e0 + 2 * U <= here; e0 += U)
+                    for (int i = 0; i < U; ++i) {
+                        float far = max2(rows[i][0].x, rows[i][0].y);
 #pragma unroll
-                        for (int i = 0; i < U; ++i) {
-                            use(i, e0 + i);
-                            fetch(i, e0 + U + i);
-                        }
-#pragma unroll
-                    for (int i = 0; i < U; ++i) use(i, e0 + i);
-                    e0 += U;
-                }
-                for (; e0 < here; e0 += U) {
+                        for (int q = 1; q < Q; ++q) far = resident::max3(rows[i][q].x, rows[i][q].y, far);
+                        hit |= (__ballot(far > inc_lane_value(en.o, (e0 + i) & 63)) != 0ull ? 1u : 0u) << i;
+                    }
+                    if (here - e0 < U) hit &= (1u << (here - e0)) - 1u;
 #pragma unroll
                     for (int i = 0; i < U; ++i)
-                        if (e0 + i < here) {
-                            // (v* is on its own list, unless an equal sample is in the block already)
-                            if ((own0 >> (e0 + i)) & 1ull) {
+                        if ((hit >> i) & 1u) {
+                            const int u = __builtin_amdgcn_readlane(pick, e0 + i);
+                            if (u != of) {
+                                flush();
+                                of = u;
+                                touched = 0ull;
 #pragma unroll
-                                for (int q = 0; q < Q; ++q) m[i][q] = mp[0][q];
-                            } else if ((own1 >> (e0 + i)) & 1ull) {
-#pragma unroll
-                                for (int q = 0; q < Q; ++q) m[i][q] = mp[1][q];
-                            } else {
-                                fetch(i, e0 + i);
+                                for (int a = 0; a < P; ++a) acc[a] = 0.0;
                             }
-                        }
+                            const float cn = inc_lane_value(en.n, e0 + i), co = inc_lane_value(en.o, e0 + i);
+                            bool any = false;
 #pragma unroll
-                    for (int i = 0; i < U; ++i)
-                        if (e0 + i < here) use(i, e0 + i);
+                            for (int q = 0; q < Q; ++q) {
+                                any |= (rows[i][q].x > co) | (rows[i][q].y > co);
+                                acc[2 * q] += inc_term(rows[i][q].x, cn, co);
+                                acc[2 * q + 1] += inc_term(rows[i][q].y, cn, co);
+                            }
+                            touched |= __ballot(any);
+                        }
+                };
+                // a guess whose similarity to an entry of the block's earlier picks is above the old coverage has lost gain
+                float near[BM];
+                if (guess) {
+                    const gcf32 row = M + (size_t)j * ld;
+#pragma unroll
+                    for (int u = 1; u < BM; ++u)
+                        if ((guess >> u) & 1u) near[u] = row[pv(u)];
                 }
+                ask(m[0], 0);
+                if (there > U) ask(m[1], U);
+                if (guess) {
+#pragma unroll
+                    for (int u = BM - 1; u >= 1; --u)
+                        if (u < sure && ((guess >> u) & 1u) && __ballot(lane < there && ((same(u) >> pick) & 1u) && near[u] > en.o) != 0ull) sure = u;
+                    here = __popcll(__ballot(lane < there && pick < sure));
+                }
+                for (int e0 = 0; e0 < here; e0 += 2 * U) {
+                    use(m[0], e0);
+                    if (e0 + U >= here) break;
+                    if (e0 + 2 * U < here) ask(m[0], e0 + 2 * U);
+                    use(m[1], e0 + U);
+                    if (e0 + 3 * U < here) ask(m[1], e0 + 3 * U);
+                }
+                // the new coverage of this wave's samples (a block that was picked again: in the order of the picks)
+                int k = pj(0);
+#pragma unroll
+                for (int u = 1; u < BM; ++u) k = pick == u ? pj(u) : k;
+                const bool write = lane < here && (unsigned)(j - pl.first) < (unsigned)min(pl.nq * 128, S::WAVE);
+                float RCD_GLOBAL *place = cur_all + (size_t)k * ld + j;
+                if (!guess) {
+                    if (write) *place = en.n;
+                } else {
+                    for (int u = 0; u < sure; ++u)
+                        if (write && pick == u) *place = en.n;
+                }
+                if (here < there) break;         // the rest is of picks that do not hold
             }
-            if (total > 0) flush(total > n0 ? pj[1] : pj[0]);
+            flush();
         }
 
-        // ---- the new coverage of this slice, and what is left to the update launch
-        auto leave = [&](auto uc, int base, int mine, int nd) {
-            constexpr int u = decltype(uc)::value;
-            if (!in_memory) write_segment(uc, base);
-            r.valid &= ~(1u << pj[u]);
+        // ---- the picks that hold; the new coverage of this slice, and what is left to the update launch
+        if (sure < B) {
+            ft = r.f;
+            roomt = r.room;
+#pragma unroll
+            for (int u = 0; u < BM; ++u)
+                if (u < sure && (lane & 15) == pj(u)) {
+                    ft += lane_double(of_gain, u);
+                    roomt -= 1;
+                }
+            order_blocks<S::KM>(ft, roomt, lane, next);
+        }
+        r.f = ft;
+        r.room = roomt;
+#pragma unroll
+        for (int u = 0; u < BM; ++u) ob[u] = next[u];
+        {
+            const bool it = lane >= r.held && lane < r.held + sure;
+            const int j = __builtin_amdgcn_ds_bpermute(4 * (lane - r.held), of_j), v = __builtin_amdgcn_ds_bpermute(4 * (lane - r.held), of_v);
+            r.held_j = it ? j : r.held_j;
+            r.held_v = it ? v : r.held_v;
+        }
+        entries += lane < sure ? lengths : 0;
+        // the samples of this wave among the picks
+        for (unsigned long long it = __ballot(lane < sure && (unsigned)(of_v - pl.first) < (unsigned)S::WAVE); it; it &= it - 1ull) {
+            const int v = pv((int)__builtin_ctzll(it));
+            resident::strike<S>(G, v, pl.first, lane);
+            dirty |= (unsigned)__builtin_amdgcn_readlane((int)mine, ((v - pl.first) & 127) >> 1);
+        }
+        const unsigned all_sure = (1u << sure) - 1u;
+        calm |= (unsigned)__ballot(lane < 16 && (picked & (unsigned)kept & all_sure) != 0u);
+        for (unsigned left = all_sure & ~(unsigned)kept; left; left &= left - 1u) {
+            const int u = (int)__builtin_ctz(left), k = pj(u);
+            write_segment(u, true);
+            calm &= ~(1u << k);
+            r.valid &= ~(1u << k);
             sweeps += 1;
             if (threadIdx.x == 0) {
-                mwbuf[MW_PEND + pj[u] * RCD_MW_MAX + w] = mine;
-                if (w == 0) st.dcount[pj[u]] = nd;
+                mwbuf[MW_PEND + k * RCD_SLICES_MAX + w] = len(u);
+                if (w == 0) st.dcount[k] = nd(u);
             }
-        };
-        auto cover = [&](auto uc) {
-            constexpr int u = decltype(uc)::value;
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (q < pl.nq && (mp[u][q].x > c[u][q].x || mp[u][q].y > c[u][q].y)) {
-                    const f32x2 top = {fmaxf(mp[u][q].x, c[u][q].x), fmaxf(mp[u][q].y, c[u][q].y)};
-                    *off<f32x2>(cur_all + (size_t)pj[u] * ld, (pl.v0 + 128u * q) * 4u) = top;
-                }
-        };
-        cover(std::integral_constant<int, 0>{});
-        if (pend0) leave(std::integral_constant<int, 0>{}, base0, len0, nd0);
-        if (B == 2) {
-            cover(std::integral_constant<int, 1>{});
-            if (pend1) leave(std::integral_constant<int, 1>{}, base1, len1, nd1);
         }
-        if (r.held > 60) {
-            write_held();
-            r.held = 0;
-        }
+        r.held += sure;
+        r.nR -= sure;
+        r.t += sure;
+        if (r.held > 64 - BM) write_held();
     }
     if (!alive) return;          // a bounded wait ran out: plans[0].bad says so, nothing is written back
     write_held();
     if (!r.done) resident::store_gains<S>(G, inc_gains(st), K, ld, pl);
     if (w != 0) return;
+#pragma unroll
+    for (int i = 32; i >= 1; i >>= 1) entries += __shfl_xor(entries, i);
     resident::store_run(r, st, plans, entries * n, sweeps, true, wall_clock64() - tick0);
     const unsigned waiting = (unsigned)__ballot(lane < K && r.room > 0 && !((r.valid >> (lane & 15)) & 1u)) & 0xFFFFu;
     if (threadIdx.x == 0 && !r.done) {
@@ -643,21 +955,3 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         st.nneed = nneed;
     }
 }
-
-namespace sliced {
-
-struct Choice {
-    void (*inc)(RcdClass *, RcdPlan *, const RcdWg *, int, int, unsigned, long long);
-    int threads;
-};
-template <int Q, int KM, int ROWS> Choice choice() { return Choice{rcd_k_inc_steps_sliced<SliceShape<Q, KM, ROWS>>, 512}; }
-
-// The smallest variant whose registers hold a slice's gains for K blocks.
-inline Choice choose(int slice, int K)
-{
-    if (slice <= 1024) return K <= 4 ? choice<1, 4, 12>() : K <= 8 ? choice<1, 8, 12>() : choice<1, 16, 8>();
-    if (slice <= 2048) return K <= 4 ? choice<2, 4, 16>() : K <= 8 ? choice<2, 8, 16>() : choice<2, 16, 6>();
-    return Choice{nullptr, 0};
-}
-
-} // namespace sliced
