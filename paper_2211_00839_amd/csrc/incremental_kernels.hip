@@ -97,14 +97,93 @@ rcd_k_inc_init(const RcdClass *__restrict__ classes)
     if (lane < K) inc_gains(st)[(size_t)lane * ld + v] = a;
 }
 
+namespace {
+
+__device__ __forceinline__ float inc_lane_value(float x, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
+}
+
+// Up to INC_NARROW_ROWS rows: 64 samples to a wave instead of 256, so that a list of one block fills the device, and the list
+// in LDS, so that a wave has thirty-two rows under way whatever the segments' lengths.
+constexpr int INC_NARROW_ROWS = 8192;
+constexpr int INC_NARROW_CHUNK = 1024;      // entries in LDS at a time
+struct NarrowShared {
+    int j[INC_NARROW_CHUNK], before[RCD_SLICES_MAX];     // entries ahead of segment i's
+    float o[INC_NARROW_CHUNK], n[INC_NARROW_CHUNK];
+};
+
+__device__ __forceinline__ void inc_update_narrow(const RcdClass &st, int k, NarrowShared &sh)
+{
+    const int ld = st.ld, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int v = blockIdx.x * 256 + wave * 64 + lane;       // (below ld, which is a multiple of 256)
+    const gcf32 cur = (gcf32)(st.cur + (size_t)k * ld);
+    const gcf32 M = (gcf32)st.M + v;
+    const int nseg = st.mw > 1 ? st.mw : 1;
+    if (tid < 64) {
+        const int len = tid < nseg ? (st.mw > 1 ? st.mwbuf[MW_PEND + k * RCD_SLICES_MAX + tid] : st.dcount[k]) : 0;
+        int incl = len;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const int x = __shfl_up(incl, d);
+            incl += lane >= d ? x : 0;
+        }
+        if (tid < RCD_SLICES_MAX) sh.before[tid] = incl - len;
+    }
+    const int total = st.dcount[k];
+    double acc = 0.0;
+    for (int base = 0; base < total; base += INC_NARROW_CHUNK) {
+        const int cnt = min(INC_NARROW_CHUNK, total - base);
+        __syncthreads();
+        for (int e = tid; e < cnt; e += 256) {
+            const int g = base + e;
+            int sg = 0;                          // the last segment that starts at g or ahead of it
+#pragma unroll
+            for (int d = RCD_SLICES_MAX / 2; d >= 1; d /= 2)
+                if (sg + d < nseg && sh.before[sg + d] <= g) sg += d;
+            const size_t at = (size_t)k * ld + (st.mw > 1 ? (size_t)sg * st.mwseg : 0) + (g - sh.before[sg]);
+            const int j = inc_dlist(st)[at];
+            sh.j[e] = j;
+            sh.o[e] = inc_dold(st)[at];
+            sh.n[e] = cur[j];
+        }
+        __syncthreads();
+        for (int first = 0; first < cnt; first += 64) {
+            const int mine = min(first + lane, cnt - 1), there = min(64, cnt - first);
+            const int j = sh.j[mine];
+            const float o = sh.o[mine], n = sh.n[mine];
+            constexpr int U = 32;
+#pragma unroll
+            for (int e0 = 0; e0 < 64; e0 += U) {
+                if (e0 >= there) break;
+                float m[U];
+                // (behind the end the last row again, whose terms are left out)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    m[u] = __builtin_nontemporal_load(M + (size_t)(unsigned)__builtin_amdgcn_readlane(j, e0 + u) * (unsigned)ld);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (e0 + u < there) acc += inc_term(m[u], inc_lane_value(n, e0 + u), inc_lane_value(o, e0 + u));
+            }
+        }
+    }
+    inc_gains(st)[(size_t)k * ld + v] += acc;
+}
+
+} // namespace
+
 // Apply the pending update lists: for every class, every block with a pending list, every tile of
 // 1024 samples v:  G[k][v] += sum over the list of the term above, added in list order.  Each of the
 // workgroup's 4 waves takes 256 samples and walks the whole list, eight rows in flight; the four waves
 // read neighbouring kilobytes of the same rows at about the same time.
 // grid = (ceil(max ld / 1024), K, ncls).
+// narrow: grid.x = ceil(max ld / 256), and lists of up to INC_NARROW_ROWS rows are applied 256 samples to a workgroup.  Taken where
+// the tiles of 1024 of one block of every class leave compute units idle.
 extern "C" __global__ void __launch_bounds__(256)
-rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int fuse_pct)
+rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int fuse_pct, int narrow)
 {
+    __shared__ NarrowShared sh;
     const RcdClass &st = classes[blockIdx.z];
     const int slot = blockIdx.y;
     if (st.done || slot >= st.nneed) return;
@@ -113,6 +192,10 @@ rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int f
     const int ld = st.ld;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (narrow && st.dcount[k] > 0 && st.dcount[k] <= INC_NARROW_ROWS) {
+        if ((int)blockIdx.x * 256 < ld) inc_update_narrow(st, k, sh);
+        return;
+    }
     const int v0 = blockIdx.x * 1024 + wave * 256;
     if (st.dcount[k] <= 0 || v0 >= ld) return;
     const ccf32 cur = (ccf32)(st.cur + (size_t)k * ld);
@@ -175,11 +258,6 @@ rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int f
 }
 
 namespace {
-
-__device__ __forceinline__ float inc_lane_value(float x, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
-}
 
 // U rows of one 64-row group (the lowest U set bits of `rows`, which has at least U): loads first, then every row's
 // terms for the blocks it is listed for.  mb: this lane's row's membership byte; cnv/cov: per block, this lane's row's

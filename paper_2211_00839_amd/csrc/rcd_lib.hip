@@ -548,6 +548,7 @@ struct Lane {
     unsigned mw_epoch = 0;      // exchanges the earlier launches of this call may have used
     long long mw_spin_ticks = 200000000;   // bound of a grid-barrier wait, 100 MHz ticks (2 s)
     dim3 update_grid;
+    bool update_narrow = false;   // its tiles are 256 samples wide
     int inc_small_bytes = 512 << 10;   // update lists up to this many bytes of rows are applied by the step loop itself
     int inc_fuse_lds = 0;              // LDS bytes of the fused update pass (its membership table); 0: no fused pass
     int inc_fuse_pct = 50;             // a class's lists are fused when together they hold this share of its samples
@@ -802,7 +803,8 @@ struct Lane {
         } else if (incremental) {
             int max_ld = 0;
             for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
-            update_grid = dim3((unsigned)((max_ld + 1023) / 1024), (unsigned)first.K, (unsigned)ncls);
+            update_narrow = (int64_t)((max_ld + 1023) / 1024) * ncls < cu_count();
+            update_grid = dim3((unsigned)(update_narrow ? max_ld / 256 : (max_ld + 1023) / 1024), (unsigned)first.K, (unsigned)ncls);
             // Large classes: while the pending lists of a class overlap (the first rounds), one fused pass applies them
             // all.  Its table of one byte per sample must fit beside nothing else in LDS.
             const int fuse_min_n = env_int("RCD_INC_FUSE_MIN_N", 16384, 0, 1 << 30);
@@ -815,7 +817,7 @@ struct Lane {
                 // few workgroups for the device (one class of 50 000: 49), so the blocks are dealt to several then, down
                 // to two each; one block each is the list-by-list kernel's job.
                 const int slots = std::min(first.K, 8);
-                const int64_t tiles = (int64_t)update_grid.x * ncls;
+                const int64_t tiles = (int64_t)((max_ld + 1023) / 1024) * ncls;
                 const int groups = (int)std::min<int64_t>(slots, std::max<int64_t>(1, (3 * (int64_t)cu_count() + tiles - 1) / tiles));
                 inc_fuse_per_wg = env_int("RCD_INC_FUSE_BLOCKS", (slots + groups - 1) / groups, 1, 8);
                 if (inc_fuse_per_wg >= 2) inc_fuse_lds = (max_ld + 1023) / 1024 * 1024;
@@ -909,10 +911,10 @@ struct Lane {
             else if (incremental)
             {
                 hipLaunchKernelGGL(rcd_k_inc_update, update_grid, dim3(256), 0, stream, (const RcdClass *)g->classes_dev,
-                                   inc_fuse_lds, inc_fuse_pct);
+                                   inc_fuse_lds, inc_fuse_pct, (int)update_narrow);
                 if (inc_fuse_lds > 0)
                     hipLaunchKernelGGL(rcd_k_inc_update_fused,
-                                       dim3(update_grid.x, (unsigned)((std::min(g->K, 8) + inc_fuse_per_wg - 1) / inc_fuse_per_wg),
+                                       dim3((unsigned)(update_narrow ? (update_grid.x + 3) / 4 : update_grid.x), (unsigned)((std::min(g->K, 8) + inc_fuse_per_wg - 1) / inc_fuse_per_wg),
                                             update_grid.z),
                                        dim3(256), (size_t)inc_fuse_lds, stream, (const RcdClass *)g->classes_dev,
                                        g->plan_dev, inc_fuse_lds, inc_fuse_pct, inc_fuse_per_wg);
