@@ -6,16 +6,19 @@
 
 namespace rules {
 
-// Least samples in the largest class of a launch for the step loop that cuts classes into slices (sliced_kernels.hip).  A
-// single class of more than four blocks is cut as soon as one workgroup's registers do not hold it: above 2560 samples with
+// Least samples in the largest class of a launch for the step loop that cuts classes into slices (sliced_kernels.hip).  Classes
+// of more than four blocks are cut as soon as one workgroup's registers do not hold them: above 2560 samples with
 // more than eight blocks, above 3072 with more than four (5120 fit, but too few registers are left).  One class, one
-// workgroup / slices, in ms: eight blocks 3072 samples 12.5 / 17.5, 3073 20.0 / 17.8, five blocks 3072 11.5 / 16.8, 3073
-// 18.1 / 16.9, twelve blocks 2561 18.2 / 17.2, sixteen 19.0 / 17.2.
-constexpr int sliced_from(int classes, int K)
-{
-    if (classes > 1) return 5121;
-    return K > 8 ? 2561 : K > 4 ? 3073 : 5121;
-}
+// workgroup / slices with two picks to a trip, in ms: eight blocks 3072 samples 12.5 / 17.5, 3073 20.0 / 17.8, five blocks 3072
+// 11.5 / 16.8, 3073 18.1 / 16.9, twelve blocks 2561 18.2 / 17.2, sixteen 19.0 / 17.2.  Several, one workgroup to a class and its
+// helpers / slices with up to eight picks to a trip: ten of 5000, four blocks 25.5 / 31.9, five 34.6 / 31.0, eight 40.4 / 32.0, sixteen
+// 54.4 / 38.1, ten of 4000, eight 31.1 / 23.9, ten of 2600, sixteen 23.4 / 19.3, 60 of 3500, eight 39.1 / 37.2, 60 of 4000, five
+// 39.1 / 39.4; thirty of 3000, eight 18.0 / 24.0, ten of 2000, sixteen 10.6 / 14.5.
+constexpr int sliced_from(int /*classes*/, int K) { return K > 8 ? 2561 : K > 4 ? 3073 : 5121; }
+
+// Below that many samples several classes are cut only where the device holds them in slices of 1024: in slices of 2048, 80 of
+// 3500, eight blocks 47.1 / 52.5, 100 of 5000, eight 107 / 121, 100 of 3000, sixteen 58.9 / 63.3 (100 of 4000, eight 69.8 / 66.9).
+constexpr int SLICED_WIDE_FROM = 5121;
 
 // Whether a recompute sweep (fp32) is better cut into pieces of 64 candidates than into tiles of 256 x 256: size(i) = samples of
 // class i of `classes`, features of d values, K blocks, a device of `cus` compute units.

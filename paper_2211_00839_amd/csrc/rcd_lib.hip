@@ -463,8 +463,7 @@ struct SlicedInc {
     std::vector<int> seg;                  // samples per slice of each class
 };
 
-// Taken from 5121 samples in the largest class on, where a class no longer fits one workgroup's registers or does so with
-// too few left; single classes of more than four blocks from where rules::sliced_from() says.
+// Taken where one workgroup's registers no longer hold a class's gains or have too few left (rules::sliced_from()).
 // Measured, the loops taken otherwise / this one with two picks to a trip / with up to eight, in ms: one class of 50 000, eight blocks
 // 586 / 387 / 251 (the whole call), of 20 000, one block 194 / 140 / 86, sixteen 263 / 152 / 121, of 12 000, four 133 / 76 / 55, of 6000, one
 // 43 / 38 / 28, three 45 / 36 / 28, sixteen 56 / 40 / 36, of 3500, seven 22.3 / 19.3 / 18.5; 20 classes of 8000, one block 74 / 64 /
@@ -484,6 +483,17 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     const int min_n = env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, cls[0].K), 0, 0x7fffffff);
     if (min_n == 0 || max_n < min_n) return none;
     if (cus / ncls < 2 || max_n > 1024 * RCD_SLICES_MAX) return none;
+    // Among several smaller ones, where the classes that are cut are a quarter of the work or more (one of 5000 beside forty of
+    // 500, eight blocks 33.9 / 25.5, of 4000 beside 200 of 300 28.4 / 27.5; of 3500 beside forty of 2000 27.0 / 27.7).
+    if (ncls > 1 && max_n < rules::SLICED_WIDE_FROM) {
+        double cut = 0.0, work = 0.0;
+        for (const RcdClass &c : cls) {
+            const double mine = (double)c.n * c.n;
+            work += mine;
+            if (c.n >= min_n) cut += mine;
+        }
+        if (4.0 * cut < work) return none;
+    }
     const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256, K = cls[0].K;
     for (const int least : {given ? given : 1024, given ? given : 2048}) {
         // (large slices with many blocks are the loop's whose exchange area holds fewer workgroups)
@@ -502,6 +512,7 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
             out.seg.push_back(seg);
             for (int w = 0; w < W; ++w) out.map.push_back(RcdWg{i, w, W, 0});
         }
+        if (ncls > 1 && largest > 1024 && !given && max_n < rules::SLICED_WIDE_FROM) return none;
         if ((int)out.map.size() > std::min(cus, RCD_MAX_SWEEP_WGS)) continue;
         if (largest > 1024 && K > 8 && widest > RCD_MW_MAX) continue;
         out.choice = sliced::choose(largest, K);
@@ -750,15 +761,16 @@ struct Lane {
             // bandwidth, and lists four times as long are better applied by the class's own workgroups
             // (20 classes of 50 000: 1.92 -> 1.86 s; one class alone: 774 -> 875 ms, so not there)
             if (ncls >= 4) inc_small_bytes = env_int("RCD_INC_SMALL_KB", 2048, 1, 1 << 20) * 1024;
-            // Where up to eight picks share a trip an update launch costs more trips.  One class: 512 KB (128 rows of a class in
-            // slices of 1024).  Several: an update launch serves all of them at once, so the smaller ones leave more to it, unless
+            // Where up to eight picks share a trip.  One class: 128 KB (32 rows of a class in slices of 1024; 32 / 64 / 128 / 256 / 512 KB:
+            // 50 000 and eight blocks 266 / 250 / 245 / 247 / 257, 20 000 and eight 87.9 / 82.8 / 82.7 / 85.8 / 90.8, one 92.1 / 82.9 / 77.9 /
+            // - / 78.7, 3500 and seven 15.5 / 15.3 / 15.6 / 16.4 / 17.3).  Several: an update launch serves all of them at once, so the smaller ones leave more to it, unless
             // the class has few blocks and nothing to do until then (128 / 256 / 512 / 1024 / 2048 KB: ten of 5121, sixteen blocks 40.6 /
             // 43.1 / 45.9 / 51.4 / 59; one of 6000 beside thirty of 500 36.0 / 40.1 / 43.2 / 49.5 / 54.5; sixteen of 16 000, twelve blocks
             // 233 / 226 / 222 / 223 / -; ten of 6000, one block - / 48.2 / 47.7 / 43.3 / 37.4, three - / 39.1 / 39.7 / 39.1 / 39.5).
             // Slices of 2048: twenty of 15 000, five blocks, 512 / 1024 / 2048 KB 172 / 174 / 182; forty of 12 000, eight 218 / 215 / 216.
             if (slc.inc && slc.several) {
                 const int largest = *std::max_element(slices.seg.begin(), slices.seg.end());
-                const int kb = ncls == 1 ? 512 : largest > 1024 ? 1024 : first.K <= 3 ? 2048 : std::min(512, std::max(128, max_n / 40));
+                const int kb = ncls == 1 ? 128 : largest > 1024 ? 1024 : first.K <= 3 ? 2048 : std::min(512, std::max(128, max_n / 40));
                 inc_small_bytes = env_int("RCD_INC_SMALL_KB", kb, 1, 1 << 20) * 1024;
             }
             HIP_TRY(hipMemcpyAsync(g->wgmap_dev, map.data(), sizeof(RcdWg) * map.size(), hipMemcpyHostToDevice, stream));

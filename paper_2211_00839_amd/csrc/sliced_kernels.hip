@@ -17,8 +17,8 @@
 //     are dropped, and nothing has been written for them.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
 // On mixtures a trip makes 7.8 steps.  With two picks to a trip (sliced_pairs_kernels.hip, for all sizes before) -> now, whole calls in
-// ms: 50 000 samples and eight blocks 387 -> 251, sixteen 480 -> 367, 40 000 and two 305 -> 190, 20 000 and eight 128 -> 92, one
-// 140 -> 86, 12 000 and four 76 -> 55, 6000 and three 36 -> 28.  A trip at 50 000 takes 21 us: candidates 2.4, first exchange 4.3, the
+// ms (inc_update_narrow's part in it: 5 to 10 %): 50 000 samples and eight blocks 390 -> 245, 20 000 and eight 128 -> 83, one
+// 140 -> 78, 12 000 and four 76 -> 48, 6000 and three 36 -> 25.  A trip at 50 000 takes 21 us: candidates 2.4, first exchange 4.3, the
 // picks 2.9, their rows and lists 2.8, second exchange 3.3, the lists' rows 4.5, the rest 1; an instruction of a wave
 // takes some seven cycles here, so the picks' and the exchanges' arithmetic counts as much as the trips through memory.
 // The tags, banks and bounded waits of the exchanges are those of multi_wg_kernels.hip; a post has sixteen pieces.
