@@ -25,6 +25,7 @@
 // Included by rcd_lib.hip after resident_kernels.hip.
 #include <hip/hip_runtime.h>
 #include "rcd_state.h"
+#include "sliced_post.h"
 
 namespace sliced {
 
@@ -64,14 +65,9 @@ template <typename S> struct SlicePlace {
     }
 };
 
-constexpr int BM = 8;              // most picks of a trip
-constexpr int POST = 16;           // 16-byte pieces of a workgroup's post
 constexpr int POST_INTS = 4 * POST;
-constexpr int ENTRIES = 1024;      // list entries that are applied in one trip, at most
 static_assert(2 * POST_INTS == RCD_SLICE_INTS && ENTRIES >= INC_SMALL && RCD_SLICES_MAX <= 64, "exchange area, a lane per workgroup");
-// An entry on its way carries its pick and its place in the pick's segment above the sample's number.
-constexpr int J_BITS = 17;
-static_assert(RCD_SLICES_MAX * 2048 <= 1 << J_BITS, "samples of the largest class that is cut into slices");
+static_assert(RCD_SLICES_MAX * SLICE_SAMPLES <= 1 << J_BITS, "samples of the largest class that is cut into slices");
 
 // High words of keys: a candidate's is above KEY_LIVE (of -1e299: 0x01FCE302); KEY_UNKNOWN where a list of the best ends.
 constexpr unsigned KEY_LIVE = 0x02000000u, KEY_UNKNOWN = 0xFFFFFFFFu;
@@ -615,14 +611,13 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                 const int start = __builtin_amdgcn_ds_bpermute(4 * (lane & ~(NW - 1)), incl - found);      // of the pick's
                 for (int g = 0; g < found; ++g) {
                     Entry e = sh.stage[lane][g];
-                    e.j |= (lane / NW) << J_BITS | (incl - found + g - start) << (J_BITS + 3);
+                    e.j = entry_word(e.j, lane / NW, incl - found + g - start);
                     sh.mine[1 + incl - found + g] = e;
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            // piece 0: eight lengths of 12 bits
-            int a = len(0) | len(1) << 12 | len(2) << 24, b = len(2) >> 8 | len(3) << 4 | len(4) << 16 | len(5) << 28;
-            int d = len(5) >> 4 | len(6) << 8 | len(7) << 20;
+            int a = (int)post_word0(len(0), len(1), len(2)), b = (int)post_word1(len(2), len(3), len(4), len(5));
+            int d = (int)post_word2(len(5), len(6), len(7));
             if (lane > 0 && lane < POST) {
                 const Entry e = sh.mine[lane];
                 a = e.j;
@@ -635,15 +630,8 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
 #pragma unroll
             for (int g = 0; g < 4; ++g) s[g] = (i32x4){0, 0, 0, 0};
             auto lengths = [&](int (&l)[BM]) {
-                const unsigned X = (unsigned)s[0].x, Y = (unsigned)s[0].y, Z = (unsigned)s[0].z;
-                l[0] = X & 0xFFF;
-                l[1] = X >> 12 & 0xFFF;
-                l[2] = X >> 24 | (Y & 0xF) << 8;
-                l[3] = Y >> 4 & 0xFFF;
-                l[4] = Y >> 16 & 0xFFF;
-                l[5] = Y >> 28 | (Z & 0xFF) << 4;
-                l[6] = Z >> 8 & 0xFFF;
-                l[7] = Z >> 20;
+#pragma unroll
+                for (int u = 0; u < BM; ++u) l[u] = post_length(u, (unsigned)s[0].x, (unsigned)s[0].y, (unsigned)s[0].z);
             };
             int l[BM], more = 0;                 // a workgroup per lane: its segments' lengths, the entries in its post
             if (W > 1) {
@@ -654,8 +642,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                         dev_load4x4(slot_of(x, lane), s[0], s[1], s[2], s[3]);
                         good = fits(x, 0, s[0]);
                         lengths(l);
-                        more = l[0] + l[1] + l[2] + l[3] + l[4] + l[5] + l[6] + l[7];
-                        more = more < POST ? more : 0;
+                        more = entries_in_post(l[0] + l[1] + l[2] + l[3] + l[4] + l[5] + l[6] + l[7]);
 #pragma unroll
                         for (int g = 1; g < 4; ++g) good = good && (g > more || fits(x, g, s[g]));
                     }
@@ -669,7 +656,8 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             }
             lengths(l);
 #pragma unroll
-            for (int u = 0; u < BM; ++u) l[u] = lane < W ? l[u] : 0;
+            for (int u = 0; u < BM; ++u) l[u] = believed(ok && lane < W, l[u]);
+            more = believed(ok, more);
             // places of the segments in the lists; a list that is too long stays so if its segments' lengths are cut here
             int kept = 0, total = 0, sure = 0;
             int nd[BM], ahead[BM];
@@ -707,7 +695,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             }
             __builtin_amdgcn_wave_barrier();
             auto place = [&](const i32x4 &e, int g) {
-                const int u = (e.x >> J_BITS) & (BM - 1), i = (unsigned)e.x >> (J_BITS + 3);
+                const int u = entry_pick(e.x), i = entry_place(e.x);
                 if (g <= more && ((kept >> u) & 1)) {
                     const int at = sh.at[u][lane] + i;
                     sh.entries[at] = Entry{e.x & ((1 << (J_BITS + 3)) - 1), __int_as_float(e.y), __int_as_float(e.z), 0};
@@ -808,7 +796,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             constexpr int U = S::ROWS;           // rows in flight
             for (int first = 0; first < total; first += 64) {
                 const Entry en = sh.entries[min(first + lane, total - 1)];
-                const int there = min(64, total - first), j = en.j & ((1 << J_BITS) - 1), pick = en.j >> J_BITS;
+                const int there = min(64, total - first), j = entry_sample(en.j), pick = en.j >> J_BITS;
                 // U rows at a time, the next ones under way; behind the end the last one again
                 f32x2 m[2][U][Q];
                 auto ask = [&](f32x2 (&rows)[U][Q], int e0) __attribute__((always_inline)) {

@@ -413,7 +413,8 @@ rcd_k_inc_steps_pairs(RcdClass *__restrict__ classes, RcdPlan *__restrict__ plan
                                                __builtin_amdgcn_readlane(d, g), 0}
                                      : (i32x4){0, 0, 0, 0};
             }
-            const int l0 = lane < W ? s[0].x : 0, l1 = lane < W ? s[0].y : 0;
+            // (posts that have not come say nothing: no place in the lists may be taken from their words)
+            const int l0 = ok && lane < W ? s[0].x : 0, l1 = ok && lane < W ? s[0].y : 0;
             const int i0 = wave_prefix(l0, lane), i1 = wave_prefix(l1, lane);
             const int nd0 = __builtin_amdgcn_readlane(i0, 63), nd1 = __builtin_amdgcn_readlane(i1, 63);
             const int keep0 = nd0 > small ? 0 : nd0, keep1 = nd1 > small ? 0 : nd1;

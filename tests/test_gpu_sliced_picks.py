@@ -77,3 +77,21 @@ def test_the_most_workgroups(rcd, monkeypatch, n, K):
     # 64 and 63 slices of 256 samples
     S = rcd.similarity(features("mixture", n, n), 32.0)
     compare(rcd, monkeypatch, S, oracle.quota(n, [1 + k % 3 for k in range(K)]), 256)
+
+
+@pytest.mark.parametrize("K,slice_", [(1, 1024), (5, 1024), (12, 1024), (7, 2048), (12, 2048)])
+def test_a_wait_that_runs_out_in_the_middle_of_a_run(rcd, monkeypatch, K, slice_):
+    # the bound set to a millisecond of a launch's ten or more from the host: some wait between the workgroups runs out, whichever
+    # it is, every kernel ends and the call is run again by the loops that wait for nobody
+    n = 6000
+    print(f"a wait runs out, K={K} slice={slice_}", flush=True)
+    S = rcd.similarity(features("mixture", n, 3), 32.0)
+    cap = np.asarray(oracle.quota(n, [1 + k % 3 for k in range(K)]), dtype=np.int64)
+    monkeypatch.setenv("RCD_MW_SLICE", str(slice_))
+    results = []
+    for ms in ("1", "2000"):
+        monkeypatch.setenv("RCD_MW_SPIN_MS", ms)
+        a, o, f = rcd.partition_class(S=S, cap=cap, mode=rcd.MODE_INCREMENTAL)
+        results.append((a.cpu().numpy(), o.cpu().numpy(), f))
+    for x, y in zip(*results):
+        assert np.array_equal(x, y)
