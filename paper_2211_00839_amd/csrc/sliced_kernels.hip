@@ -14,7 +14,10 @@
 //   - a block may be picked again in the same trip.  A gain only falls, so the best of the old gains is the best of the
 //     new ones if its own has not fallen, and it has not if no coverage that the block's earlier picks of the trip raise is below
 //     its similarity.  That is looked up once the lists are known; the first guess that does not hold and the picks behind it
-//     are dropped, and nothing has been written for them.
+//     are dropped, and nothing has been written for them.  A class remembers how many held and guesses as far as that pays
+//     (sliced_guess.h), and looks at twice as many blocks as the last trip served: where every sample has a near copy, most fail.
+//     Always as far as there are candidates -> this: such pairs, one class of 6000, one block 67 -> 41 ms, 20 000, one 222 -> 139;
+//     mixtures 26.5 -> 23.5, 78.6 -> 75.5.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
 // On mixtures a trip makes 7.8 steps.  With two picks to a trip (sliced_pairs_kernels.hip, for all sizes before) -> now, whole calls in
 // ms (inc_update_narrow's part in it: 5 to 10 %): 50 000 samples and eight blocks 390 -> 245, 20 000 and eight 128 -> 83, one
@@ -25,6 +28,7 @@
 // Included by rcd_lib.hip after resident_kernels.hip.
 #include <hip/hip_runtime.h>
 #include "rcd_state.h"
+#include "sliced_guess.h"
 #include "sliced_post.h"
 
 namespace sliced {
@@ -85,6 +89,7 @@ template <typename S> struct SliceShared {
     int nd[BM];                              // the lists' lengths
     int kept, sure, any_long;                // bit u: list u is applied here; picks that fit into this trip
     int ok[BM];
+    int guesses, ahead;                      // how the guesses went (guess_after()), and the most of a trip
 };
 
 // Every row of 16 lanes puts its best candidate and its second for block k into the slots.  They stay from trip to trip: a wave
@@ -372,6 +377,10 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     x.w = w;
     x.epoch = epoch0 + 1;
     x.deadline = tick0 + spin_ticks;
+    if (threadIdx.x == 0) {
+        sh.guesses = GUESS_FIRST;
+        sh.ahead = guesses_ahead(GUESS_FIRST);
+    }
     bool alive = true;
     long long entries = 0, sweeps = 0;
     // everyone has read the descriptor before anyone may write it back
@@ -393,6 +402,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     int ob[BM];                                  // the least blocks, in order
     order_blocks<S::KM>(r.f, r.room, lane, ob);
     unsigned calm = 0;                           // bit k: block k's last list was applied here, its next pick's may be guessed to be
+    int span = BM;                               // the blocks a trip looks at, at most
     unsigned dirty = 0xFFFFu, mine = 0;          // bit k: this wave's entries of block k in the slots are not current; see row_candidates()
     while (alive) {
         if (r.t >= r.total || ob[0] < 0) { r.done = 1; break; }
@@ -403,7 +413,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         int nb = 0, pos = -1, order = -1;        // how many; lane k: block k's place among them; lane i: the i-th of them
 #pragma unroll
         for (int i = 0; i < BM; ++i)
-            if (nb == i && i < most && ob[i] >= 0 && ((r.valid >> (ob[i] & 15)) & 1u)) {
+            if (nb == i && i < min(most, span) && ob[i] >= 0 && ((r.valid >> (ob[i] & 15)) & 1u)) {
                 nb = i + 1;
                 pos = (lane & 15) == ob[i] ? i : pos;
                 order = lane == i ? ob[i] : order;
@@ -420,7 +430,10 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         if (pl.wave < nb) {
             // a wave per block: this workgroup's best, and with everybody's the class's
             const int k = __builtin_amdgcn_readlane(order, pl.wave);
-            const int share = nb > 4 ? 2 : nb > 2 ? 4 : 8;
+            const int ahead = __builtin_amdgcn_readfirstlane(sh.ahead);
+            // how many of the class's are wanted (without guesses only what other blocks' picks take is to be made up for) and posted
+            const int need = ahead == 0 ? min(nb, 3) : nb == 1 ? 1 + ahead : nb == 2 ? 6 : nb <= 4 ? 4 : 3;
+            const int share = nb > 4 || need <= 2 ? 2 : nb > 2 || need <= 4 ? 4 : 8;
             Slot a = sh.slots[k][lane >> 5][lane & 31], p = Slot{0u, 0u, -1, 0};
             bool known = true;
             for (int g = 0; g < share; ++g) {
@@ -432,7 +445,6 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                 if (lane == src) a.hi = 0u;
                 known = known && src < 32;       // (a row's second is gone: its third is not known)
             }
-            const int need = nb == 1 ? 8 : nb == 2 ? 6 : nb <= 4 ? 4 : 3;
             int got;
             if (share == 2) got = class_best<2>(x, lane, pl.wave * 2, p, need, sh.list[pl.wave]);
             else if (share == 4) got = class_best<4>(x, lane, pl.wave * 4, p, need, sh.list[pl.wave]);
@@ -469,6 +481,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         int roomt = r.room;
         {
             const Slot cand = sh.list[lane >> 3][lane & 7];
+            int ahead = __builtin_amdgcn_readfirstlane(sh.ahead);
             unsigned long long avail = __ballot((lane >> 3) < nb && (lane & 7) < sh.listed[lane >> 3]);
             int at = 0, js = ob[0], turn = 1;    // the next of the blocks in order that has no pick yet
             unsigned before = 0;                 // the picks for block js
@@ -477,7 +490,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             for (int u = 0; u < S::PICKS; ++u)
                 if (B == u && u < most && js >= 0) {
                     const unsigned some = at >= 0 ? (unsigned)(avail >> (at & 63)) & 0xFFu : 0u;
-                    if (some != 0u && (before == 0u || ((calm >> js) & 1u))) {
+                    if (some != 0u && (before == 0u || (((calm >> js) & 1u) && ahead > 0))) {
                         const int src = at + (int)__builtin_ctz(some);
                         const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)cand.hi, src), lo = (unsigned)__builtin_amdgcn_readlane((int)cand.lo, src);
                         const double gain = inc_value(((unsigned long long)hi << 32) | lo);
@@ -490,6 +503,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                         of_same = lane == u ? (int)before : of_same;
                         of_gain = lane == u ? gain : of_gain;
                         guess |= before ? 1u << u : 0u;
+                        ahead -= before ? 1 : 0;
                         B = u + 1;
                         const bool it = (lane & 15) == js;
                         const double more = ft + gain;
@@ -913,6 +927,13 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         }
         const unsigned all_sure = (1u << sure) - 1u;
         calm |= (unsigned)__ballot(lane < 16 && (picked & (unsigned)kept & all_sure) != 0u);
+        if (threadIdx.x == 0) {
+            // (everyone has read these two, and reads them again behind a barrier)
+            const int word = guess_after(sh.guesses, __popc(guess & all_sure), ((guess >> sure) & 1u) != 0u);
+            sh.guesses = word;
+            sh.ahead = guesses_ahead(word);
+        }
+        span = blocks_after(__popcll(__ballot(lane < 16 && (picked & all_sure) != 0u)), BM);
         for (unsigned left = all_sure & ~(unsigned)kept; left; left &= left - 1u) {
             const int u = (int)__builtin_ctz(left), k = pj(u);
             write_segment(u, true);
