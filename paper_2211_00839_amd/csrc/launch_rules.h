@@ -8,17 +8,86 @@ namespace rules {
 
 // Least samples in the largest class of a launch for the step loop that cuts classes into slices (sliced_kernels.hip).  Classes
 // of more than four blocks are cut as soon as one workgroup's registers do not hold them: above 2560 samples with
-// more than eight blocks, above 3072 with more than four (5120 fit, but too few registers are left).  One class, one
-// workgroup / slices with two picks to a trip, in ms: eight blocks 3072 samples 12.5 / 17.5, 3073 20.0 / 17.8, five blocks 3072
-// 11.5 / 16.8, 3073 18.1 / 16.9, twelve blocks 2561 18.2 / 17.2, sixteen 19.0 / 17.2.  Several, one workgroup to a class and its
-// helpers / slices with up to eight picks to a trip: ten of 5000, four blocks 25.5 / 31.9, five 34.6 / 31.0, eight 40.4 / 32.0, sixteen
-// 54.4 / 38.1, ten of 4000, eight 31.1 / 23.9, ten of 2600, sixteen 23.4 / 19.3, 60 of 3500, eight 39.1 / 37.2, 60 of 4000, five
-// 39.1 / 39.4; thirty of 3000, eight 18.0 / 24.0, ten of 2000, sixteen 10.6 / 14.5.
-constexpr int sliced_from(int /*classes*/, int K) { return K > 8 ? 2561 : K > 4 ? 3073 : 5121; }
+// more than eight blocks, above 3072 with more than four (5120 fit, but too few registers are left).  One class of a mixture, one
+// workgroup / slices, in ms: eight blocks 3072 samples 13.6 / 13.8, 3073 19.7 / 13.5, five blocks 3072 11.6 / 13.2, 3073 17.7 / 13.3, four
+// 4000 16.0 / 16.7, 5000 20.7 / 20.1, 5121 39.4 / 20.5, one 4000 15.4 / 15.6, 5121 36.1 / 19.6; nine blocks 2561 16.6 / 12.8, sixteen 18.2 /
+// 13.6 (and 2560 18.3 / 14.1: the line could lie lower there).  Several, one workgroup to a class and its
+// helpers / slices: ten of 5000, four blocks 25.2 / 30.1, five 35.1 / 29.2, eight 39.8 / 31.0, sixteen 54.3 / 38.1, ten of 4000, eight 29.8 /
+// 23.4, ten of 2600, sixteen 23.1 / 19.3, 60 of 3500, eight 39.0 / 37.8, 60 of 4000, five 39.4 / 38.2; thirty of 3000, eight 18.0 /
+// 24.0, ten of 2000, sixteen 10.4 / 13.8.
+// wide: in slices of more than 1024 samples.  Several classes, of 2048: 80 of 3500, eight blocks 47.1 / 52.5, 100 of 5000, eight
+// 107 / 121, 100 of 3000, sixteen 58.9 / 63.3 (100 of 4000, eight 69.8 / 66.9).
+constexpr int SLICED_ALWAYS_FROM = 5121;
+constexpr int sliced_from(int classes, int K, bool wide = false)
+{
+    if (wide && classes > 1) return SLICED_ALWAYS_FROM;
+    return K > 8 ? 2561 : K > 4 ? 3073 : SLICED_ALWAYS_FROM;
+}
 
-// Below that many samples several classes are cut only where the device holds them in slices of 1024: in slices of 2048, 80 of
-// 3500, eight blocks 47.1 / 52.5, 100 of 5000, eight 107 / 121, 100 of 3000, sixteen 58.9 / 63.3 (100 of 4000, eight 69.8 / 66.9).
-constexpr int SLICED_WIDE_FROM = 5121;
+// Whether the classes that are cut, those of `least` samples and more, are enough of the work of a launch of several smaller ones: a
+// quarter of it or more.  One workgroup to a class / slices, eight blocks, in ms: one of 5000 beside forty of 500 33.9 / 25.5; of 3500
+// beside forty of 2000 27.0 / 27.7.  size(i) = samples of class i of `classes`.
+template <typename Size> bool enough_is_cut(const Size &size, int classes, int least)
+{
+    int largest = 0;
+    double cut = 0.0, work = 0.0;
+    for (int i = 0; i < classes; ++i) {
+        const int n = size(i);
+        const double mine = (double)n * n;
+        largest = std::max(largest, n);
+        work += mine;
+        if (n >= least) cut += mine;
+    }
+    return classes == 1 || largest >= SLICED_ALWAYS_FROM || 4.0 * cut >= work;
+}
+
+// The slices of the classes of a launch: at least `least` samples each, at most `most` of them to a class.
+// slice(i) gets the samples of class i's slices, a multiple of 256; none is empty.  Their number in all, and the largest and the most.
+struct Slices {
+    int count, largest, most;
+};
+template <typename Pitch, typename Slice> Slices slices(const Pitch &pitch, int classes, int least, int most, const Slice &slice)
+{
+    Slices out = {0, 0, 0};
+    for (int i = 0; i < classes; ++i) {
+        const int ld = pitch(i);
+        int W = std::min(most, (ld + least - 1) / least);
+        const int seg = ((ld + W - 1) / W + 255) / 256 * 256;
+        W = (ld + seg - 1) / seg;
+        slice(i, seg, W);
+        out.count += W;
+        out.largest = std::max(out.largest, seg);
+        out.most = std::max(out.most, W);
+    }
+    return out;
+}
+
+// What the sliced loops hold: samples of a slice, slices of a class, the same in slices of more than 1024 samples with more than
+// eight blocks (another loop, whose exchange area holds fewer).
+constexpr int SLICE_WIDEST = 2048, SLICES_MOST = 64, SLICES_MOST_PAIRS = 32;
+
+// 0 where the classes of a launch are not cut into slices, else the least samples of a slice: 1024 where there are compute units for
+// that, one workgroup to a unit, else 2048.  min_n, wide_n: sliced_from() without and with `wide`; given: samples of a slice, 0 to
+// choose; most, most_pairs: slices of a class at most; wgs: workgroups of the launch at most.
+template <typename Size, typename Pitch>
+int slice_least(const Size &size, const Pitch &pitch, int classes, int K, int cus, int min_n, int wide_n, int given = 0,
+                int most = SLICES_MOST, int most_pairs = SLICES_MOST_PAIRS, int wgs = 1 << 30)
+{
+    int max_n = 0;
+    for (int i = 0; i < classes; ++i) max_n = std::max(max_n, (int)size(i));
+    if (min_n == 0 || max_n < min_n || cus / classes < 2 || max_n > 1024 * SLICES_MOST) return 0;
+    if (!enough_is_cut(size, classes, min_n)) return 0;
+    for (const int least : {given ? given : 1024, given ? given : SLICE_WIDEST}) {
+        const int per_class = std::min(least > 1024 && K > 8 ? most_pairs : most, cus / classes);
+        if (per_class < 2) return 0;
+        const Slices cut = slices(pitch, classes, least, per_class, [](int, int, int) {});
+        if (cut.largest > 1024 && !given && max_n < wide_n) return 0;
+        if (cut.count > std::min(cus, wgs) || cut.largest > SLICE_WIDEST) continue;
+        if (cut.largest > 1024 && K > 8 && cut.most > SLICES_MOST_PAIRS) continue;
+        return least;
+    }
+    return 0;
+}
 
 // Whether a recompute sweep (fp32) is better cut into pieces of 64 candidates than into tiles of 256 x 256: size(i) = samples of
 // class i of `classes`, features of d values, K blocks, a device of `cus` compute units.

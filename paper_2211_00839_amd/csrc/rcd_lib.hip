@@ -476,53 +476,31 @@ struct SlicedInc {
 // 39 / 39 / 48 against 46 / 50 / 53, ten of 5000, five 38 / 38 / 27 against 34 / 39 / 38, eight 43 / 40 / 28 against 40 / 44 / 39, sixteen
 // 56 / 53 / 34 against 41 / 44 / 44; 60 of 6000, four 76 / - / 75 against 87 / - / 92.  Nothing on the host can tell.)
 // Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048; where there are not even
-// those, the loops in memory serve.  Slices of more than 1024 with more than eight blocks keep two picks to a trip (choose()).
+// those, the loops in memory serve (rules::slice_least()).  Slices of more than 1024 with more than eight blocks keep two picks to a
+// trip (choose()).
+static_assert(rules::SLICES_MOST == RCD_SLICES_MAX && rules::SLICES_MOST_PAIRS == RCD_MW_MAX && rules::SLICE_WIDEST == sliced::SLICE_SAMPLES,
+              "the rules' loops");
 SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
 {
     SlicedInc none, out;
     const int ncls = (int)cls.size();
     if (ncls < 1 || env_int("RCD_RESIDENT", 1, 0, 1) == 0) return none;
-    int max_n = 0;
-    for (const RcdClass &c : cls) max_n = std::max(max_n, c.n);
-    const int min_n = env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, cls[0].K), 0, 0x7fffffff);
-    if (min_n == 0 || max_n < min_n) return none;
-    if (cus / ncls < 2 || max_n > 1024 * RCD_SLICES_MAX) return none;
-    // Among several smaller ones, where the classes that are cut are a quarter of the work or more (one of 5000 beside forty of
-    // 500, eight blocks 33.9 / 25.5, of 4000 beside 200 of 300 28.4 / 27.5; of 3500 beside forty of 2000 27.0 / 27.7).
-    if (ncls > 1 && max_n < rules::SLICED_WIDE_FROM) {
-        double cut = 0.0, work = 0.0;
-        for (const RcdClass &c : cls) {
-            const double mine = (double)c.n * c.n;
-            work += mine;
-            if (c.n >= min_n) cut += mine;
-        }
-        if (4.0 * cut < work) return none;
-    }
-    const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256, K = cls[0].K;
-    for (const int least : {given ? given : 1024, given ? given : 2048}) {
-        // (large slices with many blocks are the loop's whose exchange area holds fewer workgroups)
-        const int most = least > 1024 && K > 8 ? RCD_MW_MAX : RCD_SLICES_MAX;
-        const int w_max = std::min(env_int("RCD_MW_MAX_WGS", most, 1, most), cus / ncls);
-        if (w_max < 2) return none;
-        out = none;
-        int largest = 0, widest = 0;
-        for (int i = 0; i < ncls; ++i) {
-            const int ld = cls[i].ld;
-            int W = std::min(w_max, (ld + least - 1) / least);
-            const int seg = ((ld + W - 1) / W + 255) / 256 * 256;
-            W = (ld + seg - 1) / seg;               // no empty slice
-            largest = std::max(largest, seg);
-            widest = std::max(widest, W);
-            out.seg.push_back(seg);
-            for (int w = 0; w < W; ++w) out.map.push_back(RcdWg{i, w, W, 0});
-        }
-        if (ncls > 1 && largest > 1024 && !given && max_n < rules::SLICED_WIDE_FROM) return none;
-        if ((int)out.map.size() > std::min(cus, RCD_MAX_SWEEP_WGS)) continue;
-        if (largest > 1024 && K > 8 && widest > RCD_MW_MAX) continue;
-        out.choice = sliced::choose(largest, K);
-        if (out.choice.inc) return out;
-    }
-    return none;
+    const int K = cls[0].K;
+    const int given = env_int("RCD_MW_SLICE", 0, 0, 1 << 20) / 256 * 256;
+    const int most = env_int("RCD_MW_MAX_WGS", RCD_SLICES_MAX, 1, RCD_SLICES_MAX), most_pairs = env_int("RCD_MW_MAX_WGS", RCD_MW_MAX, 1, RCD_MW_MAX);
+    auto pitch = [&](int i) { return cls[i].ld; };
+    const int least = rules::slice_least([&](int i) { return cls[i].n; }, pitch, ncls, K, cus,
+                                         env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, K), 0, 0x7fffffff),
+                                         env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, K, true), 0, 0x7fffffff), given, most, most_pairs,
+                                         RCD_MAX_SWEEP_WGS);
+    if (least == 0) return none;
+    const int w_max = std::min(least > 1024 && K > 8 ? most_pairs : most, cus / ncls);
+    const rules::Slices cut = rules::slices(pitch, ncls, least, w_max, [&](int i, int seg, int W) {
+        out.seg.push_back(seg);
+        for (int w = 0; w < W; ++w) out.map.push_back(RcdWg{i, w, W, 0});
+    });
+    out.choice = sliced::choose(cut.largest, K);
+    return out;
 }
 
 // Whether a recompute sweep over these classes is cut into pieces of 64 candidates instead of the fast path's 256 x 256 tiles:
