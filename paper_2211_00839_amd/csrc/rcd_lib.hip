@@ -797,7 +797,7 @@ struct Lane {
         } else if (incremental) {
             int max_ld = 0;
             for (const RcdClass &c : g->host) max_ld = std::max(max_ld, c.ld);
-            update_narrow = (int64_t)((max_ld + 1023) / 1024) * ncls < cu_count();
+            update_narrow = env_int("RCD_INC_NARROW", (int64_t)((max_ld + 1023) / 1024) * ncls < cu_count(), 0, 1) != 0;
             update_grid = dim3((unsigned)(update_narrow ? max_ld / 256 : (max_ld + 1023) / 1024), (unsigned)first.K, (unsigned)ncls);
             // Large classes: while the pending lists of a class overlap (the first rounds), one fused pass applies them
             // all.  Its table of one byte per sample must fit beside nothing else in LDS.
