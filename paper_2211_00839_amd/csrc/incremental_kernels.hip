@@ -231,7 +231,7 @@ rcd_k_inc_update(const RcdClass *__restrict__ classes, int fuse_lds_bytes, int f
         }
         if (e < nd) {
             // the segment's last rows, all of them asked for before the first is used (one at a time, up to seven trips to
-            // memory per segment, and a shared class has up to 32 segments)
+            // memory per segment, and a shared class has up to 64 segments)
             f32x4 m[U - 1];
             float cn[U - 1], co[U - 1];
 #pragma unroll

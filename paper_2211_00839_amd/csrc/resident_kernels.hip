@@ -480,11 +480,12 @@ template <typename S, int BM_> struct IncShape : S {
 //   over      number of the launch in which the class's workgroup stopped: its helpers leave
 // The list is in dlist / dold / dnew, the sums go to HELP_SUMS.  Nobody waits for a workgroup that may not be running: what
 // no helper has taken, the class's workgroup takes itself, and it waits only for slices in work.
-// (HP_LEFT, which helpers poll, in another 128-byte line than HP_READY, which they add to: in one line ten classes of 5000 take 1 %
-// longer)
+// (HP_LEFT, which helpers poll and the class's workgroup sets, in another 128-byte line than HP_READY, which they add to: in one line
+// ten classes of 5000 take 1 % longer.  HP_OVER, which they poll too, lies beside HP_READY.)
 enum { HP_LEFT = MW_SLOT + 16, HP_READY = HP_LEFT + RCD_KMAX, HP_OVER = HP_READY + RCD_KMAX, HP_RUNS = HP_OVER + 16,
        HP_END = HP_RUNS + 8 * RCD_KMAX };
-static_assert(HP_END <= MW_PEND && HP_LEFT % 16 == 0, "exchange area too small");
+static_assert(HP_END <= MW_PEND && RCD_MW_INTS % 32 == 0, "exchange area too small");
+static_assert((HP_LEFT + RCD_KMAX - 1) / 32 < HP_READY / 32, "two lines");
 
 struct Lists {
     gi32 box;                // the class's exchange area

@@ -41,10 +41,11 @@ using resident::f32x2;
 using resident::lds_barrier;
 using resident::off;
 
-// 512 threads, Q pieces of two samples each, at most KM blocks, twice ROWS rows of the lists in flight, at most PICKS picks to a
-// trip.  (Q = 2: eight rows and two sets of them would spill the picks' rows, which makes a wait of each spill.)
-template <int Q, int KM, int ROWS_, int PICKS_> struct SliceShape : Shape<512, Q, KM> {
-    static constexpr int ROWS = ROWS_, PICKS = PICKS_;
+// 512 threads, Q pieces of two samples each, at most KM blocks, twice ROWS rows of the lists in flight.  (Q = 2 with eight rows and
+// two sets of them would spill more of the picks' rows, which makes a wait of each spill: 32 registers are spilled with eight
+// blocks and ROWS = 4, four with four blocks, and two of <1, 16, 8>.)
+template <int Q, int KM, int ROWS_> struct SliceShape : Shape<512, Q, KM> {
+    static constexpr int ROWS = ROWS_;
 };
 
 // Where a wave is: it owns the class's samples [first, first + 128 Q), pieces from nq on lie outside the slice.  A row is
@@ -409,7 +410,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         if (r.t - r.t0 >= r.max_steps) { r.stop = 1; break; }
         if (!((r.valid >> ob[0]) & 1u)) break;
         // ---- the blocks: the u-th pick goes to one of the u least (f never falls)
-        const int most = min(min(r.total - r.t, r.max_steps - (r.t - r.t0)), S::PICKS);
+        const int most = min(min(r.total - r.t, r.max_steps - (r.t - r.t0)), BM);
         int nb = 0, pos = -1, order = -1;        // how many; lane k: block k's place among them; lane i: the i-th of them
 #pragma unroll
         for (int i = 0; i < BM; ++i)
@@ -467,7 +468,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         auto pj = [&](int u) { return __builtin_amdgcn_readlane(of_j, u); };
         auto pv = [&](int u) { return __builtin_amdgcn_readlane(of_v, u); };
         auto same = [&](int u) { return (unsigned)__builtin_amdgcn_readlane(of_same, u); };
-        f32x2 mp[S::PICKS][Q], two[2][Q];              // their rows, and the coverage that two of them are held against
+        f32x2 mp[BM][Q], two[2][Q];              // their rows, and the coverage that two of them are held against
         auto ask_cover = [&](auto uc) __attribute__((always_inline)) {
             constexpr int u = decltype(uc)::value;
             if (u < B) {
@@ -487,7 +488,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             unsigned before = 0;                 // the picks for block js
             double least = INFINITY;             // f among the blocks that have one
 #pragma unroll
-            for (int u = 0; u < S::PICKS; ++u)
+            for (int u = 0; u < BM; ++u)
                 if (B == u && u < most && js >= 0) {
                     const unsigned some = at >= 0 ? (unsigned)(avail >> (at & 63)) & 0xFFu : 0u;
                     if (some != 0u && (before == 0u || (((calm >> js) & 1u) && ahead > 0))) {
@@ -511,7 +512,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                         roomt = it ? roomt - 1 : roomt;
                         picked = it ? picked | 1u << u : picked;
                         avail &= ~__ballot(cand.v == vstar);
-                        if (u + 1 < S::PICKS) {
+                        if (u + 1 < BM) {
                             // the next block: the next in order, unless one that has a pick is at most that much
                             least = fmin(least, lane_double(ft, js));
                             const int k = __builtin_amdgcn_readlane(order, turn);
@@ -559,7 +560,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         each_pick([&](auto uc) {
             constexpr int u = decltype(uc)::value;
             int cnt = 0;
-            if constexpr (u < S::PICKS) if (u < B) {
+            if (u < B) {
                 f32x2 (&c)[Q] = two[u & 1];
                 if (u > 0 && ((guess >> u) & 1u)) {
                     // (what the block's picks before it leave)
@@ -576,7 +577,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                     if (pos < POST - 1) held[pos] = Entry{j, o, nw, 0};
                 });
             }
-            if constexpr (u + 2 < S::PICKS) ask_cover(std::integral_constant<int, u + 2>{});
+            if constexpr (u + 2 < BM) ask_cover(std::integral_constant<int, u + 2>{});
             if (lane == 0) sh.count[u * NW + pl.wave] = cnt;
         });
         lds_barrier();

@@ -588,13 +588,17 @@ struct Choice {
     int threads;
     bool several;            // up to eight picks to a trip, not two
 };
-template <int Q, int KM, int ROWS, int PICKS> Choice choice() { return Choice{rcd_k_inc_steps_sliced<SliceShape<Q, KM, ROWS, PICKS>>, 512, true}; }
+template <int Q, int KM, int ROWS> Choice choice() { return Choice{rcd_k_inc_steps_sliced<SliceShape<Q, KM, ROWS>>, 512, true}; }
 
+// Slices over 1024 with up to eight blocks, two picks to a trip (no register spilled) / up to eight, mixtures, in ms: forty classes of
+// 12 000, eight blocks 222 / 214.5, 20 of 15 000, five 182 / 174, 16 of 20 000, eight 291 / 280, 60 of 6000, four 71 / 69, forty of 8000, one
+// 78 / 66; every sample with a near copy 230 / 238, 183 / 199, 301 / 291, 76 / 87, 83 / 93; four picks to a trip, with which <2, 8> spills 16
+// registers, 223, 179, 289, 70, 68.5 on mixtures.
 // The smallest variant whose registers hold a slice's gains for K blocks.  At most RCD_MW_MAX slices to a class for the last.
 inline Choice choose(int slice, int K)
 {
-    if (slice <= 1024) return K <= 4 ? choice<1, 4, 8, 8>() : K <= 8 ? choice<1, 8, 8, 8>() : choice<1, 16, 8, 8>();
-    if (slice <= 2048) return K <= 4 ? choice<2, 4, 4, 8>() : K <= 8 ? choice<2, 8, 4, 8>() : Choice{rcd_k_inc_steps_pairs<pairs::PairShape<2, 16, 6>>, 512, false};
+    if (slice <= 1024) return K <= 4 ? choice<1, 4, 8>() : K <= 8 ? choice<1, 8, 8>() : choice<1, 16, 8>();
+    if (slice <= 2048) return K <= 4 ? choice<2, 4, 4>() : K <= 8 ? choice<2, 8, 4>() : Choice{rcd_k_inc_steps_pairs<pairs::PairShape<2, 16, 6>>, 512, false};
     return Choice{nullptr, 0, false};
 }
 
