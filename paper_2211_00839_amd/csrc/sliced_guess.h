@@ -9,6 +9,9 @@ namespace sliced {
 // made.
 constexpr int GUESS_ONE = 4096, GUESS_BITS = 4, GUESS_TRIPS = 4;
 constexpr int GUESS_FIRST = GUESS_ONE << GUESS_BITS;
+// It lasts from launch to launch of a call (several classes: some twenty trips each), in memory that is zero when a call starts.
+constexpr int guess_stored(int word) { return GUESS_FIRST - word; }
+constexpr int guess_loaded(int stored) { return GUESS_FIRST - stored; }
 
 // The most guesses of the next trip: as many as hold together in two trips of five (a step in a trip of its own takes about
 // two and a half times what a pick takes); where one does not, one every GUESS_TRIPS trips to see whether that is still so.

@@ -16,8 +16,8 @@
 //     its similarity.  That is looked up once the lists are known; the first guess that does not hold and the picks behind it
 //     are dropped, and nothing has been written for them.  A class remembers how many held and guesses as far as that pays
 //     (sliced_guess.h), and looks at twice as many blocks as the last trip served: where every sample has a near copy, most fail.
-//     Always as far as there are candidates -> this: such pairs, one class of 6000, one block 67 -> 41 ms, 20 000, one 222 -> 139;
-//     mixtures 26.5 -> 23.5, 78.6 -> 75.5.
+//     Always as far as there are candidates -> this: such pairs, one class of 6000, one block 67 -> 40 ms, 20 000, one 222 -> 138;
+//     mixtures 26.5 -> 23.3, 78.6 -> 74.3.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
 // On mixtures a trip makes 7.8 steps.  With two picks to a trip (sliced_pairs_kernels.hip, for all sizes before) -> now, whole calls in
 // ms (inc_update_narrow's part in it: 5 to 10 %): 50 000 samples and eight blocks 390 -> 245, 20 000 and eight 128 -> 83, one
@@ -379,8 +379,9 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     x.epoch = epoch0 + 1;
     x.deadline = tick0 + spin_ticks;
     if (threadIdx.x == 0) {
-        sh.guesses = GUESS_FIRST;
-        sh.ahead = guesses_ahead(GUESS_FIRST);
+        const int word = guess_loaded(mwbuf[MW_SLOT]);       // (this loop's posts are in inc_slices())
+        sh.guesses = word;
+        sh.ahead = guesses_ahead(word);
     }
     bool alive = true;
     long long entries = 0, sweeps = 0;
@@ -955,6 +956,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     write_held();
     if (!r.done) resident::store_gains<S>(G, inc_gains(st), K, ld, pl);
     if (w != 0) return;
+    if (threadIdx.x == 0) mwbuf[MW_SLOT] = guess_stored(sh.guesses);
 #pragma unroll
     for (int i = 32; i >= 1; i >>= 1) entries += __shfl_xor(entries, i);
     resident::store_run(r, st, plans, entries * n, sweeps, true, wall_clock64() - tick0);

@@ -591,8 +591,8 @@ struct Choice {
 template <int Q, int KM, int ROWS> Choice choice() { return Choice{rcd_k_inc_steps_sliced<SliceShape<Q, KM, ROWS>>, 512, true}; }
 
 // Slices over 1024 with up to eight blocks, two picks to a trip (no register spilled) / up to eight, mixtures, in ms: forty classes of
-// 12 000, eight blocks 222 / 214.5, 20 of 15 000, five 182 / 174, 16 of 20 000, eight 291 / 280, 60 of 6000, four 71 / 69, forty of 8000, one
-// 78 / 66; every sample with a near copy 230 / 238, 183 / 199, 301 / 291, 76 / 87, 83 / 93; four picks to a trip, with which <2, 8> spills 16
+// 12 000, eight blocks 222 / 214, 20 of 15 000, five 182 / 172, 16 of 20 000, eight 291 / 280, 60 of 6000, four 71 / 68, forty of 8000, one
+// 78 / 66; every sample with a near copy 230 / 235, 183 / 193, 301 / 288, 76 / 85, 83 / 90; four picks to a trip, with which <2, 8> spills 16
 // registers, 223, 179, 289, 70, 68.5 on mixtures.
 // The smallest variant whose registers hold a slice's gains for K blocks.  At most RCD_MW_MAX slices to a class for the last.
 inline Choice choose(int slice, int K)

@@ -35,6 +35,7 @@ static Run trips(int count, double chance)
 int main()
 {
     EXPECT(guesses_ahead(GUESS_FIRST) == 7);
+    EXPECT(guess_loaded(0) == GUESS_FIRST);              // a call starts with zeroed memory
     Run r = trips(1000, 1.0);
     EXPECT(r.made == 7000);
     r = trips(10000, 0.99);
@@ -51,6 +52,7 @@ int main()
         word = guess_after(word, (int)(rng() % 8), rng() % 2 != 0);
         EXPECT((word >> GUESS_BITS) >= 0 && (word >> GUESS_BITS) <= GUESS_ONE);
         EXPECT((word & ((1 << GUESS_BITS) - 1)) < GUESS_TRIPS);
+        EXPECT(guess_loaded(guess_stored(word)) == word);
         EXPECT(guesses_ahead(word) >= 0 && guesses_ahead(word) <= 7);
     }
     // blocks: one after a trip that served one, all of them again in three trips
