@@ -9,6 +9,7 @@ namespace sliced {
 // made.
 constexpr int GUESS_ONE = 4096, GUESS_BITS = 4, GUESS_TRIPS = 4;
 constexpr int GUESS_FIRST = GUESS_ONE << GUESS_BITS;
+constexpr int GUESS_MOST = 7;      // of a trip: its picks but the first
 // It lasts from launch to launch of a call (several classes: some twenty trips each), in memory that is zero when a call starts.
 constexpr int guess_stored(int word) { return GUESS_FIRST - word; }
 constexpr int guess_loaded(int stored) { return GUESS_FIRST - stored; }
@@ -18,9 +19,9 @@ constexpr int guess_loaded(int stored) { return GUESS_FIRST - stored; }
 constexpr int guesses_ahead(int word)
 {
     const int share = word >> GUESS_BITS, trips = word & ((1 << GUESS_BITS) - 1);
-    constexpr int at_least[7] = {1638, 2591, 3018, 3257, 3410, 3516, 3593};      // GUESS_ONE times 0.4 to the power of 1 / m
+    constexpr int at_least[GUESS_MOST] = {1638, 2591, 3018, 3257, 3410, 3516, 3593};      // GUESS_ONE times 0.4 to the power of 1 / m
     int most = 0;
-    for (int m = 0; m < 7; ++m) most += share >= at_least[m] ? 1 : 0;
+    for (int m = 0; m < GUESS_MOST; ++m) most += share >= at_least[m] ? 1 : 0;
     return most == 0 && trips >= GUESS_TRIPS - 1 ? 1 : most;
 }
 
@@ -29,8 +30,8 @@ constexpr int guess_after(int word, int held, bool cut)
 {
     int share = word >> GUESS_BITS, trips = word & ((1 << GUESS_BITS) - 1);
     if (held == 0 && !cut) return trips < GUESS_TRIPS - 1 ? word + 1 : word;
-    for (int i = 0; i < held; ++i) share += (GUESS_ONE - share) / 16;
-    if (cut) share -= share / 16;
+    share += held * ((GUESS_ONE - share) >> 4);
+    if (cut) share -= share >> 4;
     return share << GUESS_BITS;
 }
 

@@ -44,8 +44,12 @@ using resident::off;
 // 512 threads, Q pieces of two samples each, at most KM blocks, twice ROWS rows of the lists in flight.  (Q = 2 with eight rows and
 // two sets of them would spill more of the picks' rows, which makes a wait of each spill: 32 registers are spilled with eight
 // blocks and ROWS = 4, four with four blocks, and two of <1, 16, 8>.)
+// LEARN: guesses are made as far as they hold.  With more than eight blocks a trip's picks go to eight of them and guesses are rare:
+// keeping count took 0.1 to 0.9 % of a call and gave nothing (6000, sixteen blocks 28.6 / 28.8 ms, every sample with a near copy, ten of 5000
+// 40.7 / 40.8).
 template <int Q, int KM, int ROWS_> struct SliceShape : Shape<512, Q, KM> {
     static constexpr int ROWS = ROWS_;
+    static constexpr bool LEARN = KM <= BM;
 };
 
 // Where a wave is: it owns the class's samples [first, first + 128 Q), pieces from nq on lie outside the slice.  A row is
@@ -378,7 +382,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     x.w = w;
     x.epoch = epoch0 + 1;
     x.deadline = tick0 + spin_ticks;
-    if (threadIdx.x == 0) {
+    if (S::LEARN && threadIdx.x == 0) {
         const int word = guess_loaded(mwbuf[MW_SLOT]);       // (this loop's posts are in inc_slices())
         sh.guesses = word;
         sh.ahead = guesses_ahead(word);
@@ -432,7 +436,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         if (pl.wave < nb) {
             // a wave per block: this workgroup's best, and with everybody's the class's
             const int k = __builtin_amdgcn_readlane(order, pl.wave);
-            const int ahead = __builtin_amdgcn_readfirstlane(sh.ahead);
+            const int ahead = S::LEARN ? __builtin_amdgcn_readfirstlane(sh.ahead) : GUESS_MOST;
             // how many of the class's are wanted (without guesses only what other blocks' picks take is to be made up for) and posted
             const int need = ahead == 0 ? min(nb, 3) : nb == 1 ? 1 + ahead : nb == 2 ? 6 : nb <= 4 ? 4 : 3;
             const int share = nb > 4 || need <= 2 ? 2 : nb > 2 || need <= 4 ? 4 : 8;
@@ -483,7 +487,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         int roomt = r.room;
         {
             const Slot cand = sh.list[lane >> 3][lane & 7];
-            int ahead = __builtin_amdgcn_readfirstlane(sh.ahead);
+            int ahead = S::LEARN ? __builtin_amdgcn_readfirstlane(sh.ahead) : GUESS_MOST;
             unsigned long long avail = __ballot((lane >> 3) < nb && (lane & 7) < sh.listed[lane >> 3]);
             int at = 0, js = ob[0], turn = 1;    // the next of the blocks in order that has no pick yet
             unsigned before = 0;                 // the picks for block js
@@ -505,7 +509,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
                         of_same = lane == u ? (int)before : of_same;
                         of_gain = lane == u ? gain : of_gain;
                         guess |= before ? 1u << u : 0u;
-                        ahead -= before ? 1 : 0;
+                        if constexpr (S::LEARN) ahead -= before ? 1 : 0;
                         B = u + 1;
                         const bool it = (lane & 15) == js;
                         const double more = ft + gain;
@@ -929,7 +933,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
         }
         const unsigned all_sure = (1u << sure) - 1u;
         calm |= (unsigned)__ballot(lane < 16 && (picked & (unsigned)kept & all_sure) != 0u);
-        if (threadIdx.x == 0) {
+        if (S::LEARN && threadIdx.x == 0) {
             // (everyone has read these two, and reads them again behind a barrier)
             const int word = guess_after(sh.guesses, __popc(guess & all_sure), ((guess >> sure) & 1u) != 0u);
             sh.guesses = word;
@@ -956,7 +960,7 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
     write_held();
     if (!r.done) resident::store_gains<S>(G, inc_gains(st), K, ld, pl);
     if (w != 0) return;
-    if (threadIdx.x == 0) mwbuf[MW_SLOT] = guess_stored(sh.guesses);
+    if (S::LEARN && threadIdx.x == 0) mwbuf[MW_SLOT] = guess_stored(sh.guesses);
 #pragma unroll
     for (int i = 32; i >= 1; i >>= 1) entries += __shfl_xor(entries, i);
     resident::store_run(r, st, plans, entries * n, sweeps, true, wall_clock64() - tick0);
