@@ -464,11 +464,11 @@ struct SlicedInc {
 };
 
 // Taken where one workgroup's registers no longer hold a class's gains or have too few left (rules::sliced_from()).
-// Measured, the loops taken otherwise / this one with two picks to a trip / with up to eight, in ms: one class of 50 000, eight blocks
-// 586 / 387 / 251 (the whole call), of 20 000, one block 194 / 140 / 86, sixteen 263 / 152 / 121, of 12 000, four 133 / 76 / 55, of 6000, one
-// 43 / 38 / 28, three 45 / 36 / 28, sixteen 56 / 40 / 36, of 3500, seven 22.3 / 19.3 / 18.5; 20 classes of 8000, one block 74 / 64 /
-// 58, four 89 / 71 / 60, sixteen 147 / 110 / 95, ten of 6000, six 65 / 45 / 39, ten of 5121, sixteen 63 / 56 / 40; one of 6000 beside
-// thirty of 500, four 49 / 40 / 33, sixteen 55 / 53 / 36.
+// Measured on mixtures of 64 features, whole calls in ms, with two picks to a trip / with up to eight: one class of 50 000, eight blocks
+// 421 / 246, of 20 000, one block 141 / 74, eight 139 / 83, sixteen 154 / 101, of 12 000, four 71 / 47, of 6000, one 39 / 23, three 32 /
+// 23, sixteen 40 / 29, of 3500, seven 19.7 / 15.3; 20 classes of 8000, one block 66 / 51, four 66 / 57, sixteen 106 / 95, 15 of 12 000, seven
+// 121 / 103, ten of 6000, six 45 / 37, ten of 5121, sixteen 57 / 40; one of 6000 beside thirty of 500, four 38 / 28, sixteen 53 / 34.  The
+// loops in memory took one class of 50 000 586, of 12 000, four 133, of 6000, one 43; 20 of 8000, four 89.
 // (Mixtures and single clouds of 4 to 512 features gain alike.  Samples with copies gain less or lose, since a guess at the copy of a
 // pick fails and exact copies tie (a slice knows two candidates of a tie): every sample with one near copy / one exact copy / 50 points
 // repeated, two picks to a trip or one workgroup against this: one of 6000, one block 39 / 37 / 33 against 40 / 50 / 36, four 34 / 34 / 38 against
@@ -743,13 +743,15 @@ struct Lane {
             // bandwidth, and lists four times as long are better applied by the class's own workgroups
             // (20 classes of 50 000: 1.92 -> 1.86 s; one class alone: 774 -> 875 ms, so not there)
             if (ncls >= 4) inc_small_bytes = env_int("RCD_INC_SMALL_KB", 2048, 1, 1 << 20) * 1024;
-            // Where up to eight picks share a trip.  One class: 128 KB (32 rows of a class in slices of 1024; 32 / 64 / 128 / 256 / 512 KB:
-            // 50 000 and eight blocks 266 / 250 / 245 / 247 / 257, 20 000 and eight 87.9 / 82.8 / 82.7 / 85.8 / 90.8, one 92.1 / 82.9 / 77.9 /
-            // - / 78.7, 3500 and seven 15.5 / 15.3 / 15.6 / 16.4 / 17.3).  Several: an update launch serves all of them at once, so the smaller ones leave more to it, unless
-            // the class has few blocks and nothing to do until then (128 / 256 / 512 / 1024 / 2048 KB: ten of 5121, sixteen blocks 40.6 /
-            // 43.1 / 45.9 / 51.4 / 59; one of 6000 beside thirty of 500 36.0 / 40.1 / 43.2 / 49.5 / 54.5; sixteen of 16 000, twelve blocks
-            // 233 / 226 / 222 / 223 / -; ten of 6000, one block - / 48.2 / 47.7 / 43.3 / 37.4, three - / 39.1 / 39.7 / 39.1 / 39.5).
-            // Slices of 2048: twenty of 15 000, five blocks, 512 / 1024 / 2048 KB 172 / 174 / 182; forty of 12 000, eight 218 / 215 / 216.
+            // Where up to eight picks share a trip.  One class: 128 KB (32 rows of a class in slices of 1024).  Several: an update launch
+            // serves all of them at once, so the smaller ones leave more to it, unless the class has few blocks and nothing to do until
+            // then.  64 / 128 / 256 / 512 / 1024 / 2048 KB, ms (two runs differ by up to 0.5 %):
+            //   one of 50 000, eight blocks 248 / 246 / 247 / 256 / 272 / 288; of 20 000, eight 84.3 / 83.6 / 86.9 / 91.6 / 98.8 / 108.4, one
+            //   80.1 / 74.3 / 71.6 / 70.7 / 71.0 / 71.3; of 3500, seven 15.1 / 15.3 / 15.9 / 16.9 / 18.4 / 19.8
+            //   ten of 5121, sixteen 41.1 / 40.4 / 43.7 / 47.2 / 52.7 / 60.5; one of 6000 beside thirty of 500, sixteen 31.6 / 34.0 / 38.1 /
+            //   42.0 / 47.7 / 54.4; ten of 6000, one 37.2 / 39.5 / 37.1 / 38.3 / 35.3 / 32.7, three 35.2 / 34.2 / 35.3 / 34.8 / 32.7 / 35.1
+            //   slices over 1024: twenty of 15 000, five 192 / 181 / 169 / 167 / 172 / 177; forty of 12 000, eight 254 / 239 / 226 / 223 /
+            //   219 / 224
             if (slc.inc && slc.several) {
                 const int largest = *std::max_element(slices.seg.begin(), slices.seg.end());
                 const int kb = ncls == 1 ? 128 : largest > 1024 ? 1024 : first.K <= 3 ? 2048 : std::min(512, std::max(128, max_n / 40));

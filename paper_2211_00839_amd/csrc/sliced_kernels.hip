@@ -19,10 +19,10 @@
 //     Always as far as there are candidates -> this: such pairs, one class of 6000, one block 67 -> 40 ms, 20 000, one 222 -> 138;
 //     mixtures 26.5 -> 23.3, 78.6 -> 74.3.
 // Picks, sums and ties are those of the other loops, in their order: the results are the same bits.
-// On mixtures a trip makes 7.8 steps.  With two picks to a trip (sliced_pairs_kernels.hip, for all sizes before) -> now, whole calls in
-// ms (inc_update_narrow's part in it: 5 to 10 %): 50 000 samples and eight blocks 390 -> 245, 20 000 and eight 128 -> 83, one
-// 140 -> 78, 12 000 and four 76 -> 48, 6000 and three 36 -> 25.  A trip at 50 000 takes 21 us: candidates 2.4, first exchange 4.3, the
-// picks 2.9, their rows and lists 2.8, second exchange 3.3, the lists' rows 4.5, the rest 1; an instruction of a wave
+// On mixtures a trip makes 7.8 steps.  With two picks to a trip -> now, whole calls in ms on mixtures of 64 features (inc_update_narrow's
+// part in it: 5 to 10 %): 50 000 samples and eight blocks 421 -> 246, 20 000 and eight 139 -> 83, one 141 -> 74, 12 000 and four 71 -> 47,
+// 6000 and three 32 -> 23.  A trip at 50 000 takes 24.6 us in a copy that keeps clocks: candidates 1.9, first exchange 5.0, the
+// picks 3.4, their rows and lists 2.0, second exchange 4.1, the lists' rows 6.1, the rest 1.2; an instruction of a wave
 // takes some seven cycles here, so the picks' and the exchanges' arithmetic counts as much as the trips through memory.
 // The tags, banks and bounded waits of the exchanges are those of multi_wg_kernels.hip; a post has sixteen pieces.
 // Included by rcd_lib.hip after resident_kernels.hip.
