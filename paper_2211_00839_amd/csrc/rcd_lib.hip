@@ -471,10 +471,11 @@ struct SlicedInc {
 // loops in memory took one class of 50 000 586, of 12 000, four 133, of 6000, one 43; 20 of 8000, four 89.
 // (Mixtures and single clouds of 4 to 512 features gain alike.  Samples with copies gain less or lose, since a guess at the copy of a
 // pick fails and exact copies tie (a slice knows two candidates of a tie): every sample with one near copy / one exact copy / 50 points
-// repeated, two picks to a trip or one workgroup against this: one of 6000, one block 39 / 37 / 33 against 40 / 50 / 36, four 34 / 34 / 38 against
-// 33 / 36 / 37, eight 37 / 37 / 39 against 29 / 32 / 40, one of 20 000, eight 139 / 137 / 125 against 99 / 107 / 133; ten of 6000, three
-// 39 / 39 / 48 against 45 / 48 / 54, ten of 5000, five 38 / 38 / 27 against 33 / 38 / 37, eight 43 / 40 / 28 against 40 / 42 / 39, sixteen
-// 56 / 53 / 34 against 41 / 44 / 44; 60 of 6000, four 76 / - / 75 against 85 / - / 92.  Nothing on the host can tell.)
+// repeated, two picks to a trip or one workgroup against this: one of 6000, one block 39 / 37 / 33 against 40 / 48 / 32, four 34 / 34
+// / 38 against 34 / 36 / 33, eight 37 / 37 / 39 against 29 / 32 / 36, one of 20 000, eight 139 / 137 / 125 against 98 / 106 / 122; ten
+// of 6000, three 39 / 39 / 48 against 45 / 48 / 50, ten of 5000, five 38 / 38 / 27 against 33 / 38 / 34, eight 43 / 40 / 28 against 40
+// / 42 / 36, sixteen 56 / 53 / 34 against 41 / 44 / 41; 60 of 6000, four 76 / - / 75 against 85 / - / 89.  Nothing on the host can
+// tell.)
 // Slices of 1024 samples where there are compute units for them, one workgroup to a unit, else of 2048; where there are not even
 // those, the loops in memory serve (rules::slice_least()).  Slices of more than 1024 with more than eight blocks keep two picks to a
 // trip (choose()).

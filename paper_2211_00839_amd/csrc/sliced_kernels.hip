@@ -440,16 +440,14 @@ rcd_k_inc_steps_sliced(RcdClass *__restrict__ classes, RcdPlan *__restrict__ pla
             // how many of the class's are wanted (without guesses only what other blocks' picks take is to be made up for) and posted
             const int need = ahead == 0 ? min(nb, 3) : nb == 1 ? 1 + ahead : nb == 2 ? 6 : nb <= 4 ? 4 : 3;
             const int share = nb > 4 || need <= 2 ? 2 : nb > 2 || need <= 4 ? 4 : 8;
-            Slot a = sh.slots[k][lane >> 5][lane & 31], p = Slot{0u, 0u, -1, 0};
-            bool known = true;
+            Slot a = sh.slots[k][lane >> 5][lane & 31], p = Slot{KEY_UNKNOWN, 0u, -1, 0};
             for (int g = 0; g < share; ++g) {
                 const int src = best_lane(a.hi, a.lo, a.v);
-                const unsigned hi = known ? (unsigned)__builtin_amdgcn_readlane((int)a.hi, src) : KEY_UNKNOWN;
-                const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)a.lo, src);
+                const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)a.hi, src), lo = (unsigned)__builtin_amdgcn_readlane((int)a.lo, src);
                 const int v = __builtin_amdgcn_readlane(a.v, src);
                 if (lane == g) p = Slot{hi, lo, v, 0};
+                if (src >= 32) break;            // (a row's second is gone: its third is not known)
                 if (lane == src) a.hi = 0u;
-                known = known && src < 32;       // (a row's second is gone: its third is not known)
             }
             int got;
             if (share == 2) got = class_best<2>(x, lane, pl.wave * 2, p, need, sh.list[pl.wave]);
