@@ -67,7 +67,7 @@ template <typename Pitch, typename Slice> Slices slices(const Pitch &pitch, int 
 constexpr int SLICE_WIDEST = 2048, SLICES_MOST = 64, SLICES_MOST_PAIRS = 32;
 
 // 0 where the classes of a launch are not cut into slices, else the least samples of a slice: 1024 where there are compute units for
-// that, one workgroup to a unit, else 2048.  min_n, wide_n: sliced_from() without and with `wide`; given: samples of a slice, 0 to
+// that, one workgroup to a unit, else 2048.  min_n, wide_n: sliced_from() without and with `wide` (no matter for one class); given: samples of a slice, 0 to
 // choose; most, most_pairs: slices of a class at most; wgs: workgroups of the launch at most.
 template <typename Size, typename Pitch>
 int slice_least(const Size &size, const Pitch &pitch, int classes, int K, int cus, int min_n, int wide_n, int given = 0,

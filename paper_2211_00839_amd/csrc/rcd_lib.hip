@@ -492,7 +492,7 @@ SlicedInc plan_sliced(const std::vector<RcdClass> &cls, int cus)
     auto pitch = [&](int i) { return cls[i].ld; };
     const int least = rules::slice_least([&](int i) { return cls[i].n; }, pitch, ncls, K, cus,
                                          env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, K), 0, 0x7fffffff),
-                                         env_int("RCD_MW_MIN_N", rules::sliced_from(ncls, K, true), 0, 0x7fffffff), given, most, most_pairs,
+                                         ncls > 1 ? rules::sliced_from(ncls, K, true) : 0, given, most, most_pairs,
                                          RCD_MAX_SWEEP_WGS);
     if (least == 0) return none;
     const int w_max = std::min(least > 1024 && K > 8 ? most_pairs : most, cus / ncls);

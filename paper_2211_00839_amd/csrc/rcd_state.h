@@ -91,7 +91,9 @@ struct RcdClass {
 // Exchange area of the multi-workgroup step loops, in ints from RcdClass::mwbuf (zeroed when a call starts).
 enum {
     MW_SLOT = 0,                                 // 2 banks x RCD_MW_MAX slots x 16 ints: a workgroup's post (four pieces
-                                                 // of three ints and a tag: the post proper, then up to three list entries)
+                                                 // of three ints and a tag: the post proper, then up to three list entries).  The
+                                                 // sliced loop with up to eight picks, whose posts are elsewhere, keeps its count of
+                                                 // guesses in the first int from launch to launch
     MW_SLOT_INTS = 16,
     MW_PEND = MW_SLOT + 2 * MW_SLOT_INTS * RCD_MW_MAX,   // RCD_KMAX x RCD_SLICES_MAX: segment lengths of block k's pending list
     MW_END = MW_PEND + RCD_KMAX * RCD_SLICES_MAX
